@@ -59,8 +59,19 @@ typedef enum {
   PSF_EUNSUPPORTED = -4  /* current device is not gfx950 / feature absent */
 } psf_status;
 
-/* Arithmetic of the patch contraction.  Phase arguments are always formed
- * and reduced to turns in FP64; sin/cos, D_k and accumulation are FP32.
+/* Arithmetic of the patch contraction.  A patch is evaluated in one of two
+ * forms, chosen by K and the patch size (the faster one):
+ *  - dense, for few bins: every bin at every pixel, phase factors formed in
+ *    FP64 turns, products in the arithmetic below, FP32 accumulation;
+ *  - gridded, for many bins (from K = 24576 on, patches of up to 1044 pixels
+ *    a side): the same sum as a non-uniform Fourier transform, each bin
+ *    spread onto a uv grid with a kernel of 9 x 9 cells (products in the
+ *    arithmetic below, sums in FP32 and fixed point), then FP64 transforms.
+ *    Aliasing is at most 3.8e-8 of a term; measured errors are 5e-9 rms and
+ *    up to 1.5e-7 of the peak, below the dense form's.  A bin whose W D or
+ *    u', v' is not finite makes every pixel NaN.
+ * PSF_PLAIN_BF16 is always dense, PSF_MIXED_FP16 and PSF_SR_FP16 always
+ * gridded.
  * Accuracy of the split forms: an operand value v is carried as hi + lo
  * (16 significant bits in BF16, 22 in FP16), and one term's product is off
  * by up to 3 * 2^-16 (BF16) or 3 * 2^-22 (FP16) of |c a b|.  Over many
@@ -80,34 +91,26 @@ typedef enum {
   PSF_SR_FP16 = 5      /* see below: 1 product, for many bins */
 } psf_prec;
 
-/* PSF_MIXED_FP16: patches 65, 129 or 257 rows high (the symmetric form of
- * the contraction) with K >= 2^18 bins.  The column factors c_k b_kj are
- * split hi+lo in FP16 as in PSF_SPLIT_FP16; the row factors (cos and sin of
- * the row phase) are one FP16 value each, rounded stochastically: two
- * products instead of three.  A term is then off by up to 2^-11 of
- * |c a b|, a bound that does not keep the patch error below 1e-5 of the
- * peak by itself; the rounding is unbiased and its errors are independent
- * across bins (a bin's random word comes from its index), so the patch
- * error falls like 2^-12 sqrt(sum |c_k|^2) / |peak| (one standard
- * deviation): the largest over a 257 x 257 patch about 2e-6 of the peak at
- * 2^18 equally weighted bins with little decorrelation, and measured 5e-8 to
- * 3.3e-6 on the tests' workloads (K = 5.8M to 265M, sources to 3 deg), the
- * split forms' 7e-8 to 2.6e-6.  A patch of few effective bins (a few
- * heavily weighted bins) or whose peak is small against sum |c_k| (strong
- * decorrelation) has a larger error.  The result is deterministic: the
- * same inputs give the same bits.  Smaller K, and patches of other
- * heights, run as PSF_SPLIT_FP16; psf_patch_backward takes PSF_SPLIT_FP16
- * products for it.
+/* PSF_MIXED_FP16: patches 65, 129 or 257 rows high (and as many columns, to
+ * the block of 16) with K >= 2^18 bins.  The gridded form with each bin's row
+ * taps as one FP16 value each, rounded stochastically, and its column taps
+ * times c split hi + lo in FP16: two products instead of three.  A tap is
+ * then off by up to 2^-11 of itself, a bound that does not keep the patch
+ * error below 1e-5 of the peak by itself; the rounding is unbiased and its
+ * errors are independent across taps and bins (a tap's random word comes from
+ * its bin's index), so the patch error falls like 2^-12
+ * sqrt(sum |c_k|^2) / |peak| (one standard deviation, half of it at the
+ * patch's centre, 1.6 times at its edges).  A patch of few effective bins (a
+ * few heavily weighted bins) or whose peak is small against sum |c_k| (strong
+ * decorrelation) has a larger error.  The result is deterministic: the same
+ * inputs give the same bits.  Smaller K, and patches of other sizes, run as
+ * PSF_SPLIT_FP16; psf_patch_backward takes PSF_SPLIT_FP16 products for it.
  *
- * PSF_SR_FP16: as PSF_MIXED_FP16, and the column factors too are one
- * stochastically rounded FP16 value (their own random word per bin, so that
- * a term's two roundings are independent): one product per term product.
- * The same statistical bound with about 1.4 times the spread (two roundings
- * per term instead of one): measured 7e-8 to 6.3e-6 of the peak on the
- * tests' workloads (the largest on the precision workload's 2.96 deg
- * source, against a normaliser that is a lower bound of the patch's peak),
- * 6.7e-7 to 8.4e-7 over every pixel of the uniform-bin 257 x 257 PSF.  Same
- * conditions and fallbacks as PSF_MIXED_FP16. */
+ * PSF_SR_FP16: as PSF_MIXED_FP16, and the column taps times c too are one
+ * stochastically rounded FP16 value (random words of their own): one product.
+ * The same statistical bound with about 1.4 times the spread: 6.7e-7 to
+ * 8e-7 over every pixel of the uniform-bin 257 x 257 PSF.  Same conditions
+ * and fallbacks as PSF_MIXED_FP16. */
 
 /* Flag OR-ed into prec for psf_patch, psf_patch_batched and
  * psf_workspace_bytes: the normalised PSF [section 4, errors taken on PSFs
@@ -206,15 +209,15 @@ int psf_patch(const psf_obs* obs, const psf_src* h_src, const float* D, int prec
               float* P, void* ws, size_t ws_bytes, void* stream);
 
 /* Many sources per call [section 3.3: one PSF per source direction].
- * Sources are grouped by tile family (their patch size) and form, in groups
- * of at most 16 whose per-bin records fit 16 GiB: each source of a group
- * gets K records of 40 bytes (u', v' in FP64, the 16-pixel phase steps of
- * both axes, W D), written by one decorrelation launch per source; one
- * persistent contraction launch then runs every (source, tile, k-slice)
- * work item of the group, and one finalise launch writes its patches.  So
- * a call costs 3 launches per group, plus one per source, and its
- * workspace holds one group's records: where K is large (2.65e8 bins take
- * 10.6 GB per source) a group holds one source.  h_srcs (host) fixes sizes,
+ * Sources are grouped by form and size (grid or tile family), in groups of
+ * at most 16.  Gridded sources (boxcar averaging) share four launches per
+ * group: the decorrelation factors are formed while spreading, and the
+ * workspace holds one group's grids.  Otherwise a group's per-bin records
+ * fit 16 GiB: each source gets K records of 40 bytes (u', v' in FP64, the
+ * 16-pixel phase steps of both axes, W D), written by one decorrelation
+ * launch per source; one persistent contraction launch (or the gridded
+ * form's four) then runs the group, and one finalise launch writes its
+ * patches.  h_srcs (host) fixes sizes,
  * offsets and the plan; d_srcs (device, same n_src entries with the same
  * nl, nm, out_off) supplies directions and grids at run time, so a
  * captured graph can be replayed with new directions and grids (any grid

@@ -1,0 +1,957 @@
+// The gridded form of the patch contraction, for many bins.
+//
+// P_ij = 2 Re sum_k c_k exp(2 pi i (u'_k x_i + v'_k y_j)) on a regular pixel
+// grid is a non-uniform discrete Fourier transform: with x_i = x_h + (i - h) dl
+// and h = nl / 2, bin k contributes at the frequency u'_k dl (in turns, modulo
+// 1) of a transform of nl modes, and likewise along y.  So instead of
+// evaluating every bin at every pixel, each bin is spread with a smooth kernel
+// of 9 x 9 cells onto a uv grid of ml x mm cells (at least 1.96 cells per
+// pixel), and the patch is the inverse DFT of that grid divided by the
+// kernel's transform.  Work per bin: 81 cells instead of nl nm pixels.
+//
+// Kernel: Kaiser-Bessel of width 9 and shape parameter 2.3 x 9, as a
+// polynomial of degree 8 in the bin's offset from its cell per tap (even and
+// odd parts shared by mirrored taps).  The transform divided out is that of
+// the polynomials as coded, so only aliasing remains: at most 3.8e-8 of a
+// term over the whole patch (and 1.2e-7 with the FP32 evaluation, 2.5e-8
+// rms, which differs from bin to bin and averages out).
+//
+//   k_grid_init    zero cells; largest |c| (scales the fixed point and the FP16
+//                  operands)
+//   k_grid_spread  the bins onto the cells (below)
+//   k_grid_rows    inverse DFT along the columns of every grid row, FP64,
+//                  the nm modes kept, transposed
+//   k_grid_cols    inverse DFT along the rows, the nl modes, real part
+//
+// Spreading runs on the matrix cores: the bins of one wave whose taps lie in
+// one window of 16 x 16 cells are a contraction over bins of their row taps
+// (16 x bins) and their column taps times c (bins x 16, real and imaginary).
+// Successive bins of a baseline lie within a fraction of a cell of each
+// other, so a wave takes 64 bins of one baseline, a rectangle of time and
+// frequency bins shaped by how fast the track moves along each, which one or
+// two windows usually hold; bins outside the current window wait for the
+// next one, so any track is spread correctly.  Windows are folded into a
+// tile of the workgroup's part of the track in LDS, tiles into the grid, in
+// fixed point: integer sums do not depend on their order, so the result is
+// the same on every run although the workgroups meet in the grid through
+// atomics.
+//
+// FUSED, the boxcar case, forms D_k in the same kernel: bins leave no records
+// in memory (40 bytes each way, 10.6 GB per source at K = 265M).
+//
+// Measured (one 257 x 257 patch, K = 5.8M, stochastic FP16): 360 us per call,
+// spreading 340, against 1400 us of the dense contraction it replaced (FP32
+// 400 against 7510); per source at K = 265M 7.1 ms against 37 on average.  Bound: vector issue (two thirds of the cycles at K = 5.8M with 40
+// samples per bin: the samples' sines and cosines first, then the taps),
+// then LDS and the latency of the staging.
+#include <algorithm>
+
+#include "psf_device.hpp"
+#include "psf_grid.hpp"
+
+namespace psf {
+
+namespace {
+
+typedef __bf16 g_bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 g_f16x8 __attribute__((ext_vector_type(8)));
+typedef float g_f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t g_u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) uint8_t g_lds;
+
+constexpr int kW = 9;             // taps per axis
+constexpr int kWin = 16;          // cells per axis of a window
+constexpr int kSlack = kWin - kW; // a window holds anchors 0 .. kSlack past its origin
+constexpr int kTileCells = 2048;  // cells of a workgroup's LDS tile
+constexpr int kWaves = 4;
+constexpr int kThreads = 64 * kWaves;
+constexpr int kTileSide = 45;     // a tile grows to about this side when its chunk leaves room
+constexpr int kTabRows = 1024;    // samples of a chunk whose projections sit in LDS
+constexpr int kTabFreq = 512;     // frequency bins whose centre frequencies do
+constexpr int kRun = 8;           // batches of 64 bins summed in FP32 before a window is folded (2^9 bins)
+constexpr int kInitBlocks = 512;
+constexpr int kMargin = 1;        // cells added around a tile's sampled extent
+
+// Operand staging of one wave: 16 rows (taps' cells) x 64 bins.  16-bit
+// forms: a plane of hi and one of lo, rows of 128 bytes padded by 16 so that
+// eight rows' 16-byte reads fall on distinct banks; FP32: one plane, rows of
+// 256 + 16 bytes.
+constexpr int kRow16 = 144, kPlane16 = 16 * kRow16, kRow32 = 272;
+constexpr int kStage = 5120;  // bytes per wave: the operand, up to a whole number of 16-byte stores per lane
+
+// The taps' polynomials times kTapScale: tap r and tap 8 - r are
+// E_r(f^2) +- f O_r(f^2), f = position - nearest cell in [-1/2, 1/2].
+constexpr float kTapScale = 256.0f;
+constexpr float kE[5][5] = {{2.002013025e-05f, 6.172497524e-04f, 1.670259167e-03f, 7.180632092e-04f, -4.018611799e-05f},
+                            {5.964126438e-03f, 4.019754753e-02f, 1.738595404e-02f, -2.347377595e-03f, -3.952386396e-05f},
+                            {1.223278940e-01f, 2.172718942e-01f, -3.498638421e-02f, -2.999314456e-04f, 5.284860381e-04f},
+                            {6.036517024e-01f, -8.782624267e-03f, -4.322065413e-02f, 1.082540862e-02f, -1.368907047e-03f},
+                            {1.000000000e+00f, -4.986084700e-01f, 1.183041185e-01f, -1.779340580e-02f, 1.820146339e-03f}};
+constexpr float kO[4][4] = {{-1.689896308e-04f, -1.282629906e-03f, -1.401485410e-03f, -1.478675258e-04f},
+                            {-2.372954227e-02f, -3.653368726e-02f, -1.952710212e-03f, 1.121683628e-03f},
+                            {-2.715461552e-01f, -4.635402188e-02f, 2.174760029e-02f, -2.793780062e-03f},
+                            {-6.170070171e-01f, 2.074417621e-01f, -3.204887360e-02f, 2.866369672e-03f}};
+// 1 / (transform of the kernel at frequency xi), a polynomial in (4 xi)^2
+// for |xi| <= 0.2552 (relative error 1.3e-13)
+constexpr double kInvHat[12] = {4.05856101315633433e-01, 4.66157209092129265e-01, 2.80608321608683930e-01,
+                                1.18036114521012508e-01, 3.90287000662849701e-02, 1.08188056068415379e-02,
+                                2.61583858432692246e-03, 5.72886663654686968e-04, 1.06769820665924113e-04,
+                                2.69661860537872370e-05, 1.03610339097734577e-07, 1.69455818779958946e-06};
+
+// Cells hold c / 2^ecm (|.| <= sqrt 2) times the taps in fixed point:
+// kAccBits fractional bits in a window's accumulators (two tap scales and
+// the coefficients' own), kTileBits - log_tile in a tile of at most 2^log_tile
+// bins.
+constexpr int kCoefBits = 4;
+constexpr int kAccBits = 8 + 8 + kCoefBits;
+constexpr int kTileBits = 30;
+__host__ __device__ constexpr int cell_bits(int log_k) { return 61 - log_k; }
+
+// State of one source, behind its grids: whether a bin was not finite (the
+// patch is then NaN); the init blocks' maxima; the spreading workgroups' sums
+// of Re c (fused form).
+struct UvGridState {
+  uint32_t poison;
+  uint32_t pad[63];
+  uint32_t maxima[kInitBlocks];
+  double peak[kGridMaxWgs];
+};
+
+template <class S>
+__device__ __forceinline__ unsigned long long* cells_of(const S& s) {
+  return reinterpret_cast<unsigned long long*>(s.work);
+}
+
+__device__ __forceinline__ double inv_hat(double xi) {
+  const double z = 16.0 * xi * xi;
+  double v = kInvHat[11];
+#pragma unroll
+  for (int q = 10; q >= 0; --q) v = fma(v, z, kInvHat[q]);
+  return v;
+}
+
+// The nine taps of a bin at offset f from its nearest cell.
+__device__ __forceinline__ void taps(float f, float t[kW]) {
+  const float g = f * f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float e = kTapScale * kE[r][4], o = kTapScale * kO[r][3];
+#pragma unroll
+    for (int q = 3; q >= 0; --q) e = __builtin_fmaf(e, g, kTapScale * kE[r][q]);
+#pragma unroll
+    for (int q = 2; q >= 0; --q) o = __builtin_fmaf(o, g, kTapScale * kO[r][q]);
+    t[r] = __builtin_fmaf(f, o, e);
+    t[8 - r] = __builtin_fmaf(-f, o, e);
+  }
+  float e = kTapScale * kE[4][4];
+#pragma unroll
+  for (int q = 3; q >= 0; --q) e = __builtin_fmaf(e, g, kTapScale * kE[4][q]);
+  t[4] = e;
+}
+
+// Position of frequency f step (turns) on a torus of M cells: nearest cell
+// (0 .. M - 1) and the offset from it; finite input only.
+__device__ __forceinline__ void torus(double f, double step, int M, int* cell, float* off) {
+  double t = f * step;
+  t = (t - floor(t)) * M;
+  const double n = rint(t);
+  *off = static_cast<float>(t - n);
+  const int i = static_cast<int>(n);
+  *cell = i >= M ? i - M : i;
+}
+
+__device__ __forceinline__ int wrap(int d, int M) { return d < 0 ? d + M : d; }  // d > -M
+
+typedef const __attribute__((address_space(4))) UvGridSrc karg_gsrc;
+__device__ __forceinline__ karg_gsrc& gsrc(int s) {
+  typedef const __attribute__((address_space(4))) uint8_t karg_byte;
+  return ((karg_gsrc*)((karg_byte*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(UvGridArgs, src)))[s];
+}
+
+__device__ __forceinline__ UvGridState* state_of(const UvGridArgs& a, karg_gsrc& s) {
+  return reinterpret_cast<UvGridState*>(s.work + (static_cast<size_t>(a.ml) * a.mm + static_cast<size_t>(a.ml) * s.nm) *
+                                                   sizeof(double2));
+}
+
+// The exponent e for which 2^e exceeds every |Re c|, |Im c| of a source; each
+// wave for itself.
+__device__ __forceinline__ int max_exponent(karg_gsrc& s, int n) {
+  uint32_t m = 0;
+  for (int q = threadIdx.x & 63; q < n; q += 64) m = max(m, s.maxima[q]);
+  for (int o = 32; o > 0; o >>= 1) m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
+  return static_cast<int>(__builtin_amdgcn_readfirstlane(m) >> 23) - 126;
+}
+
+}  // namespace
+
+// Zeroes the cells and finds the largest |.| of the n floats that scale a
+// source: its coefficients' parts, or in the fused form the weights (|D| <= 1;
+// one pass, by source 0's blocks, for all sources).  Block q leaves its
+// largest as bits in maxima[q]; later kernels take the largest of those.
+__global__ __launch_bounds__(256) void k_grid_init(UvGridArgs a) {
+  karg_gsrc& s = gsrc(blockIdx.y);
+  const int64_t id = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, step = static_cast<int64_t>(gridDim.x) * 256;
+  g_u32x4* q = reinterpret_cast<g_u32x4*>(s.work);
+  const int64_t ncell = static_cast<int64_t>(a.ml) * a.mm;
+  for (int64_t i = id; i < ncell; i += step) q[i] = g_u32x4{0, 0, 0, 0};
+  if (id == 0) state_of(a, s)->poison = 0;
+  if (a.fused && blockIdx.y > 0) return;
+  const uint32_t* c = reinterpret_cast<const uint32_t*>(a.fused ? a.o.W : reinterpret_cast<const float*>(s.c));
+  const int64_t n = a.fused ? a.o.K : 2 * a.o.K;
+  uint32_t m = 0;
+  // 16 bytes per load where the array allows, its last n mod 4 words apart
+  const bool wide = (reinterpret_cast<uintptr_t>(c) & 15) == 0;
+  const int64_t n4 = wide ? n / 4 : 0;
+  const g_u32x4* c4 = reinterpret_cast<const g_u32x4*>(c);
+#pragma unroll 8
+  for (int64_t k = id; k < n4; k += step) {
+    const g_u32x4 v = c4[k];
+    m = max(max(max(m, v[0] & 0x7fffffffu), max(v[1] & 0x7fffffffu, v[2] & 0x7fffffffu)), v[3] & 0x7fffffffu);
+  }
+  for (int64_t k = 4 * n4 + id; k < n; k += step) m = max(m, c[k] & 0x7fffffffu);
+  for (int o = 32; o > 0; o >>= 1) m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
+  __shared__ uint32_t w[4];
+  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) s.maxima[blockIdx.x] = max(max(w[0], w[1]), max(w[2], w[3]));
+}
+
+namespace {
+
+// How an operand is carried: FP32, split hi + lo in BF16 or FP16, or one
+// FP16 value rounded stochastically.
+constexpr uint32_t kWeyl = 0x9E3779B1u;
+enum Mode : int { kM32, kMBF16, kMFP16, kMSR };
+__host__ __device__ constexpr Mode row_mode(int prec) {
+  return prec == kFP32 ? kM32 : prec == kSplitBF16 ? kMBF16 : prec == kSplitFP16 ? kMFP16 : kMSR;
+}
+__host__ __device__ constexpr Mode col_mode(int prec) { return prec == kMixedFP16 ? kMFP16 : row_mode(prec); }
+
+// One axis' nine operand values of a bin into the stage, at rows row0 ..
+// row0 + 8, column `lane` (rw: the bin's random word).
+template <Mode M>
+__device__ __forceinline__ void stage_taps(g_lds* st, int row0, int lane, const float t[kW], uint32_t rw) {
+  if constexpr (M == kM32) {
+    typedef __attribute__((address_space(3))) float lds_f32;
+    g_lds* p = st + row0 * kRow32 + lane * 4;
+#pragma unroll
+    for (int r = 0; r < kW; ++r) *reinterpret_cast<lds_f32*>(p + r * kRow32) = t[r];
+  } else {
+    typedef __attribute__((address_space(3))) uint16_t lds_u16;
+    g_lds* p = st + row0 * kRow16 + lane * 2;
+#pragma unroll
+    for (int r = 0; r < kW; r += 2) {
+      const bool two = r + 1 < kW;
+      const float v0 = t[r], v1 = two ? t[two ? r + 1 : r] : 0.f;
+      uint32_t hi, lo = 0;
+      if constexpr (M == kMBF16) {
+        hi = pack_bf16x2(v0, v1);
+        lo = pack_bf16x2(v0 - bf16_lo_to_f32(hi), v1 - bf16_hi_to_f32(hi));
+      } else if constexpr (M == kMFP16) {
+        hi = pack_f16x2(v0, v1);
+        lo = f16_lo_pair(hi, v0, v1);
+      } else {
+        // a word of its own for every tap, stepped by the golden ratio
+        f16x2_t h = {0, 0};
+        h = __builtin_amdgcn_cvt_sr_f16_f32(h, v0, rw + r * kWeyl, false);
+        if (two) h = __builtin_amdgcn_cvt_sr_f16_f32(h, v1, rw + (r + 1) * kWeyl, true);
+        hi = __builtin_bit_cast(uint32_t, h);
+      }
+      *reinterpret_cast<lds_u16*>(p + r * kRow16) = static_cast<uint16_t>(hi);
+      if (M != kMSR) *reinterpret_cast<lds_u16*>(p + r * kRow16 + kPlane16) = static_cast<uint16_t>(lo);
+      if (two) {
+        *reinterpret_cast<lds_u16*>(p + (r + 1) * kRow16) = static_cast<uint16_t>(hi >> 16);
+        if (M != kMSR) *reinterpret_cast<lds_u16*>(p + (r + 1) * kRow16 + kPlane16) = static_cast<uint16_t>(lo >> 16);
+      }
+    }
+  }
+}
+
+template <Mode M>
+__device__ __forceinline__ void stage_clear(g_lds* st, int lane) {
+  typedef __attribute__((address_space(3))) g_u32x4 lds_u32x4;
+  constexpr int n = M == kMSR ? kPlane16 : M == kM32 ? 16 * kRow32 : 2 * kPlane16;
+  static_assert((n + 1023) / 1024 * 1024 <= kStage, "the stage holds the operand");
+#pragma unroll
+  for (int q = 0; q < (n + 1023) / 1024; ++q)
+    *reinterpret_cast<lds_u32x4*>(st + q * 1024 + lane * 16) = g_u32x4{0, 0, 0, 0};
+}
+
+// A wave's LDS operations run in order; this keeps the compiler's order too.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The operand fragments of the staged 64 bins: 16-bit forms two chunks of 32
+// bins x (hi, lo), one value each in the stochastic form; FP32 four groups of
+// 16 bins.
+struct Frags {
+  g_u32x4 v[4];
+};
+template <Mode M>
+__device__ __forceinline__ Frags stage_read(const g_lds* st, int lane) {
+  typedef const __attribute__((address_space(3))) g_u32x4 lds_u32x4;
+  const int lr = lane & 15, lg = lane >> 4;
+  Frags f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    if (M == kM32)
+      f.v[q] = *reinterpret_cast<lds_u32x4*>(st + lr * kRow32 + q * 64 + lg * 16);
+    else if (M != kMSR || (q & 1) == 0)
+      f.v[q] = *reinterpret_cast<lds_u32x4*>(st + (q & 1) * kPlane16 + lr * kRow16 + (q >> 1) * 64 + lg * 16);
+  }
+  return f;
+}
+
+template <Mode M>
+__device__ __forceinline__ g_f32x4 mma16(g_u32x4 a, g_u32x4 b, g_f32x4 c) {
+  if constexpr (M == kMBF16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(g_bf16x8, a), __builtin_bit_cast(g_bf16x8, b), c,
+                                                   0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(g_f16x8, a), __builtin_bit_cast(g_f16x8, b), c, 0,
+                                                  0, 0);
+}
+
+// acc += A B over the staged bins (go: the lanes whose bins take part).
+template <Mode MA, Mode MB>
+__device__ __forceinline__ g_f32x4 contract_frags(const Frags& a, const Frags& b, uint64_t go, g_f32x4 acc) {
+  if constexpr (MA == kM32) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (((go >> (16 * q)) & 0xffff) == 0) continue;  // none of these 16 bins in this window
+      const g_f32x4 av = __builtin_bit_cast(g_f32x4, a.v[q]), bv = __builtin_bit_cast(g_f32x4, b.v[q]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], bv[e], acc, 0, 0, 0);
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      acc = mma16<MB>(a.v[2 * h], b.v[2 * h], acc);
+      if (MB != kMSR) acc = mma16<MB>(a.v[2 * h], b.v[2 * h + 1], acc);
+      if (MA != kMSR) acc = mma16<MB>(a.v[2 * h + 1], b.v[2 * h], acc);
+    }
+  }
+  return acc;
+}
+
+__device__ __forceinline__ uint32_t mix_word(uint32_t h) {
+  h ^= h >> 16;
+  h *= 0x85EBCA6Bu;
+  h ^= h >> 13;
+  h *= 0xC2B2AE35u;
+  h ^= h >> 16;
+  return h;
+}
+
+// A workgroup's tile of the grid in LDS.
+struct Tile {
+  int ox, oy, bx, by;  // origin (cells of the torus) and extent; bx = 0: none
+};
+
+struct Cells {
+  unsigned long long* g;
+  int ml, mm, shift;
+};
+
+__device__ __forceinline__ void add_cell(const Cells& c, int i, int j, int part, int v) {
+  if (v == 0) return;
+  const int64_t w = static_cast<int64_t>(v) << c.shift;
+  __hip_atomic_fetch_add(&c.g[2 * (static_cast<int64_t>(i) * c.mm + j) + part], static_cast<unsigned long long>(w),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// x to fixed point, up or down at random with x as the mean (h: random word).
+// Rounded to nearest, the smallest cells of a window, the kernel's tails,
+// would lose up to half a unit each time, always towards zero.
+__device__ __forceinline__ int to_int(float x, float scale, uint32_t h) {
+  const float r = __builtin_bit_cast(float, (h >> 9) | 0x3f800000u);  // [1, 2)
+  return static_cast<int>(floorf(__builtin_fmaf(x, scale, r))) - 1;
+}
+
+// A window's accumulators (origin wx, wy) into the tile, cells outside the
+// tile straight into the grid.  h: a random word of the fold.
+__device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, int* tre, int* tim, int wx, int wy,
+                                            float to_fixed, int lane, uint32_t h, const g_f32x4& re, const g_f32x4& im) {
+  const int j = lane & 15, i0 = 4 * (lane >> 4);
+  const int rx = wrap(wx - t.ox, cells.ml), ry = wrap(wy - t.oy, cells.mm);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int vr = to_int(re[e], to_fixed, h), vi = to_int(im[e], to_fixed, h + 0x9E3779B1u);
+    h += 2 * 0x9E3779B1u;
+    const int ti = rx + i0 + e, tj = ry + j;
+    if (ti < t.bx && tj < t.by) {
+      __hip_atomic_fetch_add(&tre[ti * t.by + tj], vr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_fetch_add(&tim[ti * t.by + tj], vi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+      int gi = wx + i0 + e, gj = wy + j;
+      if (gi >= cells.ml) gi -= cells.ml;
+      if (gj >= cells.mm) gj -= cells.mm;
+      add_cell(cells, gi, gj, 0, vr);
+      add_cell(cells, gi, gj, 1, vi);
+    }
+  }
+}
+
+__device__ __forceinline__ int first_lane(uint64_t m) { return __builtin_ctzll(m); }
+__device__ __forceinline__ int last_lane(uint64_t m) { return 63 - __builtin_clzll(m); }
+
+// Where a window of one axis starts: it holds the anchor a of the first
+// waiting bin and extends towards the anchor b of the last.
+__device__ __forceinline__ int window_origin(int a, int b, int M) {
+  int d = b - a;
+  if (d > M / 2) d -= M;
+  if (d < -M / 2) d += M;
+  const int o = d > kSlack ? a : d < -kSlack ? a - kSlack : a + min(d, 0) - (kSlack - (d < 0 ? -d : d)) / 2;
+  return o < 0 ? o + M : o;
+}
+
+// What a chunk of one baseline's bins needs: time rows t0 .. t0 + rows of nf
+// frequency bins, of which the bins [la, lb) (counted from the baseline's
+// first) belong to the workgroup.
+struct Chunk {
+  int64_t base, la, lb, t0;
+  int b, nf, nt, nc, rows;
+};
+
+// Sum over one bin's samples of exp(-2 pi i phi), phi = (A_t nu_c - A_k nu_k)
+// / c: channels in groups of four whose frequencies sit in registers, the
+// projections A_t from the chunk's table in LDS (tab, row t of time bin tr at
+// tab[t rows + tr]) or, for bins too long for it, from the rows themselves.
+// The products round separately, so that identical rows cancel exactly.
+template <int NCH>
+__device__ __forceinline__ void sum_group(const double* tab, int pitch, int ntu, int ntl, const double nu[4], int nch,
+                                          double aknu, float* sre, float* sim) {
+#pragma clang fp contract(off)
+  for (int t = 0; t < ntu; ++t) {
+    const double at = tab[t * pitch];
+    if (t < ntl) {
+#pragma unroll
+      for (int j = 0; j < (NCH == 0 ? 4 : NCH); ++j) {
+        if (NCH == 0 && j >= nch) continue;
+        const cf32 e = expi_turns_hw(-((at * nu[j] - aknu) * kInvCLight));
+        *sre += e.re;
+        *sim += e.im;
+      }
+    }
+  }
+}
+
+// Decorrelation factor of this lane's bin (time bin tr of the chunk,
+// channels c0 .. c1), as k_decorr forms it.
+__device__ __forceinline__ cf32 bin_factor(const ObsView& o, const Chunk& ch, const double* tab, bool in, int tr, int c0,
+                                           int c1, double aknu, double l0, double m0, double lw) {
+#pragma clang fp contract(off)
+  float sre = 0.f, sim = 0.f;
+  const int64_t first = (ch.t0 + tr) * ch.nt;
+  const int ntl = in ? static_cast<int>(min(static_cast<int64_t>(ch.nt), o.n_t - first)) : 0;
+  for (int cb = c0; __any(in && cb < c1); cb += 4) {
+    const int nch = in ? min(4, c1 - cb) : 0;  // <= 0: none left for this lane
+    double nu[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) nu[j] = o.freq[max(0, min(cb + max(0, min(j, nch - 1)), o.n_ch - 1))];
+    const int nl = nch > 0 ? ntl : 0;
+    if (tab != nullptr) {
+      const uint64_t act = __ballot(nl > 0);
+      if (act == __ballot(nl > 0 && nch == 1)) sum_group<1>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+      else if (act == __ballot(nl > 0 && nch == 2)) sum_group<2>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+      else if (act == __ballot(nl > 0 && nch == 4)) sum_group<4>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+      else sum_group<0>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+    } else {
+      for (int t = 0; t < nl; ++t) {
+        const double* row = o.uvw + 3 * (static_cast<int64_t>(ch.b) * o.n_t + first + t);
+        const double at = row[0] * l0 + row[1] * m0 + row[2] * lw;
+        for (int j = 0; j < nch; ++j) {
+          const cf32 e = expi_turns_hw(-((at * nu[j] - aknu) * kInvCLight));
+          sre += e.re;
+          sim += e.im;
+        }
+      }
+    }
+  }
+  const float inv = in ? 1.0f / static_cast<float>(ntl * (c1 - c0)) : 0.f;
+  return {sre * inv, sim * inv};
+}
+
+// Waits for this workgroup's LDS traffic only: __syncthreads also waits for
+// the atomics into the grid, whose results nobody here reads.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+}  // namespace
+
+// FUSED: the decorrelation factors are formed here from the samples (boxcar
+// averaging), else u', v' and c come from records.
+template <int PREC, bool FUSED>
+__global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
+  constexpr Mode MA = row_mode(PREC), MB = col_mode(PREC);
+  __shared__ int tre[kTileCells], tim[kTileCells];
+  __shared__ __attribute__((aligned(16))) uint8_t stage_raw[kWaves * kStage];
+  __shared__ double tab[FUSED ? kTabRows : 1], tabnu[FUSED ? kTabFreq : 1];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  g_lds* st = (g_lds*)stage_raw + wave * kStage;
+  karg_gsrc& s = gsrc(blockIdx.y);
+  const BinRec* rec = s.rec;
+  const float2* cf = s.c;
+  const ObsView& o = a.o;
+  double l0 = s.l0, m0 = s.m0, l_first = s.l_first, m_first = s.m_first, dl = s.dl, dm = s.dm;
+  if (s.dir != nullptr) {
+    l0 = s.dir[0];
+    m0 = s.dir[1];
+    l_first = s.dir[2];
+    m_first = s.dir[3];
+    dl = s.dir[4];
+    dm = s.dir[5];
+  }
+  const double n0 = sqrt(1.0 - l0 * l0 - m0 * m0), lw = n0 - 1.0, l0n = l0 / n0, m0n = m0 / n0;
+  // offsets from the source of the pixels that modes (0, 0) stand for;
+  // nothing to shift where they are rounding of a grid centred on the source
+  const double xh = (l_first + (s.nl / 2) * dl) - l0, yh = (m_first + (s.nm / 2) * dm) - m0;
+  const bool shift = !(fabs(xh) <= 1e-12 * fabs(dl) && fabs(yh) <= 1e-12 * fabs(dm));
+  UvGridState* state = state_of(a, s);
+  const int ecm = max_exponent(s, a.n_init);
+  const float to_fixed = ldexpf(1.0f, kTileBits - a.log_tile - kAccBits);
+  const Cells cells{cells_of(s), a.ml, a.mm, cell_bits(a.log_k) - (kTileBits - a.log_tile)};
+  Tile tile{0, 0, 0, 0};
+  int tile_bins = 0;  // bins folded into the tile since it was last empty
+  double peak = 0.0;  // this lane's share of sum Re c
+  uint32_t fold = mix_word((blockIdx.x * kWaves + wave) * 64 + lane);  // random word of the next fold
+  for (int q = threadIdx.x; q < kTileCells; q += kThreads) tre[q] = tim[q] = 0;
+  lds_barrier();
+
+  // The tile into the grid, left zero; every wave has passed a barrier since
+  // its last fold.
+  auto flush_tile = [&]() {
+    for (int i = wave; i < tile.bx; i += kWaves) {
+      int gi = tile.ox + i;
+      if (gi >= a.ml) gi -= a.ml;
+      for (int j = lane; j < tile.by; j += 64) {
+        int gj = tile.oy + j;
+        if (gj >= a.mm) gj -= a.mm;
+        const int e = i * tile.by + j;
+        add_cell(cells, gi, gj, 0, tre[e]);
+        add_cell(cells, gi, gj, 1, tim[e]);
+        tre[e] = tim[e] = 0;
+      }
+    }
+    tile_bins = 0;
+  };
+
+  int64_t ka = static_cast<int64_t>(blockIdx.x) * a.wg_bins;
+  const int64_t kb = min(o.K, ka + a.wg_bins);
+  for (int b = ka < kb ? find_baseline(o.koff, o.n_bl, ka) : o.n_bl; ka < kb && b < o.n_bl; ++b) {
+    Chunk ch;
+    ch.b = b;
+    ch.base = o.koff[b];
+    const int64_t kend = b + 1 < o.n_bl ? min(kb, o.koff[b + 1]) : kb;
+    if (kend <= ka) continue;
+    ch.nt = max(1, o.bl_bin[2 * b]);
+    ch.nc = max(1, o.bl_bin[2 * b + 1]);
+    ch.nf = 1 + (o.n_ch - 1) / ch.nc;
+    ch.la = ka - ch.base;
+    ch.lb = kend - ch.base;
+    ka = kend;
+    const int64_t tb0 = o.tboff[b];
+    ch.t0 = ch.la / ch.nf;
+    const int64_t t1 = (ch.lb + ch.nf - 1) / ch.nf;
+    while (ch.t0 < t1) {
+      // Sample the track: 32 times x both ends of the band; the longest
+      // prefix whose extent fits the tile is this chunk (at most as many
+      // bins as the tile's fixed point allows and rows as the table holds).
+      int64_t left = t1 - ch.t0;
+      left = min(left, static_cast<int64_t>(max(1, (1 << a.log_tile) / ch.nf)));
+      if (FUSED && ch.nt <= kTabRows) left = min(left, static_cast<int64_t>(kTabRows / ch.nt));
+      const int nt = static_cast<int>(left);
+      const int smp = lane >> 1;
+      const int64_t tl = ch.t0 + (static_cast<int64_t>(nt - 1) * smp) / 31;
+      double pu, pv;
+      if constexpr (FUSED) {
+        const int f = (lane & 1) * (ch.nf - 1);
+        const double nu = bin_freq(o.freq, f * ch.nc, f * ch.nc + min(ch.nc, o.n_ch - f * ch.nc)) * kInvCLight;
+        const double* uc = o.uvw_c + 3 * (tb0 + tl);
+        pu = (uc[0] - uc[2] * l0n) * nu;
+        pv = (uc[1] - uc[2] * m0n) * nu;
+      } else {
+        const int64_t ls = min(max(tl * ch.nf + (lane & 1) * (ch.nf - 1), ch.la), ch.lb - 1);
+        pu = rec[ch.base + ls].up;
+        pv = rec[ch.base + ls].vp;
+      }
+      pu *= dl * a.ml;
+      pv *= dm * a.mm;
+      const double ru = __shfl(pu, 0), rv = __shfl(pv, 0);
+      const float x = static_cast<float>(pu - ru), y = static_cast<float>(pv - rv);
+      float xlo = fminf(x, __shfl_xor(x, 1)), xhi = fmaxf(x, __shfl_xor(x, 1));
+      float ylo = fminf(y, __shfl_xor(y, 1)), yhi = fmaxf(y, __shfl_xor(y, 1));
+#pragma unroll
+      for (int q = 2; q < 64; q <<= 1) {
+        const float p0 = __shfl_up(xlo, q), p1 = __shfl_up(xhi, q), p2 = __shfl_up(ylo, q), p3 = __shfl_up(yhi, q);
+        if (lane >= q) {
+          xlo = fminf(xlo, p0);
+          xhi = fmaxf(xhi, p1);
+          ylo = fminf(ylo, p2);
+          yhi = fmaxf(yhi, p3);
+        }
+      }
+      const float ex = ceilf(xhi - xlo) + (kW + 1 + 2 * kMargin), ey = ceilf(yhi - ylo) + (kW + 1 + 2 * kMargin);
+      const uint64_t fits = __ballot(ex * ey <= kTileCells && ex <= a.ml && ey <= a.mm && ch.nf <= (1 << a.log_tile));
+      Tile box{0, 0, 0, 0};
+      ch.rows = nt;
+      float vt;  // cells per time bin
+      const float vf = fmaxf(fabsf(__shfl(x, 1)), fabsf(__shfl(y, 1))) / max(1, ch.nf - 1);  // per frequency bin
+      if (fits & 1) {
+        const int sl = last_lane(fits), ss = sl >> 1;
+        ch.rows = static_cast<int>((static_cast<int64_t>(nt - 1) * ss) / 31) + 1;
+        vt = fmaxf(fabsf(__shfl(x, 2 * ss)), fabsf(__shfl(y, 2 * ss))) / max(1, ch.rows - 1);
+        box.bx = __builtin_amdgcn_readfirstlane(static_cast<int>(__shfl(ex, sl)));
+        box.by = __builtin_amdgcn_readfirstlane(static_cast<int>(__shfl(ey, sl)));
+        const double fx = floor(ru + __shfl(xlo, sl)) - (kW / 2 + kMargin);
+        const double fy = floor(rv + __shfl(ylo, sl)) - (kW / 2 + kMargin);
+        box.ox = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(fx - floor(fx / a.ml) * a.ml), 0), a.ml - 1));
+        box.oy = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(fy - floor(fy / a.mm) * a.mm), 0), a.mm - 1));
+      } else {
+        vt = fmaxf(fabsf(__shfl(x, 62)), fabsf(__shfl(y, 62))) / max(1, nt - 1);
+      }
+      ch.rows = __builtin_amdgcn_readfirstlane(ch.rows);
+      // rectangle of time x frequency bins per wave: the fewest windows
+      int lt = 0;
+      float best = 3.4e38f;
+      for (int q = 0; q <= 6; ++q) {
+        const int bt = 1 << q, bf = 64 >> q;
+        const float cost = static_cast<float>(((ch.rows + bt - 1) >> q) * ((ch.nf + bf - 1) / bf)) *
+                           (1.0f + 0.5f * (bt * vt + bf * vf) * (1.0f / kSlack));
+        if (cost < best) {
+          best = cost;
+          lt = q;
+        }
+      }
+      lt = __builtin_amdgcn_readfirstlane(lt);
+      const int bt = 1 << lt, bf = 64 >> lt;
+
+      lds_barrier();  // the previous chunk's folds and table reads are done
+      // keep the tile while the chunk lies inside it and its sums cannot
+      // overflow; else empty it and lay a new one around the chunk
+      const int rx = wrap(box.ox - tile.ox, a.ml), ry = wrap(box.oy - tile.oy, a.mm);
+      const int nbins = box.bx == 0 ? 0 : ch.rows * ch.nf;
+      if (box.bx == 0 || rx + box.bx > tile.bx || ry + box.by > tile.by || tile_bins + nbins > (1 << a.log_tile)) {
+        flush_tile();
+        tile = box;
+        if (box.bx > 0) {
+          tile.bx = max(box.bx, min(min(a.ml, kTileSide), kTileCells / box.by));
+          tile.by = max(box.by, min(a.mm, kTileCells / tile.bx));
+          tile.ox = wrap(box.ox - (tile.bx - box.bx) / 2, a.ml);
+          tile.oy = wrap(box.oy - (tile.by - box.by) / 2, a.mm);
+        }
+      }
+      tile_bins += nbins;
+      const bool use_tab = FUSED && ch.nt <= kTabRows, use_nu = FUSED && ch.nf <= kTabFreq;
+      if constexpr (FUSED) {
+#pragma clang fp contract(off)
+        if (use_tab) {
+          const int64_t r0 = ch.t0 * ch.nt;
+          const int n = ch.rows * ch.nt;
+          for (int i = threadIdx.x; i < n; i += kThreads) {
+            const double* row = o.uvw + 3 * (static_cast<int64_t>(b) * o.n_t + min(r0 + i, static_cast<int64_t>(o.n_t) - 1));
+            const int tr = i / ch.nt;
+            tab[(i - tr * ch.nt) * ch.rows + tr] = row[0] * l0 + row[1] * m0 + row[2] * lw;
+          }
+        }
+        if (use_nu)
+          for (int f = threadIdx.x; f < ch.nf; f += kThreads)
+            tabnu[f] = bin_freq(o.freq, f * ch.nc, f * ch.nc + min(ch.nc, o.n_ch - f * ch.nc));
+      }
+      lds_barrier();
+
+      const int nqt = (ch.rows + bt - 1) >> lt, nqf = (ch.nf + bf - 1) / bf;
+      const int nq = nqt * nqf, per = (nq + kWaves - 1) / kWaves;
+      const int q0 = wave * per, q1 = min(nq, q0 + per);
+      g_f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
+      int wx = -1, wy = 0;  // the current window's origin, -1: none
+      int run = 0;  // batches in the current window's accumulators
+      int qt_now = -1;
+      double pt = 0.0, qtv = 0.0, ak = 0.0;  // the time bin's projections (metres)
+      for (int q = q0; q < q1; ++q) {
+        const int qt = q / nqf, qf = q - qt * nqf;
+        const int tr = (qt << lt) + (lane & (bt - 1)), f = qf * bf + (lane >> lt);
+        const int64_t l = (ch.t0 + tr) * ch.nf + f;
+        const bool in = tr < ch.rows && f < ch.nf && l >= ch.la && l < ch.lb;
+        const int64_t k = ch.base + (in ? l : ch.la);
+        double up, vp;
+        float2 c0;
+        if constexpr (FUSED) {
+          const float W = o.W[k];
+          if (qt != qt_now) {
+#pragma clang fp contract(off)
+            const double* uc = o.uvw_c + 3 * (tb0 + ch.t0 + min(tr, ch.rows - 1));
+            const double u = uc[0], v = uc[1], w = uc[2];
+            ak = u * l0 + v * m0 + w * lw;
+            pt = (u - w * l0n) * kInvCLight;
+            qtv = (v - w * m0n) * kInvCLight;
+            qt_now = qt;
+          }
+          const int fc = min(f, ch.nf - 1);
+          const int c0i = fc * ch.nc, c1i = c0i + min(ch.nc, o.n_ch - c0i);
+          const double nu = use_nu ? tabnu[fc] : bin_freq(o.freq, c0i, c1i);
+          const cf32 D = bin_factor(o, ch, use_tab ? tab : nullptr, in, min(tr, ch.rows - 1), c0i, c1i, ak * nu, l0, m0, lw);
+          up = pt * nu;
+          vp = qtv * nu;
+          c0 = make_float2(W * D.re, W * D.im);
+          if (in) peak += static_cast<double>(c0.x);
+        } else {
+          up = rec[k].up;
+          vp = rec[k].vp;
+          c0 = cf[k];
+        }
+        // finite? (u', v' and c: anything else makes the patch NaN)
+        const bool ok = in && isfinite(up) && isfinite(vp) && isfinite(c0.x) && isfinite(c0.y);
+        if (in && !ok) state->poison = 1;
+        int ax = 0, ay = 0;
+        float fx = 0.f, fy = 0.f;
+        cf32 c = {0.f, 0.f};
+        if (ok) {
+          torus(up, dl, a.ml, &ax, &fx);
+          torus(vp, dm, a.mm, &ay, &fy);
+          c = cf32{ldexpf(c0.x, kCoefBits - ecm), ldexpf(c0.y, kCoefBits - ecm)};
+          if (shift) c = cmul(c, expi_turns_hw(up * xh + vp * yh));
+        }
+        ax = wrap(ax - kW / 2, a.ml);
+        ay = wrap(ay - kW / 2, a.mm);
+        float tx[kW], ty[kW];
+        taps(fx, tx);
+        taps(fy, ty);
+        uint64_t wait = __ballot(ok);
+        while (wait != 0) {
+          const int fl = first_lane(wait);
+          const int fax = __builtin_amdgcn_readlane(ax, fl), fay = __builtin_amdgcn_readlane(ay, fl);
+          if (wx < 0 || run == kRun || wrap(fax - wx, a.ml) > kSlack || wrap(fay - wy, a.mm) > kSlack) {
+            run = 0;
+            if (wx >= 0) {
+              fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im);
+              re = im = g_f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            const int ll = last_lane(wait);
+            wx = window_origin(fax, __builtin_amdgcn_readlane(ax, ll), a.ml);
+            wy = window_origin(fay, __builtin_amdgcn_readlane(ay, ll), a.mm);
+          }
+          ++run;
+          const int dx = wrap(ax - wx, a.ml), dy = wrap(ay - wy, a.mm);
+          const bool go = ((wait >> lane) & 1) != 0 && dx <= kSlack && dy <= kSlack;
+          const uint64_t going = __ballot(go);
+          wait &= ~going;
+          const uint32_t rwa = MA == kMSR ? static_cast<uint32_t>(k) * 0xC2B2AE35u : 0;
+          const uint32_t rwb = MB == kMSR ? mix_word(static_cast<uint32_t>(k)) : 0;
+          stage_clear<MA>(st, lane);
+          wave_order();
+          if (go) stage_taps<MA>(st, dx, lane, tx, rwa);
+          wave_order();
+          const Frags fa = stage_read<MA>(st, lane);
+          wave_order();
+          stage_clear<MB>(st, lane);
+          wave_order();
+          float tb[kW];
+#pragma unroll
+          for (int r = 0; r < kW; ++r) tb[r] = ty[r] * c.re;
+          if (go) stage_taps<MB>(st, dy, lane, tb, rwb);
+          wave_order();
+          const Frags fr = stage_read<MB>(st, lane);
+          wave_order();
+          re = contract_frags<MA, MB>(fa, fr, going, re);
+#pragma unroll
+          for (int r = 0; r < kW; ++r) tb[r] = ty[r] * c.im;
+          if (go) stage_taps<MB>(st, dy, lane, tb, rwb ^ 0xAAAAAAAAu);
+          wave_order();
+          const Frags fi = stage_read<MB>(st, lane);
+          wave_order();
+          im = contract_frags<MA, MB>(fa, fi, going, im);
+        }
+      }
+      if (wx >= 0) fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im);
+      ch.t0 += ch.rows;
+    }
+  }
+  lds_barrier();
+  flush_tile();
+  if constexpr (FUSED) {
+    // sum Re c of the workgroup, in a fixed order
+    for (int q = 32; q > 0; q >>= 1) peak += __shfl_xor(peak, q);
+    lds_barrier();
+    if (lane == 0) tab[wave] = peak;
+    lds_barrier();
+    if (threadIdx.x == 0) {
+      double p = 0.0;
+      for (int w = 0; w < kWaves; ++w) p += tab[w];
+      state_of(a, s)->peak[blockIdx.x] = p;
+    }
+  }
+}
+
+// In-place inverse DFT (sign +) of the M complex values in `v` (LDS), radix
+// 2, decimation in frequency: the result is in bit-reversed order.  tw holds
+// exp(2 pi i q / M), q < M / 2.
+__device__ __forceinline__ void fft_lds(double2* v, const double2* tw, int M) {
+  for (int half = M >> 1, sh = 0; half > 0; half >>= 1, ++sh) {
+    for (int t = threadIdx.x; t < (M >> 1); t += blockDim.x) {
+      const int p = t & (half - 1);
+      const int i0 = ((t - p) << 1) + p;
+      const double2 x = v[i0], y = v[i0 + half], w = tw[p << sh];
+      const double dr = x.x - y.x, di = x.y - y.y;
+      v[i0] = make_double2(x.x + y.x, x.y + y.y);
+      v[i0 + half] = make_double2(dr * w.x - di * w.y, dr * w.y + di * w.x);
+    }
+    __syncthreads();
+  }
+}
+
+__device__ __forceinline__ void fft_twiddles(double2* tw, int M) {
+  for (int q = threadIdx.x; q < (M >> 1); q += blockDim.x) {
+    double sn, cs;
+    sincospi(2.0 * q / M, &sn, &cs);
+    tw[q] = make_double2(cs, sn);
+  }
+}
+
+__device__ __forceinline__ int bit_reverse(int i, int log_m) {
+  return static_cast<int>(__brev(static_cast<unsigned>(i)) >> (32 - log_m));
+}
+
+// Grid row blockIdx.x: cells to modes 0 .. nm - 1 of the patch's columns
+// (mode j - nm / 2), divided by the kernel's transform, to mid[j][row].
+__global__ __launch_bounds__(256) void k_grid_rows(UvGridArgs a) {
+  extern __shared__ double2 fft_buf[];
+  karg_gsrc& s = gsrc(blockIdx.y);
+  const int M = a.mm, log_m = 31 - __clz(M), row = blockIdx.x;
+  double2* v = fft_buf;
+  double2* tw = fft_buf + M;
+  const long long* g = reinterpret_cast<const long long*>(cells_of(s)) + 2 * static_cast<int64_t>(row) * M;
+  for (int q = threadIdx.x; q < M; q += 256) v[q] = make_double2(static_cast<double>(g[2 * q]), static_cast<double>(g[2 * q + 1]));
+  fft_twiddles(tw, M);
+  __syncthreads();
+  fft_lds(v, tw, M);
+  double2* mid = reinterpret_cast<double2*>(s.work) + static_cast<int64_t>(a.ml) * a.mm;
+  for (int j = threadIdx.x; j < s.nm; j += 256) {
+    const int m = j - s.nm / 2;
+    const double2 z = v[bit_reverse(m < 0 ? m + M : m, log_m)];
+    const double f = inv_hat(static_cast<double>(m) / M);
+    mid[static_cast<int64_t>(j) * a.ml + row] = make_double2(z.x * f, z.y * f);
+  }
+}
+
+// Patch column blockIdx.x: inverse DFT of mid[column] to its rows' pixels.
+__global__ __launch_bounds__(256) void k_grid_cols(UvGridArgs a) {
+  extern __shared__ double2 fft_buf[];
+  karg_gsrc& s = gsrc(blockIdx.y);
+  const int col = blockIdx.x;
+  if (col >= s.nm) return;
+  const int M = a.ml, log_m = 31 - __clz(M);
+  double2* v = fft_buf;
+  double2* tw = fft_buf + M;
+  const double2* mid = reinterpret_cast<const double2*>(s.work) + static_cast<int64_t>(a.ml) * a.mm +
+                       static_cast<int64_t>(col) * M;
+  for (int q = threadIdx.x; q < M; q += 256) v[q] = mid[q];
+  fft_twiddles(tw, M);
+  __syncthreads();
+  fft_lds(v, tw, M);
+  double scale = ldexp(2.0, max_exponent(s, a.n_init) - cell_bits(a.log_k));
+  if (state_of(a, s)->poison != 0) scale = __builtin_nan("");
+  const bool norm = a.fused ? s.norm != 0 : s.peak != nullptr;
+  double peak = 1.0;
+  if (norm && a.fused) {
+    // 2 sum Re c: the spreading workgroups' sums, in a fixed order
+    double p = 0.0;
+    for (int q = threadIdx.x; q < a.n_wg; q += 256) p += state_of(a, s)->peak[q];
+    for (int q = 32; q > 0; q >>= 1) p += __shfl_xor(p, q);
+    __syncthreads();  // the twiddles are read no more
+    if ((threadIdx.x & 63) == 0) tw[threadIdx.x >> 6].x = p;
+    __syncthreads();
+    peak = 2.0 * (((tw[0].x + tw[1].x) + tw[2].x) + tw[3].x);
+  } else if (norm) {
+    peak = *s.peak;
+  }
+  for (int i = threadIdx.x; i < s.nl; i += 256) {
+    const int m = i - s.nl / 2;
+    const double2 z = v[bit_reverse(m < 0 ? m + M : m, log_m)];
+    const float p = static_cast<float>(z.x * inv_hat(static_cast<double>(m) / M) * scale);
+    // normalised: 0 where the peak is 0 (no weight at all)
+    s.P[static_cast<int64_t>(i) * s.nm + col] =
+        !norm ? p : peak != 0.0 ? static_cast<float>(static_cast<double>(p) / peak) : 0.0f;
+  }
+}
+
+// ---------------------------------------------------------------- host side
+int grid_axis(int n) {
+  int m = 32;
+  while (100LL * m < 196LL * n) m <<= 1;
+  return m <= kGridMaxAxis ? m : 0;
+}
+
+size_t grid_bytes(const GridPlan& g, int nm) {
+  return (static_cast<size_t>(g.ml) * g.mm + static_cast<size_t>(g.ml) * nm) * sizeof(double2) +
+         sizeof(UvGridState);
+}
+
+template <int PREC>
+static void launch_spread(const UvGridArgs& a, dim3 grid, hipStream_t stream) {
+  if (a.fused)
+    hipLaunchKernelGGL((k_grid_spread<PREC, true>), grid, dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((k_grid_spread<PREC, false>), grid, dim3(kThreads), 0, stream, a);
+}
+
+hipError_t launch_grid(int prec, UvGridArgs a, hipStream_t stream) {
+  if (a.n_src < 1 || a.n_src > kMaxBatch || a.ml < 32 || a.mm < 32 || a.ml > kGridMaxAxis || a.mm > kGridMaxAxis ||
+      (a.ml & (a.ml - 1)) != 0 || (a.mm & (a.mm - 1)) != 0 || a.o.K < 1)
+    return hipErrorInvalidValue;
+  int nm = 0;
+  for (int s = 0; s < a.n_src; ++s) {
+    if (a.src[s].nl > a.ml || a.src[s].nm > a.mm) return hipErrorInvalidValue;
+    nm = a.src[s].nm > nm ? a.src[s].nm : nm;
+    // every source of the fused form is scaled by the weights' maximum
+    const int m = a.fused ? 0 : s;
+    a.src[s].maxima = reinterpret_cast<UvGridState*>(
+                          a.src[m].work +
+                          (static_cast<size_t>(a.ml) * a.mm + static_cast<size_t>(a.ml) * a.src[m].nm) * sizeof(double2))
+                          ->maxima;
+  }
+  const int64_t K = a.o.K;
+  a.log_k = 0;
+  while ((int64_t(1) << a.log_k) < K) ++a.log_k;
+  // Bins a tile may sum: the fewer, the finer its fixed point (a fold is off
+  // by a third of 2^(log_tile - 30) of the largest |c| per cell, at random, so
+  // the patch by about 2^log_tile / sqrt(K) in the same unit); the more, the
+  // fewer tiles are emptied into the grid.  With 2^10 at K = 2^16 and twice as
+  // many per fourfold K this stays near 1e-8 of sum |c| (2^14 throughout:
+  // 1.3e-7 at K = 76760).  At least what kRun batches hold and, so that a row
+  // of frequency bins fits, the number of channels.
+  a.log_tile = std::min(14, std::max(9, 10 + (a.log_k - 16) / 2));
+  while (a.log_tile < 14 && (1 << a.log_tile) < a.o.n_ch) ++a.log_tile;
+  // contiguous bins per workgroup: a few rounds of the 768 that the chip
+  // runs at once, at least 512 bins each
+  const int64_t want = 3072 / a.n_src;
+  const int64_t span = (K + want - 1) / want;
+  a.wg_bins = span < 512 ? 512 : span;
+  a.n_wg = static_cast<int>((K + a.wg_bins - 1) / a.wg_bins);
+  const unsigned n_src = static_cast<unsigned>(a.n_src);
+  const int64_t words = std::max(static_cast<int64_t>(a.ml) * a.mm, K / (a.fused ? 4 : 2));
+  a.n_init = static_cast<int>(std::min<int64_t>(kInitBlocks, (words + 255) / 256));
+  hipLaunchKernelGGL(k_grid_init, dim3(static_cast<unsigned>(a.n_init), n_src), dim3(256), 0, stream, a);
+  const dim3 sg(static_cast<unsigned>(a.n_wg), n_src);
+  switch (prec) {
+    case kFP32: launch_spread<kFP32>(a, sg, stream); break;
+    case kSplitBF16: launch_spread<kSplitBF16>(a, sg, stream); break;
+    case kSplitFP16: launch_spread<kSplitFP16>(a, sg, stream); break;
+    case kMixedFP16: launch_spread<kMixedFP16>(a, sg, stream); break;
+    case kSRFP16: launch_spread<kSRFP16>(a, sg, stream); break;
+    default: return hipErrorInvalidValue;
+  }
+  hipLaunchKernelGGL(k_grid_rows, dim3(static_cast<unsigned>(a.ml), n_src), dim3(256),
+                     static_cast<size_t>(a.mm) * 3 / 2 * sizeof(double2), stream, a);
+  hipLaunchKernelGGL(k_grid_cols, dim3(static_cast<unsigned>(nm), n_src), dim3(256),
+                     static_cast<size_t>(a.ml) * 3 / 2 * sizeof(double2), stream, a);
+  return hipGetLastError();
+}
+
+}  // namespace psf

@@ -43,20 +43,6 @@
 // lo = round16(v - hi); the product uses hi*hi + hi*lo + lo*hi (three MFMAs)
 // with FP32 accumulation.
 //
-// Mixed form (symmetric form only): the columns c_k b_kj are split as above,
-// the rows (cos and sin) are one FP16 value each: a * (b_hi + b_lo), two
-// MFMAs.  Rounded to nearest, a row value would carry an error that
-// neighbouring visibilities share (their phases are nearly equal, and where
-// the phase is small cos rounds to 1 for all of them), which adds up
-// coherently over a baseline's bins.  The rows are instead rounded
-// stochastically (the conversion instruction's random-word operand, a
-// per-visibility Weyl sequence in the bin index): unbiased, with errors
-// independent across visibilities, which average out over many of them.
-// Stochastic form (symmetric form only): the columns too are one
-// stochastically rounded FP16 value (their own per-visibility random word,
-// a hash of the bin index, so that a term's two roundings are independent):
-// a * b, one MFMA.
-//
 // Symmetric form.  With N = 2h + 1 rows, x_i = delta + (i - h) dl where
 // delta = (l_first + h dl) - l0 is the offset of the grid's centre row from
 // the source (0 for a centred grid), so a_ki = e_k a_k(s_i) with
@@ -116,7 +102,7 @@ struct TileArgs {
 
 template <int PREC>
 __device__ __forceinline__ f32x4 mfma16(const bf16x8& a, const bf16x8& b, f32x4 acc) {
-  if constexpr (PREC == kSplitFP16 || PREC == kMixedFP16 || PREC == kSRFP16) {
+  if constexpr (PREC == kSplitFP16) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b),
                                                   acc, 0, 0, 0);
   } else {
@@ -174,19 +160,18 @@ struct TileGeom {
   static constexpr int TI = 16 * TBI, TJ = 16 * TBJ;
   static constexpr int RA = TI / 8, RB = TJ / 8;  // rows per generator thread (stride 8)
   static constexpr bool F32 = PREC == kFP32;
-  // operands carried as hi + lo (A: tile rows, B: tile columns)
-  static constexpr bool TWOA = PREC == kSplitBF16 || PREC == kSplitFP16;
-  static constexpr bool TWOB = TWOA || PREC == kMixedFP16;
+  // operands carried as hi + lo
+  static constexpr bool TWO = PREC == kSplitBF16 || PREC == kSplitFP16;
   static constexpr int GA = TI * kRowBytes, GB = TJ * kRowBytes;  // one group / plane
   static constexpr int APL = (F32 ? 2 : 1) * GA, BPL = (F32 ? 2 : 1) * GB;
-  static constexpr int NPLA = TWOA ? 2 : 1, NPLB = TWOB ? 2 : 1;
+  static constexpr int NPL = TWO ? 2 : 1;
   // symmetric form: C blocks of the tile, and B planes (Re d and Im d when
   // the tile holds both groups, else the one its rows read)
   static constexpr int CB = SYM ? sym_cb(TBI, TBJ) : TBI;
   static constexpr int NBP = SYM && CB > 0 && CB < TBI ? 2 : 1;
-  static constexpr int BUF = NPLA * APL + NBP * NPLB * BPL;
+  static constexpr int BUF = NPL * APL + NBP * NPL * BPL;
   // byte offset of B's part (0 hi, 1 lo) of plane pl within a buffer
-  static constexpr int boff(int part, int pl) { return NPLA * APL + (pl * NPLB + part) * BPL; }
+  static constexpr int boff(int part, int pl) { return NPL * APL + (pl * NPL + part) * BPL; }
   // Chunk buffers.  2: the chunk being contracted and the chunk being
   // generated.  3: also the next chunk, complete one barrier early, so that
   // its first operand fragments can be read ahead of the barrier (measured
@@ -195,8 +180,6 @@ struct TileGeom {
   static constexpr int LDS = NBUF * BUF;
   static_assert(LDS <= 160 * 1024, "LDS of a workgroup exceeds 160 KiB");
   static_assert(!SYM || CB >= 0, "no symmetric form for this tile type");
-  static_assert(SYM || (PREC != kMixedFP16 && PREC != kSRFP16),
-                "the mixed and stochastic forms exist for the symmetric form only");
 };
 
 // Sub-tile of one contraction wave: m x n blocks at block (i0, j0) of the
@@ -315,7 +298,7 @@ struct Gen {
   using G = TileGeom<PREC, TBI, TBJ>;
   static constexpr int R = IS_A ? TBI : TBJ;  // rows per thread
   static constexpr int GSTRIDE = IS_A ? G::GA : G::GB;
-  static constexpr int GOFF = IS_A ? 0 : G::NPLA * G::APL;
+  static constexpr int GOFF = IS_A ? 0 : G::NPL * G::APL;
   static constexpr int GLO = IS_A ? G::APL : G::BPL;
   static constexpr int P = 1;  // chunks of records held ahead
 
@@ -443,27 +426,6 @@ __device__ __forceinline__ void store_pair(lds_t* hi_plane, int lo_off, int gstr
   }
 }
 
-// Mixed form: two row values of visibilities 2 gv and 2 gv + 1 (random
-// words r0, r1) as one FP16 value each, rounded stochastically: the
-// conversion adds the top bits of the random word below the kept ones and
-// truncates, so each value rounds up with probability equal to its
-// fractional position between its two FP16 neighbours.
-__device__ __forceinline__ void store_pair_sr(lds_t* plane, int row, int gv, float v0, float v1, uint32_t r0,
-                                              uint32_t r1) {
-  typedef __attribute__((address_space(3))) uint32_t lds_u32;
-  // each conversion writes one half and keeps the other; the two together
-  // write both, so the initial value is never read (left undefined, so that
-  // no register is cleared for it)
-  f16x2_t h;
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Wuninitialized"
-  h = __builtin_amdgcn_cvt_sr_f16_f32(h, v0, r0, false);
-#pragma clang diagnostic pop
-  h = __builtin_amdgcn_cvt_sr_f16_f32(h, v1, r1, true);
-  *reinterpret_cast<lds_u32*>(plane + row * kRowBytes + swz(row, gv >> 2) + (gv & 3) * 4) =
-      __builtin_bit_cast(uint32_t, h);
-}
-
 // Phase-factor generation of the symmetric form (see the file comment).
 // Thread (gv, rc) owns visibilities 2 gv and 2 gv + 1 of each 32-visibility
 // chunk and row (column) class rc.  A (waves 0-3): unit n of its sequence
@@ -480,11 +442,6 @@ __device__ __forceinline__ void store_pair_sr(lds_t* plane, int row, int gv, flo
 template <int PREC, int TBI, int TBJ, bool IS_A>
 struct GenSym {
   using G = TileGeom<PREC, TBI, TBJ, true>;
-  // how this side's values are stored: stochastically rounded (store_pair_sr)
-  // for the rows of the mixed form and both sides of the stochastic form,
-  // else split or FP32 (store_pair<OP>)
-  static constexpr int OP = PREC == kMixedFP16 ? kSplitFP16 : PREC;
-  static constexpr bool SR = (IS_A && PREC == kMixedFP16) || PREC == kSRFP16;
   static constexpr int CB = G::CB;
   static constexpr bool HC = CB > 0, HS = CB < TBI;
   static constexpr int N0 = IS_A && !HC ? 1 : 0;
@@ -507,10 +464,6 @@ struct GenSym {
   double ru[P][2];  // B: u' (for the offset factor)
   cf32 rst[P][2];
   cf32 rcc[P][2];
-  bool rok[P][2];      // pointer form: the bin lies inside the slice
-  uint32_t rrw[P][2];  // stochastic rounding: the bins' random words
-  uint32_t rw[2];
-  uint32_t wl;  // A, stochastic rounding: this thread's part of the rows' word
   int vo, vc;   // byte offsets of this thread's first bin in a chunk's records and coefficients
   cf32 z[2], zp[2];
   float tc[2];
@@ -529,82 +482,24 @@ struct GenSym {
     ke = ke_;
     vo = 2 * gv * static_cast<int>(sizeof(BinRec));
     vc = 2 * gv * static_cast<int>(sizeof(float2));
-    if (BUF && PREC != kSRFP16) asm volatile("" : "+v"(vo), "+v"(vc));
-    if (BUF && SR && IS_A) {
-      wl = static_cast<uint32_t>(2 * gv) * kWeyl;
-      // kept opaque, so that the compiler does not fold the per-chunk sum
-      // below back into one product per bin
-      asm volatile("" : "+v"(wl));
-    }
+    // kept opaque, so that the per-bin and per-field constants added to them
+    // become the load instructions' immediate offsets
+    asm volatile("" : "+v"(vo), "+v"(vc));
   }
-  static constexpr uint32_t kWeyl = 0x9E3779B1u;
-  // How a chunk's records and coefficients are read (same values either
-  // way).  Buffer form: through buffer resources that start at the chunk's
-  // first bin and end at the slice's end (ke), so bins past it read as 0
-  // (u' = v' = 0, a zero step and c = 0: their B values are 0, no
-  // contribution, and their A values finite); the resources are uniform
-  // (scalar) and a thread's offsets into them fixed, so no per-bin address
-  // arithmetic remains (65- and 129-pixel stochastic families 4-7% faster).
-  // Pointer form, kept for the B waves of the 257-pixel stochastic tiles:
-  // that kernel sits at the 128-register limit of four waves per SIMD,
-  // where the buffer form on both sides made the allocator spill inside the
-  // chunk loop (9% slower); past the slice's end it reads the last bin and
-  // takes c = 0.
-  static constexpr bool BUF = !(PREC == kSRFP16 && TBJ >= 17 && !IS_A);
-  // The random word of bin kg: for the rows kg times the golden ratio mod
-  // 2^32, whose top bits (the ones the conversion uses) are equidistributed
-  // in kg; for the columns a 32-bit mixing hash of kg (multiply-xorshift
-  // finaliser), independent of the rows' word.
-  static __device__ __forceinline__ uint32_t col_word(uint32_t h) {
-    h ^= h >> 16;
-    h *= 0x85EBCA6Bu;
-    h ^= h >> 13;
-    h *= 0xC2B2AE35u;
-    h ^= h >> 16;
-    return h;
-  }
-  // Bin kg = k0 + 2 gv + e of chunk n (k0 = kb + 32 n).
-  // The thread's offsets for one chunk, kept opaque to the compiler so that
-  // the per-bin and per-field constants added to them become the load
-  // instructions' immediate offsets rather than one register per load: in
-  // the stochastic form a fresh copy per chunk, which the compiler cannot
-  // hoist out of the chunk loop either (its four waves per SIMD leave no
-  // registers for hoisted offsets: 1-2% faster), elsewhere the offsets made
-  // opaque once (a copy per chunk was 2% slower for the two-wave 257-pixel
-  // split kernel).
-  __device__ __forceinline__ int2 offsets() const {
-    int2 v = {vo, vc};
-    if (BUF && PREC == kSRFP16) asm volatile("" : "+v"(v.x), "+v"(v.y));
-    return v;
-  }
-  __device__ __forceinline__ void fetch(int64_t n, int e, int2 vof, double& f, double& u, cf32& st, cf32& cc,
-                                        bool& ok, uint32_t& rwd) const {
+  // A chunk's records and coefficients are read through buffer resources
+  // that start at the chunk's first bin and end at the slice's end (ke), so
+  // bins past it read as 0 (u' = v' = 0, a zero step and c = 0: their B
+  // values are 0, no contribution, and their A values finite); the resources
+  // are uniform (scalar) and a thread's offsets into them fixed, so no
+  // per-bin address arithmetic remains.
+  // Bin k0 + 2 gv + e of chunk n (k0 = kb + 32 n).
+  __device__ __forceinline__ void fetch(int64_t n, int e, double& f, double& u, cf32& st, cf32& cc) const {
     const int64_t k0 = kb + n * kPatchChunkSym;
-    const int j = 2 * gv + e;
-    if constexpr (!BUF) {
-      const int64_t kg = k0 + j;
-      if (SR) rwd = IS_A ? static_cast<uint32_t>(kg) * kWeyl : col_word(static_cast<uint32_t>(kg));
-      ok = kg < ke;
-      const int64_t kc = ok ? kg : ke - 1;
-      const BinRec* r = recs + kc;
-      f = IS_A ? r->up : r->vp;
-      const float2 s = IS_A ? r->step_a : r->step_b;
-      st = {s.x, s.y};
-      if (!IS_A) {
-        u = r->up;
-        const float2 c = cptr[kc];
-        cc = {c.x, c.y};
-      }
-      return;
-    }
-    // the rows' word as (k0 + e) times the multiplier (uniform) plus this
-    // thread's part
-    if (SR) rwd = IS_A ? static_cast<uint32_t>(k0 + e) * kWeyl + wl : col_word(static_cast<uint32_t>(k0 + j));
     const int64_t left = ke - k0;
     const int nb = left <= 0 ? 0 : left >= kPatchChunkSym ? kPatchChunkSym : static_cast<int>(left);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<BinRec*>(recs + k0), 0, nb * static_cast<int>(sizeof(BinRec)), 0x00020000);
-    const int ro = vof.x + e * static_cast<int>(sizeof(BinRec));
+    const int ro = vo + e * static_cast<int>(sizeof(BinRec));
     if (IS_A) {
       f = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rr, ro + offsetof(BinRec, up), 0, 0));
       st = __builtin_bit_cast(cf32, __builtin_amdgcn_raw_buffer_load_b64(rr, ro + offsetof(BinRec, step_a), 0, 0));
@@ -616,25 +511,23 @@ struct GenSym {
       const __amdgpu_buffer_rsrc_t rcs = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<float2*>(cptr + k0), 0, nb * static_cast<int>(sizeof(float2)), 0x00020000);
       cc = __builtin_bit_cast(cf32,
-                              __builtin_amdgcn_raw_buffer_load_b64(rcs, vof.y + e * static_cast<int>(sizeof(float2)), 0, 0));
+                              __builtin_amdgcn_raw_buffer_load_b64(rcs, vc + e * static_cast<int>(sizeof(float2)), 0, 0));
     }
   }
   __device__ __forceinline__ void prime() {
 #pragma unroll
     for (int j = 0; j < P; ++j) {
-      const int2 vof = offsets();
 #pragma unroll
-      for (int e = 0; e < 2; ++e) fetch(j, e, vof, rf[j][e], ru[j][e], rst[j][e], rcc[j][e], rok[j][e], rrw[j][e]);
+      for (int e = 0; e < 2; ++e) fetch(j, e, rf[j][e], ru[j][e], rst[j][e], rcc[j][e]);
     }
   }
   __device__ __forceinline__ void begin(lds_t* smem, int buf) {
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-      if (SR) rw[e] = rrw[0][e];
       z[e] = expi_turns_hw(rf[0][e] * pos0);
       const cf32 zs = rst[0][e];
       if (!IS_A) {
-        cf32 cc = BUF || rok[0][e] ? rcc[0][e] : cf32{0.f, 0.f};
+        cf32 cc = rcc[0][e];
         // a grid not centred on the source: the row-independent factor
         // exp(2 pi i u' delta) joins the coefficient (FP64-reduced, used once)
         if (delta != 0.0) cc = cmul(cc, expi_turns_hw(ru[0][e] * delta));
@@ -668,33 +561,19 @@ struct GenSym {
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       if (q < q0 || q >= q1) continue;
-      if constexpr (SR && !IS_A) {
-        if constexpr (BOTH) {
-          store_pair_sr(plane, 16 * q + rc, gv, z[0].re, z[1].re, rw[0], rw[1]);
-          store_pair_sr(plane + G::NPLB * G::BPL, 16 * q + rc, gv, z[0].im, z[1].im, rw[0], rw[1]);
-        } else if constexpr (ONLY_IM) {
-          store_pair_sr(plane, 16 * q + rc, gv, z[0].im, z[1].im, rw[0], rw[1]);
-        } else {
-          store_pair_sr(plane, 16 * q + rc, gv, z[0].re, z[1].re, rw[0], rw[1]);
-        }
-      } else if constexpr (SR) {
+      if constexpr (IS_A) {
         const int n = N0 + q;
-        if (HC && n < CB) store_pair_sr(plane, 16 * n + rc, gv, z[0].re, z[1].re, rw[0], rw[1]);
+        if (HC && n < CB) store_pair<PREC>(plane, LO, GSTRIDE, 16 * n + rc, gv, z[0].re, z[1].re);
         if (HS && n >= 1 && CB + n - 1 < TBI)
-          store_pair_sr(plane, 16 * (CB + n - 1) + rc, gv, z[0].im, z[1].im, rw[0], rw[1]);
-      } else if constexpr (IS_A) {
-        const int n = N0 + q;
-        if (HC && n < CB) store_pair<OP>(plane, LO, GSTRIDE, 16 * n + rc, gv, z[0].re, z[1].re);
-        if (HS && n >= 1 && CB + n - 1 < TBI)
-          store_pair<OP>(plane, LO, GSTRIDE, 16 * (CB + n - 1) + rc, gv, z[0].im, z[1].im);
+          store_pair<PREC>(plane, LO, GSTRIDE, 16 * (CB + n - 1) + rc, gv, z[0].im, z[1].im);
       } else {
         if constexpr (BOTH) {
-          store_pair<OP>(plane, LO, GSTRIDE, 16 * q + rc, gv, z[0].re, z[1].re);
-          store_pair<OP>(plane + G::NPLB * G::BPL, LO, GSTRIDE, 16 * q + rc, gv, z[0].im, z[1].im);
+          store_pair<PREC>(plane, LO, GSTRIDE, 16 * q + rc, gv, z[0].re, z[1].re);
+          store_pair<PREC>(plane + G::NPL * G::BPL, LO, GSTRIDE, 16 * q + rc, gv, z[0].im, z[1].im);
         } else if constexpr (ONLY_IM) {
-          store_pair<OP>(plane, LO, GSTRIDE, 16 * q + rc, gv, z[0].im, z[1].im);
+          store_pair<PREC>(plane, LO, GSTRIDE, 16 * q + rc, gv, z[0].im, z[1].im);
         } else {
-          store_pair<OP>(plane, LO, GSTRIDE, 16 * q + rc, gv, z[0].re, z[1].re);
+          store_pair<PREC>(plane, LO, GSTRIDE, 16 * q + rc, gv, z[0].re, z[1].re);
         }
       }
       if (q + 1 < R) step();
@@ -709,13 +588,9 @@ struct GenSym {
         ru[j][e] = ru[j + 1][e];
         rst[j][e] = rst[j + 1][e];
         rcc[j][e] = rcc[j + 1][e];
-        rok[j][e] = rok[j + 1][e];
-        rrw[j][e] = rrw[j + 1][e];
       }
-    const int2 vof = offsets();
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-      fetch(n, e, vof, rf[P - 1][e], ru[P - 1][e], rst[P - 1][e], rcc[P - 1][e], rok[P - 1][e], rrw[P - 1][e]);
+    for (int e = 0; e < 2; ++e) fetch(n, e, rf[P - 1][e], ru[P - 1][e], rst[P - 1][e], rcc[P - 1][e]);
   }
 };
 
@@ -740,9 +615,8 @@ __device__ __forceinline__ void wave_item(const TileArgs& a, lds_t* smem, int bi
   // symmetric form's S rows read Im d when the tile holds both groups)
   constexpr int CH = SYM ? kPatchChunkSym : kChunk;
   constexpr int BP = G::NBP == 2 && WI0 >= G::CB ? 1 : 0;
-  // generation rows spread over the contraction steps of a chunk (the
-  // mixed and stochastic forms have no second pass)
-  constexpr int NSTEP = G::F32 ? 2 * N : PREC == kMixedFP16 || PREC == kSRFP16 ? N : N + M;
+  // generation rows spread over the contraction steps of a chunk
+  constexpr int NSTEP = G::F32 ? 2 * N : N + M;
   typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
   typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
   const int lane = threadIdx.x & 63;
@@ -807,7 +681,7 @@ __device__ __forceinline__ void wave_item(const TileArgs& a, lds_t* smem, int bi
 #pragma unroll
       for (int r = 0; r < M; ++r) pah[r] = ldA(Ah, 0, r);
       pbh = ldB(Ah, 0, 0);
-      if constexpr (G::TWOB) pbl = ldB(Ah, 1, 0);
+      if constexpr (G::TWO) pbl = ldB(Ah, 1, 0);
     }
   };
   int cur = 0;  // buffer of chunk n
@@ -862,17 +736,17 @@ __device__ __forceinline__ void wave_item(const TileArgs& a, lds_t* smem, int bi
           const bf16x8 bl = nbl;
           if (c + 1 < N) {
             nbh = ldB(Ah, 0, c + 1);
-            if constexpr (G::TWOB) nbl = ldB(Ah, 1, c + 1);
+            if constexpr (G::TWO) nbl = ldB(Ah, 1, c + 1);
           }
 #pragma unroll
           for (int r = 0; r < M; ++r) {
             if (!on(r, c)) continue;
             acc[r][c] = mfma16<PREC>(pah[r], bh[c], acc[r][c]);
-            if constexpr (G::TWOB) acc[r][c] = mfma16<PREC>(pah[r], bl, acc[r][c]);
+            if constexpr (G::TWO) acc[r][c] = mfma16<PREC>(pah[r], bl, acc[r][c]);
           }
           gen_step();
         }
-        if constexpr (G::TWOA) {
+        if constexpr (G::TWO) {
           bf16x8 nal = ldA(Ah, 1, 0);
 #pragma unroll
           for (int r = 0; r < M; ++r) {
@@ -883,7 +757,7 @@ __device__ __forceinline__ void wave_item(const TileArgs& a, lds_t* smem, int bi
               if (on(r, c)) acc[r][c] = mfma16<PREC>(al, bh[c], acc[r][c]);
             gen_step();
           }
-        } else if constexpr (PREC != kMixedFP16 && PREC != kSRFP16) {
+        } else {
 #pragma unroll
           for (int r = 0; r < M; ++r) gen_step();
         }
@@ -1063,14 +937,10 @@ __device__ __forceinline__ void role_loop(const BatchArgs& a, karg_plan* plans, 
 // block tiles of the 65-pixel family, whose per-chunk matrix work is small
 // enough that a second workgroup's waves are needed to cover the barrier and
 // LDS latency of each chunk (16 patches of 65 pixels at K = 23.2M,
-// split-BF16: 38.0 to 28.6 ms), and four for every tile of the stochastic
-// form, whose one product per block leaves each chunk mostly latency
-// (single 257 x 257 patch at K = 5.8M: 1.58 to 1.27 ms, though the
-// compiler keeps 128 registers by spilling some of the item-loop state;
-// 16 patches of 129: 11.8 to 8.7 ms).
+// split-BF16: 38.0 to 28.6 ms).
 template <int PREC, int I0, int I1, int J0, int J1, bool SYM>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512),
-                          amdgpu_waves_per_eu(PREC == kSRFP16 ? 4 : 2, I0 <= 5 || PREC == kSRFP16 ? 4 : 2)))
+                          amdgpu_waves_per_eu(2, I0 <= 5 ? 4 : 2)))
 void k_patch(BatchArgs a) {
   constexpr int L00 = TileGeom<PREC, I0, J0, SYM>::LDS, L01 = TileGeom<PREC, I0, J1, SYM>::LDS;
   constexpr int L10 = TileGeom<PREC, I1, J0, SYM>::LDS, L11 = TileGeom<PREC, I1, J1, SYM>::LDS;
@@ -1229,7 +1099,7 @@ void plan_tiles(int nbi, int nbj, TilePlan* t) {
     }
 }
 
-int tile_wgs_per_cu(const TilePlan& t, int prec) { return t.tbi[0] <= 5 || prec == kSRFP16 ? 2 : 1; }
+int tile_wgs_per_cu(const TilePlan& t) { return t.tbi[0] <= 5 ? 2 : 1; }
 
 bool sym_patch_size(int nl, int nm) {
   const int nbj = (nm + 15) / 16;
@@ -1250,19 +1120,15 @@ static hipError_t launch_family(const BatchArgs& a, dim3 grid, hipStream_t strea
       return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  if constexpr (PREC == kMixedFP16 || PREC == kSRFP16) {
-    return hipErrorInvalidValue;  // symmetric form only
-  } else {
-    if (t.tbi[0] == 9 && t.tbi[1] == 8)
-      hipLaunchKernelGGL((k_patch<PREC, 9, 8, 17, 17, false>), grid, dim3(512), 0, stream, a);
-    else if (t.tbi[0] == 9)
-      hipLaunchKernelGGL((k_patch<PREC, 9, 9, 9, 9, false>), grid, dim3(512), 0, stream, a);
-    else if (t.tbi[0] == 5)
-      hipLaunchKernelGGL((k_patch<PREC, 5, 5, 5, 5, false>), grid, dim3(512), 0, stream, a);
-    else
-      hipLaunchKernelGGL((k_patch<PREC, 8, 8, 8, 8, false>), grid, dim3(512), 0, stream, a);
-    return hipGetLastError();
-  }
+  if (t.tbi[0] == 9 && t.tbi[1] == 8)
+    hipLaunchKernelGGL((k_patch<PREC, 9, 8, 17, 17, false>), grid, dim3(512), 0, stream, a);
+  else if (t.tbi[0] == 9)
+    hipLaunchKernelGGL((k_patch<PREC, 9, 9, 9, 9, false>), grid, dim3(512), 0, stream, a);
+  else if (t.tbi[0] == 5)
+    hipLaunchKernelGGL((k_patch<PREC, 5, 5, 5, 5, false>), grid, dim3(512), 0, stream, a);
+  else
+    hipLaunchKernelGGL((k_patch<PREC, 8, 8, 8, 8, false>), grid, dim3(512), 0, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_patch(int prec, const BatchArgs& a, int64_t n_wg, hipStream_t stream) {
@@ -1278,8 +1144,6 @@ hipError_t launch_patch(int prec, const BatchArgs& a, int64_t n_wg, hipStream_t 
     case kSplitBF16: return launch_family<kSplitBF16>(a, grid, stream);
     case kSplitFP16: return launch_family<kSplitFP16>(a, grid, stream);
     case kPlainBF16: return launch_family<kPlainBF16>(a, grid, stream);
-    case kMixedFP16: return launch_family<kMixedFP16>(a, grid, stream);
-    case kSRFP16: return launch_family<kSRFP16>(a, grid, stream);
     default: return hipErrorInvalidValue;
   }
 }

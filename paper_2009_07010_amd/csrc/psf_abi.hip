@@ -126,16 +126,8 @@ bool sym_source(const psf_src* s) { return sym_patch_size(s->nl, s->nm); }
 // chunk for seeds and records, twice that in the symmetric form, 4.7 cycles
 // each).  Measured kernels behave closer to the sum of the two than to their
 // maximum.
-static void chunk_costs(const TilePlan& t, int prec, bool sym, int64_t K, double cost[2][2]) {
-  // (the mixed and stochastic forms run two and one products where they run
-  // at all, see contraction_prec: plans of their split-FP16 routes are
-  // split-FP16 plans)
-  const bool many = sym && K >= kMixedMinK;
-  const double mfma_per_block = prec == PSF_FP32                     ? 256.0
-                                : prec == PSF_PLAIN_BF16             ? 16.0
-                                : prec == PSF_MIXED_FP16 && many ? 32.0
-                                : prec == PSF_SR_FP16 && many    ? 16.0
-                                                                     : 48.0;
+static void chunk_costs(const TilePlan& t, int prec, bool sym, double cost[2][2]) {
+  const double mfma_per_block = prec == PSF_FP32 ? 256.0 : prec == PSF_PLAIN_BF16 ? 16.0 : 48.0;
   for (int r = 0; r < 2; ++r)
     for (int c = 0; c < 2; ++c) {
       const double mf = mfma_per_block * tile_max_simd_blocks(t.tbi[r], t.tbj[c], sym);
@@ -154,7 +146,7 @@ double patch_work(const psf_obs* o, const psf_src* s, int prec) {
   plan_tiles((s->nl + 15) / 16, (s->nm + 15) / 16, &t);
   const bool sym = sym_source(s);
   double cost[2][2];
-  chunk_costs(t, prec, sym, o->K, cost);
+  chunk_costs(t, prec, sym, cost);
   const int cnt_i[2] = {t.ti_a, t.ti_b}, cnt_j[2] = {t.tj_a, t.tj_b};
   const double chunks = static_cast<double>(chunk_count(o, sym));
   double work = 0.0;
@@ -171,7 +163,7 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
   const int64_t chunks = chunk_count(o, p.sym);
   const int64_t ch = p.sym ? kPatchChunkSym : kPatchChunk;
   double cost[2][2];
-  chunk_costs(t, prec, p.sym, o->K, cost);
+  chunk_costs(t, prec, p.sym, cost);
   // k-slices per tile so that every work item costs about item_work
   for (int r = 0; r < 2; ++r)
     for (int c = 0; c < 2; ++c) {
@@ -184,11 +176,109 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
   return p;
 }
 
-PatchPlan plan_patch(const psf_obs* o, const psf_src* s, int prec, int target_wgs) {
+// Which patches run gridded.  Measured (MI355X, us per psf_patch call): the
+// dense form costs 40 us (60 in its symmetric families, whose many slices few
+// threads sum) plus its contraction, in split-BF16 0.09 ns per bin at 65 x 65,
+// 0.34 at 257 x 257 and 5.3 at 600 x 600 (patch_work at 256 CUs and 2.1 GHz
+// follows these within 40%); the gridded form 45 us, 0.06 ns per bin whatever
+// the patch, and 0.03-0.08 ns per cell.  At K = 30400 the two meet (dense 39
+// against gridded 55 us at 33 x 33, 82 against 66 at 257 x 257), below 24576
+// bins the dense call is the shorter.  PSF_PLAIN_BF16, a negative control,
+// stays dense; the mixed and stochastic arithmetics exist in the gridded form
+// only.
+GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec) {
+  constexpr int64_t kMinBins = 24576;
+  GridPlan g;
+  const int kp = launch_prec(prec, o->K, sym_source(s));
+  if (kp == PSF_PLAIN_BF16 || o->K < kMinBins) return g;
+  const int ml = grid_axis(s->nl), mm = grid_axis(s->nm);
+  if (ml == 0 || mm == 0) return g;
+  const double dense = (sym_source(s) ? 60e-6 : 40e-6) + patch_work(o, s, kp) / (kTargetWorkgroups * 2.1e9);
+  const double grid = 45e-6 + static_cast<double>(o->K) * 0.06e-9 + static_cast<double>(ml) * mm * 0.05e-9;
+  if (dense <= grid && kp != PSF_MIXED_FP16 && kp != PSF_SR_FP16) return g;
+  g.ml = ml;
+  g.mm = mm;
+  return g;
+}
+
+UvGridArgs grid_args(const psf_obs* o, const GridPlan& g, bool fused) {
+  UvGridArgs a;
+  a.o = view(o);
+  a.n_src = 0;
+  a.ml = g.ml;
+  a.mm = g.mm;
+  a.fused = fused ? 1 : 0;
+  return a;
+}
+
+bool grid_fused(const psf_obs* o) {
+  return o->win_t == nullptr && o->win_c == nullptr && !use_wave_bins(view(o));
+}
+
+UvGridSrc grid_src(const psf_src* h_src, const BinRec* rec, const float2* c, void* work, float* P, const double* dir,
+                 const double* peak) {
+  UvGridSrc s;
+  s.rec = rec;
+  s.c = c;
+  s.work = static_cast<uint8_t*>(work);
+  s.P = P;
+  s.peak = peak;
+  s.norm = 0;
+  s.maxima = nullptr;
+  s.dir = dir;
+  s.l0 = h_src->l0;
+  s.m0 = h_src->m0;
+  s.l_first = h_src->l_first;
+  s.m_first = h_src->m_first;
+  s.dl = h_src->dl;
+  s.dm = h_src->dm;
+  s.nl = h_src->nl;
+  s.nm = h_src->nm;
+  return s;
+}
+
+int run_grid(int kp, const UvGridArgs& a, hipStream_t s) {
+  hipEvent_t ev0;
+  hipError_t e;
+  if ((e = timed_launch_begin(s, &ev0)) != hipSuccess) return hip_fail(e, "timing event");
+  if ((e = launch_grid(kp, a, s)) != hipSuccess) return hip_fail(e, "gridded patch launch");
+  if ((e = timed_launch_end(s, ev0)) != hipSuccess) return hip_fail(e, "timing event");
+  return PSF_OK;
+}
+
+int run_grid_fused(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, void* work, float* P,
+                   hipStream_t s, const double* dir, bool norm) {
+  UvGridArgs g = grid_args(obs, plan.grid, true);
+  g.n_src = 1;
+  g.src[0] = grid_src(h_src, nullptr, nullptr, work, P, dir);
+  g.src[0].norm = norm ? 1 : 0;
+  return run_grid(launch_prec(prec, obs->K, plan.sym), g, s);
+}
+
+int patch_of(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, BinRec* rec, float2* c,
+             float* partial, float* P, hipStream_t s, const double* dir) {
+  if (plan.grid.ml > 0 && grid_fused(obs)) return run_grid_fused(obs, h_src, plan, prec, partial, P, s, dir, false);
+  if (obs->K > 0) {
+    const hipError_t e = launch_decorr(view(obs), h_src->l0, h_src->m0, h_src->dl, h_src->dm, nullptr, nullptr, rec, c,
+                                       nullptr, s, dir);
+    if (e != hipSuccess) return hip_fail(e, "k_decorr launch");
+  }
+  return contract(obs, h_src, plan, prec, rec, c, partial, P, s, dir);
+}
+
+PatchPlan plan_patch(const psf_obs* o, const psf_src* s, int prec, int target_wgs, bool gridded) {
+  const GridPlan g = gridded ? grid_route(o, s, prec) : GridPlan();
+  if (g.ml > 0) {
+    PatchPlan p;
+    plan_tiles((s->nl + 15) / 16, (s->nm + 15) / 16, &p.tp);
+    p.sym = sym_source(s);
+    p.grid = g;
+    p.partial_elems = grid_bytes(g, s->nm) / sizeof(float);
+    return p;
+  }
   TilePlan t;
   plan_tiles((s->nl + 15) / 16, (s->nm + 15) / 16, &t);
-  const int wgs = tile_wgs_per_cu(t, launch_prec(prec, o->K, sym_source(s)));
-  return plan_patch_items(o, s, prec, patch_work(o, s, prec) / (target_wgs * wgs));
+  return plan_patch_items(o, s, prec, patch_work(o, s, prec) / (target_wgs * tile_wgs_per_cu(t)));
 }
 
 size_t patch_workspace(const psf_obs* o, const PatchPlan& p) {
@@ -229,14 +319,18 @@ int launch_prec(int prec, int64_t K, bool sym) {
   // a few bins: split-BF16's per-term error (3 2^-16 of a term) is not
   // averaged away, so FP32 products run instead (same plan, negligible cost)
   if (kp == PSF_SPLIT_BF16 && K < kSmallK) kp = PSF_FP32;
-  // the mixed and stochastic forms need many bins, and exist for the
-  // symmetric form only
+  // the mixed and stochastic arithmetics need many bins; patches of other
+  // sizes than the symmetric families' keep split-FP16
   if ((kp == PSF_MIXED_FP16 || kp == PSF_SR_FP16) && (K < kMixedMinK || !sym)) kp = PSF_SPLIT_FP16;
   return kp;
 }
 
-// (every source of a launch shares the form)
-int contraction_prec(int prec, const BatchArgs& a) { return launch_prec(prec, a.K, a.src[0].sym != 0); }
+// (every source of a launch shares the form; the dense contraction has no
+// mixed or stochastic products)
+int contraction_prec(int prec, const BatchArgs& a) {
+  const int kp = launch_prec(prec, a.K, a.src[0].sym != 0);
+  return kp == PSF_MIXED_FP16 || kp == PSF_SR_FP16 ? PSF_SPLIT_FP16 : kp;
+}
 
 int run_batch(int prec, const BatchArgs& a, int64_t n_wg, hipStream_t s) {
   hipEvent_t ev0;
@@ -252,6 +346,12 @@ int run_batch(int prec, const BatchArgs& a, int64_t n_wg, hipStream_t s) {
 
 int contract(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, const BinRec* rec,
              const float2* c, float* partial, float* P, hipStream_t s, const double* dir, const double* peak) {
+  if (plan.grid.ml > 0) {
+    UvGridArgs g = grid_args(obs, plan.grid, false);
+    g.n_src = 1;
+    g.src[0] = grid_src(h_src, rec, c, partial, P, dir, peak);
+    return run_grid(launch_prec(prec, obs->K, plan.sym), g, s);
+  }
   BatchArgs a;
   a.n_src = 1;
   a.flush_chunks = kFlushChunks;
@@ -405,8 +505,13 @@ int psf_patch(const psf_obs* obs, const psf_src* h_src, const float* D, int prec
   const bool norm = prec_normalise(prec);
   prec = prec_base(prec);
   if (P == nullptr) return fail(PSF_EINVAL, "P is NULL");
-  const PatchPlan plan = plan_patch(obs, h_src, prec, kTargetWorkgroups);
-  const size_t need = patch_workspace(obs, plan);
+  PatchPlan plan = plan_patch(obs, h_src, prec, kTargetWorkgroups);
+  size_t need = patch_workspace(obs, plan);
+  if (ws_bytes < need && plan.grid.ml > 0) {
+    // room for the dense form's slabs but not for a large patch's grid
+    plan = plan_patch(obs, h_src, prec, kTargetWorkgroups, false);
+    need = patch_workspace(obs, plan);
+  }
   if (ws == nullptr || ws_bytes < need)
     return fail(PSF_EWORKSPACE, "psf_patch needs %zu workspace bytes, got %zu", need, ws_bytes);
   if ((st = check_device()) != PSF_OK) return st;
@@ -421,6 +526,8 @@ int psf_patch(const psf_obs* obs, const psf_src* h_src, const float* D, int prec
   w += align_up(plan.partial_elems * sizeof(float), 256);
   double* peak = reinterpret_cast<double*>(w);  // [0]: the peak; [1..]: its reduction scratch
 
+  if (plan.grid.ml > 0 && D == nullptr && grid_fused(obs))
+    return run_grid_fused(obs, h_src, plan, prec, partial, P, s, nullptr, norm);
   hipError_t e = hipSuccess;
   if (obs->K > 0) {
     e = launch_decorr(view(obs), h_src->l0, h_src->m0, h_src->dl, h_src->dm, reinterpret_cast<const float2*>(D),
@@ -473,7 +580,9 @@ extern "C" int psf_patch_noalloc(const psf_obs* obs, const psf_src* h_src, const
   if ((st = validate_src(h_src, 0)) != PSF_OK) return st;
   if ((st = validate_prec(prec)) != PSF_OK) return st;
   if (P == nullptr) return fail(PSF_EINVAL, "P is NULL");
-  const size_t need = patch_workspace(obs, plan_patch(obs, h_src, prec_base(prec), kTargetWorkgroups));
+  // the dense form's bytes decide, whichever form runs (psf_patch takes the
+  // dense one where the grid does not fit)
+  const size_t need = patch_workspace(obs, plan_patch(obs, h_src, prec_base(prec), kTargetWorkgroups, false));
   if (need > kNoAllocScratchBytes)
     return fail(PSF_EWORKSPACE,
                 "psf_patch_noalloc needs %zu bytes of scratch for this observation and patch; its fixed scratch "

@@ -30,6 +30,7 @@ namespace psf {
 namespace {
 
 constexpr size_t kRecordBudget = size_t(16) << 30;  // bytes of per-bin records per group
+constexpr size_t kGridBudget = size_t(1) << 30;     // bytes of grids per group of the fused gridded form
 constexpr int kComputeUnits = 256;                  // MI355X: one contraction workgroup per CU
 constexpr int kDefaultItemsPerCU = 2;
 const int kFlushCandidates[] = {32, 64, 128};
@@ -40,15 +41,25 @@ constexpr int kMaxItemsPerCU = 4;  // the largest candidate: bounds the workspac
 // one contraction launch share both.
 struct Family {
   int tbi0, tbi1, tbj0, tbj1, sym;
+  int ml = 0, mm = 0;  // grid of the gridded form, 0: dense contraction
   bool operator==(const Family& o) const {
-    return tbi0 == o.tbi0 && tbi1 == o.tbi1 && tbj0 == o.tbj0 && tbj1 == o.tbj1 && sym == o.sym;
+    return tbi0 == o.tbi0 && tbi1 == o.tbi1 && tbj0 == o.tbj0 && tbj1 == o.tbj1 && sym == o.sym && ml == o.ml &&
+           mm == o.mm;
   }
 };
 
-Family family_of(const psf_src& s) {
+Family dense_family(const psf_src& s) {
   TilePlan t;
   plan_tiles((s.nl + 15) / 16, (s.nm + 15) / 16, &t);
   return {t.tbi[0], t.tbi[1], t.tbj[0], t.tbj[1], sym_source(&s) ? 1 : 0};
+}
+
+// Sources of the gridded form share a launch where their grids and the form
+// (which decides the arithmetic) agree.
+Family family_of(const psf_obs* o, const psf_src& s, int prec) {
+  const GridPlan g = grid_route(o, &s, prec);
+  if (g.ml == 0) return dense_family(s);
+  return {0, 0, 0, 0, sym_source(&s) ? 1 : 0, g.ml, g.mm};
 }
 
 struct Tuning {
@@ -93,30 +104,26 @@ int parse_tuning(const char* json, std::vector<Tuning>* out) {
   return PSF_OK;
 }
 
-// Work items per CU when the caller gives no table (kp: the precision the
-// contraction runs in): one for the 257- and 129-pixel families, whose
-// items are large, in the forms that run one workgroup per CU; four for the
-// 65-pixel family, whose kernel runs two workgroups per CU (two items each);
-// in the stochastic form, which runs two workgroups per CU for every
-// family, two for the 257-pixel family and four for the 129-pixel one; two
-// otherwise.
-int default_items_per_cu(const Family& f, int kp) {
-  if (f.tbi0 == 9 && (f.tbi1 == 8 || f.tbi1 == 9)) return kp != PSF_SR_FP16 ? 1 : f.tbi1 == 8 ? 2 : 4;
+// Work items per CU when the caller gives no table: one for the 257- and
+// 129-pixel families, whose items are large; four for the 65-pixel family,
+// whose kernel runs two workgroups per CU (two items each); two otherwise.
+int default_items_per_cu(const Family& f) {
+  if (f.tbi0 == 9 && (f.tbi1 == 8 || f.tbi1 == 9)) return 1;
   if (f.tbi0 == 5 && f.tbi1 == 5 && f.tbj0 == 5) return 4;
   return kDefaultItemsPerCU;
 }
 
 // Persistent contraction workgroups for a launch of `items` work items of
-// this family in precision kp: one per CU, two where the kernel runs two.
-int64_t launch_wgs(const TilePlan& t, int64_t items, int kp) {
-  return std::min<int64_t>(items, static_cast<int64_t>(kComputeUnits) * tile_wgs_per_cu(t, kp));
+// this family: one per CU, two where the kernel runs two.
+int64_t launch_wgs(const TilePlan& t, int64_t items) {
+  return std::min<int64_t>(items, static_cast<int64_t>(kComputeUnits) * tile_wgs_per_cu(t));
 }
 constexpr int kMaxDefaultItemsPerCU = 4;
 
-Tuning tuning_for(const std::vector<Tuning>& table, const Family& f, int kp) {
+Tuning tuning_for(const std::vector<Tuning>& table, const Family& f) {
   for (const Tuning& t : table)
     if (t.fam == f) return t;
-  return {f, default_items_per_cu(f, kp), kFlushChunks};
+  return {f, default_items_per_cu(f), kFlushChunks};
 }
 
 // Group boundaries: sources ordered by family (stable), then cut into groups
@@ -126,23 +133,29 @@ struct Group {
   std::vector<int> idx;
 };
 
-int group_capacity(const psf_obs* o) {
+// Sources per group: at most kMaxBatch whose per-bin records (dense form, or
+// gridded from records) or grids fit the budgets.
+int group_capacity(const psf_obs* o, const Family& f) {
+  if (f.ml > 0 && grid_fused(o)) {
+    const size_t g = grid_bytes({f.ml, f.mm}, f.mm);
+    return static_cast<int>(std::max<size_t>(1, std::min<size_t>(kMaxBatch, kGridBudget / g)));
+  }
   const size_t rec = static_cast<size_t>(std::max<int64_t>(o->K, 1)) * (sizeof(BinRec) + sizeof(float2));
   return static_cast<int>(std::max<size_t>(1, std::min<size_t>(kMaxBatch, kRecordBudget / rec)));
 }
 
-std::vector<Group> make_groups(const psf_obs* o, int n_src, const psf_src* h) {
+std::vector<Group> make_groups(const psf_obs* o, int n_src, const psf_src* h, int prec) {
   std::vector<Family> fams;
   for (int s = 0; s < n_src; ++s) {
-    const Family f = family_of(h[s]);
+    const Family f = family_of(o, h[s], prec);
     if (std::find(fams.begin(), fams.end(), f) == fams.end()) fams.push_back(f);
   }
-  const int cap = group_capacity(o);
   std::vector<Group> groups;
   for (const Family& f : fams) {
+    const int cap = group_capacity(o, f);
     Group g{f, {}};
     for (int s = 0; s < n_src; ++s) {
-      if (!(family_of(h[s]) == f)) continue;
+      if (!(family_of(o, h[s], prec) == f)) continue;
       g.idx.push_back(s);
       if (static_cast<int>(g.idx.size()) == cap) {
         groups.push_back(g);
@@ -162,6 +175,13 @@ struct GroupPlan {
 
 GroupPlan plan_group(const psf_obs* o, const psf_src* h, const Group& g, int prec, int items_per_cu) {
   GroupPlan gp;
+  if (g.fam.ml > 0) {  // gridded: one grid per source in place of the slabs
+    for (int s : g.idx) {
+      gp.plans.push_back(plan_patch(o, &h[s], prec, kTargetWorkgroups));
+      gp.partial_elems += align_up(gp.plans.back().partial_elems, 64);
+    }
+    return gp;
+  }
   double work = 0.0;
   for (int s : g.idx) work += patch_work(o, &h[s], prec);
   const double item_work = work / (static_cast<double>(kComputeUnits) * items_per_cu);
@@ -182,10 +202,10 @@ size_t records_bytes(const psf_obs* o) {
 // largest group, for the largest items-per-CU a tuning table may ask][the
 // normalisation peaks of up to kMaxBatch sources].
 size_t batch_workspace_for(const psf_obs* o, int n_src, const psf_src* h, int prec, int max_items_per_cu) {
-  const std::vector<Group> groups = make_groups(o, n_src, h);
+  const std::vector<Group> groups = make_groups(o, n_src, h, prec);
   size_t rec = 0, part = 0;
   for (const Group& g : groups) {
-    rec = std::max(rec, g.idx.size() * records_bytes(o));
+    if (!(g.fam.ml > 0 && grid_fused(o))) rec = std::max(rec, g.idx.size() * records_bytes(o));
     part = std::max(part, plan_group(o, h, g, prec, max_items_per_cu).partial_elems * sizeof(float));
   }
   return align_up(rec, 256) + align_up(part, 256) + kMaxBatch * kPeakBytes;
@@ -193,21 +213,25 @@ size_t batch_workspace_for(const psf_obs* o, int n_src, const psf_src* h, int pr
 
 int run_batched(const psf_obs* obs, int n_src, const psf_src* h, const psf_src* d, int prec, bool norm,
                 const std::vector<Tuning>& table, float* P_all, void* ws, hipStream_t st, size_t peak_off) {
-  const std::vector<Group> groups = make_groups(obs, n_src, h);
+  const std::vector<Group> groups = make_groups(obs, n_src, h, prec);
   const size_t rec = records_bytes(obs);
   size_t rec_area = 0;
-  for (const Group& g : groups) rec_area = std::max(rec_area, g.idx.size() * rec);
+  for (const Group& g : groups)
+    if (!(g.fam.ml > 0 && grid_fused(obs))) rec_area = std::max(rec_area, g.idx.size() * rec);
   uint8_t* base = static_cast<uint8_t*>(ws);
   float* partial = reinterpret_cast<float*>(base + align_up(rec_area, 256));
   const ObsView ov = view(obs);
   for (const Group& g : groups) {
-    const Tuning tu = tuning_for(table, g.fam, launch_prec(prec, obs->K, g.fam.sym != 0));
+    const Tuning tu = tuning_for(table, g.fam);
     const GroupPlan gp = plan_group(obs, h, g, prec, tu.items_per_cu);
     BatchArgs a;
     a.n_src = static_cast<int>(g.idx.size());
     a.flush_chunks = tu.flush;
     a.K = obs->K;
     a.n_items = gp.items;
+    const bool fused = g.fam.ml > 0 && grid_fused(obs);
+    UvGridArgs ga = grid_args(obs, {g.fam.ml, g.fam.mm}, fused);
+    ga.n_src = a.n_src;
     int64_t item0 = 0;
     size_t poff = 0;
     for (int q = 0; q < a.n_src; ++q) {
@@ -216,22 +240,29 @@ int run_batched(const psf_obs* obs, int n_src, const psf_src* h, const psf_src* 
       BinRec* rec = reinterpret_cast<BinRec*>(r);
       float2* c = reinterpret_cast<float2*>(r + align_up(static_cast<size_t>(obs->K) * sizeof(BinRec), 256));
       const double* dir = reinterpret_cast<const double*>(d + s);
-      if (obs->K > 0) {
+      if (obs->K > 0 && !fused) {
         hipError_t e = launch_decorr_sources(ov, dir, 0, 1, rec, c, 0, st);
         if (e != hipSuccess) return hip_fail(e, "k_decorr launch");
       }
       double* peak = reinterpret_cast<double*>(base + peak_off + q * kPeakBytes);
-      if (norm) {
+      if (norm && !fused) {
         hipError_t e = launch_peak(c, obs->K, peak + 1, peak, st);
         if (e != hipSuccess) return hip_fail(e, "peak launch");
       }
       a.src[q] = src_plan(&h[s], gp.plans[q], rec, c, partial + poff, P_all + h[s].out_off, dir,
                           norm ? peak : nullptr);
       a.src[q].item0 = item0;
-      item0 += tile_plan_items(gp.plans[q].tp);
+      ga.src[q] = grid_src(&h[s], rec, c, partial + poff, P_all + h[s].out_off, dir, norm ? peak : nullptr);
+      ga.src[q].norm = norm ? 1 : 0;
+      if (g.fam.ml == 0) item0 += tile_plan_items(gp.plans[q].tp);
       poff += align_up(gp.plans[q].partial_elems, 64);
     }
-    const int64_t n_wg = launch_wgs(gp.plans[0].tp, gp.items, contraction_prec(prec, a));
+    if (g.fam.ml > 0) {
+      const int rc = run_grid(launch_prec(prec, obs->K, g.fam.sym != 0), ga, st);
+      if (rc != PSF_OK) return rc;
+      continue;
+    }
+    const int64_t n_wg = launch_wgs(gp.plans[0].tp, gp.items);
     int rc = run_batch(prec, a, n_wg, st);
     if (rc != PSF_OK) return rc;
   }
@@ -257,6 +288,8 @@ size_t autotune_workspace(const psf_obs* o, int n_src, const psf_src* h, int pre
   for (int q = 0; q < n_src; ++q) {
     const double iw = patch_work(o, &h[q], prec) / (static_cast<double>(kComputeUnits) * kMaxItemsPerCU);
     part = std::max(part, plan_patch_items(o, &h[q], prec, iw).partial_elems);
+    const GridPlan g = grid_route(o, &h[q], prec);
+    if (g.ml > 0) part = std::max(part, grid_bytes(g, h[q].nm) / sizeof(float));
     pix = std::max(pix, static_cast<size_t>(h[q].nl) * h[q].nm);
   }
   return records_bytes(o) + align_up(part * sizeof(float), 256) + align_up(pix * sizeof(float), 256);
@@ -306,7 +339,7 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
   std::vector<Family> fams;
   std::vector<int> rep;
   for (int q = 0; q < n_src; ++q) {
-    const Family f = family_of(h_srcs[q]);
+    const Family f = dense_family(h_srcs[q]);
     if (std::find(fams.begin(), fams.end(), f) == fams.end()) {
       fams.push_back(f);
       rep.push_back(q);
@@ -317,6 +350,8 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
     for (int ipc : kItemsCandidates) {
       const double iw = patch_work(obs, &h_srcs[q], prec) / (static_cast<double>(kComputeUnits) * ipc);
       part = std::max(part, plan_patch_items(obs, &h_srcs[q], prec, iw).partial_elems);
+      const GridPlan g = grid_route(obs, &h_srcs[q], prec);
+      if (g.ml > 0) part = std::max(part, grid_bytes(g, h_srcs[q].nm) / sizeof(float));
     }
   const size_t need = autotune_workspace(obs, n_src, h_srcs, prec);
   if (ws == nullptr || ws_bytes < need)
@@ -346,8 +381,12 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
     }
     double best_ms = 1e30;
     int best_ipc = kDefaultItemsPerCU, best_flush = kFlushChunks;
+    // a gridded patch has no launch shape to choose: timed once, as it runs
+    const PatchPlan own = plan_patch(obs, &src, prec, kTargetWorkgroups);
+    const bool gridded = own.grid.ml > 0;
     for (int ipc : kItemsCandidates) {
       for (int fl : kFlushCandidates) {
+        if (gridded && (ipc != kItemsCandidates[0] || fl != kFlushCandidates[0])) continue;
         const double iw = patch_work(obs, &src, prec) / (static_cast<double>(kComputeUnits) * ipc);
         const PatchPlan plan = plan_patch_items(obs, &src, prec, iw);
         BatchArgs a;
@@ -356,10 +395,17 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
         a.K = obs->K;
         a.src[0] = src_plan(&src, plan, rec, c, partial, P, nullptr);
         a.n_items = tile_plan_items(plan.tp);
-        const int64_t n_wg = launch_wgs(plan.tp, a.n_items, contraction_prec(prec, a));
+        const int64_t n_wg = launch_wgs(plan.tp, a.n_items);
         constexpr int kReps = 3;
         const int kp = contraction_prec(prec, a);
-        if ((e = launch_patch(kp, a, n_wg, s)) != hipSuccess) {  // warm-up
+        auto launch = [&]() {
+          if (!gridded) return launch_patch(kp, a, n_wg, s);
+          UvGridArgs g = grid_args(obs, own.grid, false);
+          g.n_src = 1;
+          g.src[0] = grid_src(&src, rec, c, partial, P, nullptr);
+          return launch_grid(kp, g, s);
+        };
+        if ((e = launch()) != hipSuccess) {  // warm-up
           rc = hip_fail(e, "k_patch launch");
           break;
         }
@@ -367,7 +413,7 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
           rc = hip_fail(e, "hipEventRecord");
           break;
         }
-        for (int r = 0; r < kReps && e == hipSuccess; ++r) e = launch_patch(kp, a, n_wg, s);
+        for (int r = 0; r < kReps && e == hipSuccess; ++r) e = launch();
         if (e != hipSuccess) {
           rc = hip_fail(e, "k_patch launch");
           break;
@@ -381,8 +427,8 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
         ms /= kReps;
         if (ms < best_ms) {
           best_ms = ms;
-          best_ipc = ipc;
-          best_flush = fl;
+          if (!gridded) best_ipc = ipc;
+          if (!gridded) best_flush = fl;
         }
       }
       if (rc != PSF_OK) break;

@@ -295,11 +295,7 @@ int psf_clean_hogbom(const psf_obs* obs, const psf_src* h_grid, float* residual,
     src.l0 = h_grid->l_first + i * h_grid->dl;
     src.m0 = h_grid->m_first + j * h_grid->dm;
     if (src.l0 * src.l0 + src.m0 * src.m0 >= 1.0) return fail(PSF_EINVAL, "peak pixel outside the sky");
-    if (obs->K > 0 &&
-        (e = launch_decorr(view(obs), src.l0, src.m0, src.dl, src.dm, nullptr, nullptr, rec, c, nullptr, s)) !=
-            hipSuccess)
-      return hip_fail(e, "k_decorr launch");
-    if ((st = contract(obs, &src, plan, prec, rec, c, partial, P, s)) != PSF_OK) return st;
+    if ((st = patch_of(obs, &src, plan, prec, rec, c, partial, P, s)) != PSF_OK) return st;
     hipLaunchKernelGGL(k_clean_subtract, dim3(static_cast<unsigned>((n + kMaxThreads - 1) / kMaxThreads)),
                        dim3(kMaxThreads), 0, s, residual, P, n, peak, static_cast<float>(gain));
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_clean_subtract launch");
@@ -352,10 +348,7 @@ int psf_clean_hogbom_device(const psf_obs* obs, const psf_src* h_grid, float* re
     hipLaunchKernelGGL(k_clean_place, dim3(1), dim3(1), 0, s, state, peak, n, h_grid->nm, threshold, gain, it,
                        comp_i, comp_j, comp_amp, n_comp);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "peak search launch");
-    if ((e = launch_decorr(view(obs), 0.0, 0.0, h_grid->dl, h_grid->dm, nullptr, nullptr, rec, c, nullptr, s,
-                           dir)) != hipSuccess)
-      return hip_fail(e, "k_decorr launch");
-    if ((st = contract(obs, h_grid, plan, prec, rec, c, partial, P, s, dir)) != PSF_OK) return st;
+    if ((st = patch_of(obs, h_grid, plan, prec, rec, c, partial, P, s, dir)) != PSF_OK) return st;
     hipLaunchKernelGGL(k_clean_subtract_dev, dim3(static_cast<unsigned>((n + kMaxThreads - 1) / kMaxThreads)),
                        dim3(kMaxThreads), 0, s, residual, P, n, peak, state);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_clean_subtract_dev launch");

@@ -1,0 +1,57 @@
+// The gridded form of the patch: host plan and launchers (k_grid.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "psf_kernels.hpp"
+
+namespace psf {
+
+// Grid of one patch, in cells along the row and column axes (powers of two).
+// ml = 0: the patch takes the dense contraction.
+struct GridPlan {
+  int ml = 0, mm = 0;
+};
+
+// Cells per axis of a patch of n pixels: the smallest power of two (at least
+// 32) that oversamples it by 1.96 or more; 0 if that exceeds kGridMaxAxis.
+constexpr int kGridMaxAxis = 2048;
+int grid_axis(int n);
+// Bytes of one source's grid, half-transformed grid and state.
+size_t grid_bytes(const GridPlan& g, int nm);
+
+// Per-source part of a gridded launch; direction and grid as in SrcPlan.
+// Fused launches form the decorrelation factors from the observation; others
+// read records and coefficients.
+struct UvGridSrc {
+  const BinRec* rec;
+  const float2* c;
+  uint8_t* work;  // grid_bytes: cells, half-transformed grid, state
+  float* P;
+  const double* peak;  // not fused: see SrcPlan
+  const double* dir;
+  uint32_t* maxima;  // filled by launch_grid
+  double l0, m0, l_first, m_first, dl, dm;
+  int nl, nm;
+  int norm;  // fused: divide by 2 sum Re c, summed here
+};
+
+constexpr int kGridMaxWgs = 4096;  // spreading workgroups per source
+
+struct UvGridArgs {
+  ObsView o;
+  int n_src;
+  int ml, mm;  // cells per axis (every source of the launch)
+  int fused;
+  // filled by launch_grid: ceil(log2 K), log2 of the bins a tile may sum,
+  // spreading workgroups and the contiguous bins of each, init blocks
+  int log_k, log_tile, n_wg, n_init;
+  int64_t wg_bins;
+  UvGridSrc src[kMaxBatch];
+};
+
+// Clears the grids, finds the scale, spreads the bins, transforms and writes
+// the patches of every source of `a`.
+hipError_t launch_grid(int prec, UvGridArgs a, hipStream_t stream);
+
+}  // namespace psf

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/psf.h"
+#include "psf_grid.hpp"
 #include "psf_kernels.hpp"
 
 namespace psf {
@@ -26,6 +27,7 @@ struct PatchPlan {
   TilePlan tp;
   size_t partial_elems;
   bool sym;  // symmetric form of the contraction (see k_patch.hip)
+  GridPlan grid;  // ml > 0: the patch runs gridded (k_grid.hip) and partial_elems is its grid's size
 };
 
 // Whether a source's contraction runs in the symmetric form: a patch size
@@ -52,10 +54,26 @@ ObsView view(const psf_obs* o);
 size_t align_up(size_t x, size_t a);
 // Matrix-core / generator cost of a source's whole patch (SIMD cycles).
 double patch_work(const psf_obs* o, const psf_src* s, int prec);
+// The grid of a patch that runs in the gridded form, ml = 0 for one that runs
+// as a dense contraction.
+GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec);
+// Fills everything of a gridded launch but its sources.
+UvGridArgs grid_args(const psf_obs* o, const GridPlan& g, bool fused);
+// Whether a gridded patch forms its decorrelation factors while spreading
+// (boxcar averaging, bins of one lane each), without records.
+bool grid_fused(const psf_obs* o);
+int run_grid_fused(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, void* work, float* P,
+                   hipStream_t s, const double* dir, bool norm);
+UvGridSrc grid_src(const psf_src* h_src, const BinRec* rec, const float2* c, void* work, float* P, const double* dir,
+                 const double* peak = nullptr);
+// The gridded patches of the sources of a, in the arithmetic prec (kp:
+// launch_prec's).
+int run_grid(int kp, const UvGridArgs& a, hipStream_t s);
 // Tile plan whose work items each cost about item_work.
 PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double item_work);
-// Tile plan with about target_wgs work items.
-PatchPlan plan_patch(const psf_obs* o, const psf_src* s, int prec, int target_wgs);
+// Plan of one patch: its grid where grid_route takes the gridded form (and
+// gridded allows it), else a tile plan with about target_wgs work items.
+PatchPlan plan_patch(const psf_obs* o, const psf_src* s, int prec, int target_wgs, bool gridded = true);
 size_t patch_workspace(const psf_obs* o, const PatchPlan& p);
 // The precision a contraction runs in for the caller's prec, K bins and
 // form (small K and non-symmetric patches change it, see kSmallK,
@@ -75,6 +93,11 @@ int method2_patch_device_dir(int32_t N, double cell, const float* S, const doubl
 int contract(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, const BinRec* rec,
              const float2* c, float* partial, float* P, hipStream_t s, const double* dir = nullptr,
              const double* peak = nullptr);
+
+// One patch with its decorrelation factors formed in the call (rec, c and
+// partial: psf_patch's workspace).
+int patch_of(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, BinRec* rec, float2* c,
+             float* partial, float* P, hipStream_t s, const double* dir = nullptr);
 
 SrcPlan src_plan(const psf_src* h_src, const PatchPlan& plan, const BinRec* rec, const float2* c, float* partial,
                  float* P, const double* dir, const double* peak = nullptr);

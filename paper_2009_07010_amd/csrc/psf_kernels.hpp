@@ -30,10 +30,8 @@ struct BinRec {
   float2 step_a, step_b;  // FP64-reduced, FP32 sin/cos
 };
 
-// kMixedFP16: symmetric form only; the row operand (cos and sin) is one FP16
-// value, rounded stochastically, the column operand is split hi + lo in
-// FP16 (two products).  kSRFP16: symmetric form only; both operands one
-// stochastically rounded FP16 value each (one product).
+// kMixedFP16 and kSRFP16 exist in the gridded form only (k_grid.hip): one
+// operand, or both, one stochastically rounded FP16 value.
 enum Prec : int { kFP32 = 0, kSplitBF16 = 1, kSplitFP16 = 2, kPlainBF16 = 3, kMixedFP16 = 4, kSRFP16 = 5 };
 
 // Tiling of one patch.  Row tiles come in two heights (ti_a tiles of tbi[0]
@@ -102,6 +100,8 @@ constexpr double kAdjointScale = 1.0 / 4096.0;
 hipError_t launch_decorr(const ObsView& o, double l0, double m0, double dl, double dm, const float2* D_in,
                          float2* D_out, BinRec* rec_out, float2* c_out, float2* coef_out, hipStream_t stream,
                          const double* dir = nullptr);
+// Whether few long bins make a wave per bin the better decorrelation.
+bool use_wave_bins(const ObsView& o);
 // Method-1 (sinc) decorrelation factors, written as (D, 0).
 hipError_t launch_decorr_sinc(const ObsView& o, double l0, double m0, float2* D_out, hipStream_t stream);
 // Records of n_src sources in one launch: source y's direction and grid are
@@ -124,9 +124,8 @@ void plan_tiles(int nbi, int nbj, TilePlan* tp);
 // 65, 129 or 257 and nm falls in the same tile family).
 bool sym_patch_size(int nl, int nm);
 // Contraction workgroups one compute unit runs at once for this tile plan
-// and launch precision (its kernel's occupancy): 2 for the 5 x 5 block tiles
-// and for the stochastic form, else 1.
-int tile_wgs_per_cu(const TilePlan& t, int prec);
+// (its kernel's occupancy): 2 for the 5 x 5 block tiles, else 1.
+int tile_wgs_per_cu(const TilePlan& t);
 // Blocks of the busiest SIMD (its two contraction waves) of a tbi x tbj tile.
 int tile_max_simd_blocks(int tbi, int tbj, bool sym);
 size_t tile_plan_partial_elems(const TilePlan& tp);

@@ -229,13 +229,9 @@ int psf_method2_spectrum(const psf_obs* obs, int32_t N, double cell, int prec, f
                                             align_up(static_cast<size_t>(obs->K) * sizeof(float2), 256));
   float* Peff = reinterpret_cast<float*>(w + L.Peff);
   hipError_t e;
-  if (obs->K > 0) {
-    // At the phase centre every sample's phase difference is exactly 0, so
-    // D_k = 1 and u' = u: the effective PSF.
-    e = launch_decorr(view(obs), 0.0, 0.0, cell, cell, nullptr, nullptr, rec, c, nullptr, s);
-    if (e != hipSuccess) return hip_fail(e, "k_decorr launch");
-  }
-  if ((st = contract(obs, &g, plan, prec, rec, c, partial, Peff, s)) != PSF_OK) return st;
+  // At the phase centre every sample's phase difference is exactly 0, so
+  // D_k = 1 and u' = u: the effective PSF.
+  if ((st = patch_of(obs, &g, plan, prec, rec, c, partial, Peff, s)) != PSF_OK) return st;
   const int64_t NN = static_cast<int64_t>(N) * N;
   float2* Sc = reinterpret_cast<float2*>(S);
   hipLaunchKernelGGL(k_m2_load, dim3(static_cast<unsigned>((NN + 255) / 256)), dim3(256), 0, s, Peff, g.nm, Sc, N);
