@@ -39,11 +39,15 @@
 // FUSED, the boxcar case, forms D_k in the same kernel: bins leave no records
 // in memory (40 bytes each way, 10.6 GB per source at K = 265M).
 //
-// Measured (one 257 x 257 patch, K = 5.8M, stochastic FP16): 360 us per call,
-// spreading 340, against 1400 us of the dense contraction it replaced (FP32
-// 400 against 7510); per source at K = 265M 7.1 ms against 37 on average.  Bound: vector issue (two thirds of the cycles at K = 5.8M with 40
-// samples per bin: the samples' sines and cosines first, then the taps),
-// then LDS and the latency of the staging.
+// Measured (one 257 x 257 patch, K = 5.8M in bins of 10 x 4 samples,
+// stochastic FP16): 307 us per call, spreading 275, against 1400 us of the
+// dense contraction it replaced (FP32 345 against 7540); per source at K =
+// 265M of baseline-dependent bins 4.4 ms against 37.  The workgroups' time at
+// K = 5.8M: half is the set-up of chunks and their tables (latency), a third the
+// samples' factors, a sixth staging and contraction; at one sample per bin
+// (K = 116M) staging and contraction are 60% and the factors 30%, bound by
+// vector issue (two thirds of the cycles) and LDS (one third), which three
+// waves per SIMD overlap only in part.
 #include <algorithm>
 
 #include "psf_device.hpp"
@@ -68,6 +72,9 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kTileSide = 45;     // a tile grows to about this side when its chunk leaves room
 constexpr int kTabRows = 1024;    // samples of a chunk whose projections sit in LDS
 constexpr int kTabFreq = 512;     // frequency bins whose centre frequencies do
+constexpr int kGridMaxLevels = 6, kLeastSpan = 1024;  // of spans
+constexpr int kCutBlocks = 8;     // workgroups that cut the bins into spans
+constexpr int kEvenMin = 3, kEvenMax = 16;  // channels per bin summed as evenly spaced
 constexpr int kRun = 8;           // batches of 64 bins summed in FP32 before a window is folded (2^9 bins)
 constexpr int kInitBlocks = 512;
 constexpr int kMargin = 1;        // cells added around a tile's sampled extent
@@ -114,7 +121,9 @@ struct UvGridState {
   uint32_t poison;
   uint32_t pad[63];
   uint32_t maxima[kInitBlocks];
-  double peak[kGridMaxWgs];
+  uint32_t next;  // spans handed out beyond the workgroups' first
+  double peak[kGridMaxSpans];
+  int64_t first[kGridMaxSpans];  // source 0, fused: first bin of every span
 };
 
 template <class S>
@@ -149,18 +158,17 @@ __device__ __forceinline__ void taps(float f, float t[kW]) {
   t[4] = e;
 }
 
+__device__ __forceinline__ int wrap(int d, int M) { return d & (M - 1); }  // M: a power of two
+
 // Position of frequency f step (turns) on a torus of M cells: nearest cell
-// (0 .. M - 1) and the offset from it; finite input only.
+// (0 .. M - 1) and the offset from it.  A frequency that is not finite has an
+// offset that is not, in some cell.
 __device__ __forceinline__ void torus(double f, double step, int M, int* cell, float* off) {
-  double t = f * step;
-  t = (t - floor(t)) * M;
+  const double t = __builtin_amdgcn_fract(f * step) * M;
   const double n = rint(t);
   *off = static_cast<float>(t - n);
-  const int i = static_cast<int>(n);
-  *cell = i >= M ? i - M : i;
+  *cell = wrap(static_cast<int>(n), M);
 }
-
-__device__ __forceinline__ int wrap(int d, int M) { return d < 0 ? d + M : d; }  // d > -M
 
 typedef const __attribute__((address_space(4))) UvGridSrc karg_gsrc;
 __device__ __forceinline__ karg_gsrc& gsrc(int s) {
@@ -184,17 +192,123 @@ __device__ __forceinline__ int max_exponent(karg_gsrc& s, int n) {
 
 }  // namespace
 
+namespace {
+
+// The bins are handed out in contiguous spans of equal or falling cost: with
+// one level, a span per workgroup; with more, a span of half the workgroup's
+// even share, one of a quarter and so on, the last two alike, so that
+// workgroups that find their spans cheaper take more of the later ones, while
+// most bins lie in long spans (whose tracks are cut into fewer chunks).
+// First unit of span i, in units of the last level's span.
+__host__ __device__ inline int span_units(const UvGridArgs& a, int i) {
+  const int q = i / a.n_wg, all = 1 << (a.levels - 1);
+  return a.n_wg * (all - (all >> q)) + (i - q * a.n_wg) * (all >> (q + 1) > 0 ? all >> (q + 1) : 1);
+}
+
+// What a bin of nt x nc samples costs to spread, from the cycles measured per
+// 64 bins: staging and contraction, the samples' factors (a row of evenly
+// spaced channels costs little more than one channel), and the set-up of its
+// chunk, which holds at most kTabRows samples in time.
+__device__ __forceinline__ float bin_cost(int nt, int nc, int nf) {
+  const float row = nc >= kEvenMin && nc <= kEvenMax ? 600.f + 20.f * nc : 350.f * nc;
+  return 3500.f + nt * (row + 3500.f / nf);
+}
+
+// The fused form's spans, equal parts of the cost rather than of the bins:
+// the bins of baseline-dependent averaging are of one to hundreds of samples.
+// A thread sums consecutive baselines; of kCutBlocks workgroups, each places
+// the spans that begin in its share of every thread's baselines.
+__device__ void cut_spans(const UvGridArgs& a, int block, int64_t* first) {
+  __shared__ double wave_sum[4];
+  const ObsView& o = a.o;
+  const int per = (o.n_bl + 255) / 256;
+  const int b0 = min(o.n_bl, static_cast<int>(threadIdx.x) * per), b1 = min(o.n_bl, b0 + per);
+  float w = 0.f;  // of a bin of the baseline last looked at
+  auto cost = [&](int b) {
+    const int nt = max(1, o.bl_bin[2 * b]), nc = max(1, o.bl_bin[2 * b + 1]);
+    w = bin_cost(min(nt, o.n_t), min(nc, o.n_ch), 1 + (o.n_ch - 1) / nc);
+    return static_cast<double>(w) * static_cast<double>((b + 1 < o.n_bl ? o.koff[b + 1] : o.K) - o.koff[b]);
+  };
+  // the first kCutBlocks baselines of the thread (up to 2048 in all) stay in
+  // registers: one round of loads
+  double own[kCutBlocks], sum = 0.0;
+  float own_w[kCutBlocks];
+#pragma unroll
+  for (int r = 0; r < kCutBlocks; ++r) {
+    own[r] = b0 + r < b1 ? cost(b0 + r) : 0.0;
+    own_w[r] = w;
+  }
+#pragma unroll
+  for (int r = 0; r < kCutBlocks; ++r) sum += own[r];
+  for (int b = b0 + kCutBlocks; b < b1; ++b) sum += cost(b);
+  double upto = sum;  // of this thread and those before it
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int step = 1; step < 64; step <<= 1) {
+    const double v = __shfl_up(upto, step);
+    if (lane >= step) upto += v;
+  }
+  if (lane == 63) wave_sum[wave] = upto;
+  double x = __shfl_up(upto, 1);  // where this thread's first baseline begins
+  __syncthreads();
+  if (lane == 0) x = 0.0;
+  double before = 0.0, all = 0.0;
+  for (int q = 0; q < 4; ++q) {
+    if (q == wave) before = all;
+    all += wave_sum[q];
+  }
+  x += before;
+  const double end = lane == 63 ? before + wave_sum[wave] : upto + before;  // the next thread's x
+  const double unit = all / span_units(a, a.n_span);
+  // the spans that begin in [x0, x1), the cost of baseline b's bins
+  auto place = [&](int b, double x0, double x1, float bin) {
+    const int u = static_cast<int>(x0 / unit) - 1;
+    int i = 0, q = 0;
+    for (; q < a.levels && span_units(a, (q + 1) * a.n_wg) <= u; ++q) i += a.n_wg;
+    i += max(0, u - span_units(a, i)) / max(1, 1 << (a.levels - 1) >> (q + 1));
+    for (; i < a.n_span; ++i) {
+      const double at = span_units(a, i) * unit;
+      if (at < x0) continue;
+      if (!(at < x1)) break;
+      first[i] = o.koff[b] + static_cast<int64_t>((at - x0) / bin);
+    }
+  };
+  double x0 = x, x1 = x;
+  float bin = 1.f;
+#pragma unroll
+  for (int r = 0; r < kCutBlocks; ++r) {
+    const double next = b0 + r + 1 == b1 ? end : x + own[r];
+    if (r == block) {
+      x0 = x;
+      x1 = next;
+      bin = own_w[r];
+    }
+    x = next;
+  }
+  if (b0 + block < b1) place(b0 + block, x0, x1, bin);
+  for (int b = b0 + kCutBlocks; b < b1; ++b) {
+    const double next = b + 1 < b1 ? x + cost(b) : (cost(b), end);
+    if ((b - b0) % kCutBlocks == block) place(b, x, next, w);
+    x = next;
+  }
+}
+
+}  // namespace
+
 // Zeroes the cells and finds the largest |.| of the n floats that scale a
 // source: its coefficients' parts, or in the fused form the weights (|D| <= 1;
 // one pass, by source 0's blocks, for all sources).  Block q leaves its
 // largest as bits in maxima[q]; later kernels take the largest of those.
 __global__ __launch_bounds__(256) void k_grid_init(UvGridArgs a) {
   karg_gsrc& s = gsrc(blockIdx.y);
-  const int64_t id = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, step = static_cast<int64_t>(gridDim.x) * 256;
+  if (static_cast<int>(blockIdx.x) >= a.n_init) {  // kCutBlocks more where fused
+    if (blockIdx.y == 0) cut_spans(a, blockIdx.x - a.n_init, state_of(a, s)->first);
+    return;
+  }
+  const int64_t id = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, step = static_cast<int64_t>(a.n_init) * 256;
   g_u32x4* q = reinterpret_cast<g_u32x4*>(s.work);
   const int64_t ncell = static_cast<int64_t>(a.ml) * a.mm;
   for (int64_t i = id; i < ncell; i += step) q[i] = g_u32x4{0, 0, 0, 0};
-  if (id == 0) state_of(a, s)->poison = 0;
+  if (id == 0) state_of(a, s)->poison = state_of(a, s)->next = 0;
   if (a.fused && blockIdx.y > 0) return;
   const uint32_t* c = reinterpret_cast<const uint32_t*>(a.fused ? a.o.W : reinterpret_cast<const float*>(s.c));
   const int64_t n = a.fused ? a.o.K : 2 * a.o.K;
@@ -228,7 +342,7 @@ __host__ __device__ constexpr Mode row_mode(int prec) {
 __host__ __device__ constexpr Mode col_mode(int prec) { return prec == kMixedFP16 ? kMFP16 : row_mode(prec); }
 
 // One axis' nine operand values of a bin into the stage, at rows row0 ..
-// row0 + 8, column `lane` (rw: the bin's random word).
+// row0 + 8, column `lane` (rw: a random word of the bin and axis).
 template <Mode M>
 __device__ __forceinline__ void stage_taps(g_lds* st, int row0, int lane, const float t[kW], uint32_t rw) {
   if constexpr (M == kM32) {
@@ -371,11 +485,17 @@ __device__ __forceinline__ int to_int(float x, float scale, uint32_t h) {
 }
 
 // A window's accumulators (origin wx, wy) into the tile, cells outside the
-// tile straight into the grid.  h: a random word of the fold.
+// tile straight into the grid.  h: a random word of the fold.  A bin whose
+// u', v' or c is not finite leaves some accumulator so: the source is poisoned.
 __device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, int* tre, int* tim, int wx, int wy,
-                                            float to_fixed, int lane, uint32_t h, const g_f32x4& re, const g_f32x4& im) {
+                                            float to_fixed, int lane, uint32_t h, const g_f32x4& re, const g_f32x4& im,
+                                            UvGridState* state) {
   const int j = lane & 15, i0 = 4 * (lane >> 4);
   const int rx = wrap(wx - t.ox, cells.ml), ry = wrap(wy - t.oy, cells.mm);
+  float all = 0.f;  // 0 unless one is not finite
+#pragma unroll
+  for (int e = 0; e < 4; ++e) all = __builtin_fmaf(0.f, re[e], __builtin_fmaf(0.f, im[e], all));
+  if (all != 0.f) state->poison = 1;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     const int vr = to_int(re[e], to_fixed, h), vi = to_int(im[e], to_fixed, h + 0x9E3779B1u);
@@ -392,6 +512,13 @@ __device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, i
       add_cell(cells, gi, gj, 1, vi);
     }
   }
+}
+
+__device__ __forceinline__ double uniform(double x) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
+  const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)));
+  return __builtin_bit_cast(double, hi << 32 | lo);
 }
 
 __device__ __forceinline__ int first_lane(uint64_t m) { return __builtin_ctzll(m); }
@@ -413,6 +540,9 @@ __device__ __forceinline__ int window_origin(int a, int b, int M) {
 struct Chunk {
   int64_t base, la, lb, t0;
   int b, nf, nt, nc, rows;
+  int left;   // samples from the chunk's first on (at most 2^30)
+  int full;   // samples of a whole bin
+  float inv;  // 1 / full
 };
 
 // Sum over one bin's samples of exp(-2 pi i phi), phi = (A_t nu_c - A_k nu_k)
@@ -424,54 +554,156 @@ template <int NCH>
 __device__ __forceinline__ void sum_group(const double* tab, int pitch, int ntu, int ntl, const double nu[4], int nch,
                                           double aknu, float* sre, float* sim) {
 #pragma clang fp contract(off)
-  for (int t = 0; t < ntu; ++t) {
-    const double at = tab[t * pitch];
-    if (t < ntl) {
+  constexpr int kRows = NCH == 1 ? 4 : NCH == 2 ? 2 : 1;  // four sine-cosine pairs at a time, for their latency
+  auto rows = [&](int t, auto many) {
+#pragma clang fp contract(off)
+    constexpr int n = decltype(many)::value;
+    double at[n];
+#pragma unroll
+    for (int i = 0; i < n; ++i) at[i] = tab[(t + i) * pitch];
+#pragma unroll
+    for (int i = 0; i < n; ++i)
 #pragma unroll
       for (int j = 0; j < (NCH == 0 ? 4 : NCH); ++j) {
-        if (NCH == 0 && j >= nch) continue;
-        const cf32 e = expi_turns_hw(-((at * nu[j] - aknu) * kInvCLight));
-        *sre += e.re;
-        *sim += e.im;
+        const cf32 e = expi_turns_hw(-((at[i] * nu[j] - aknu) * kInvCLight));
+        const bool on = t + i < ntl && (NCH != 0 || j < nch);
+        *sre += on ? e.re : 0.f;
+        *sim += on ? e.im : 0.f;
       }
+  };
+  int t = 0;
+  for (; t + kRows <= ntu; t += kRows) rows(t, std::integral_constant<int, kRows>());
+  if (kRows > 1)
+    for (; t < ntu; ++t) rows(t, std::integral_constant<int, 1>());
+}
+
+// The same sum for n evenly spaced channels about nu_k (half spacing h, in
+// s/m): a sample row's channels sum to exp(-2 pi i (A_t - A_k) nu_k / c)
+// times the Dirichlet kernel 1 + 2 cos x + ... + 2 cos((n - 1) x / 2) (n odd)
+// or 2 cos(x / 2) + 2 cos(3 x / 2) + ... (n even), x = 4 pi A_t h, so that a
+// row costs two sine-cosine pairs and three operations per channel pair
+// instead of a pair and eight operations per channel.  The cosines step by
+// their differences, d <- d - 4 sin^2(x / 2) a, a <- a + d, which loses
+// nothing at small x.  From 3 channels (2 save nothing) to 16 (the steps'
+// rounding grows with their number): 10 x 4 samples take 490 vector
+// instructions per 64 bins with all else, 1270 channel by channel.
+// m: (n - 1) / 2, at most mm; SAME: every lane has mm and ntu rows.  Half the
+// sum is returned.
+template <bool SAME>
+__device__ __forceinline__ void sum_even(const double* tab, int pitch, int ntu, int ntl, double nkc, double ak, double h,
+                                         bool odd, int m, int mm, float* sre, float* sim) {
+  // two rows at a time, for the latency of the sine and cosine
+  for (int t = 0; t < ntu; t += 2) {
+    float a[2], d[2], q[2], s4[2];
+    cf32 e[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const double at = tab[min(t + i, ntu - 1) * pitch];
+      e[i] = expi_turns_hw((ak - at) * nkc);
+      const cf32 b = expi_half_turns(at * h);
+      s4[i] = -4.0f * b.im * b.im;
+      a[i] = odd ? 1.0f : b.re;
+      d[i] = odd ? -0.5f * s4[i] : 0.0f;
+      q[i] = odd ? 0.5f : b.re;
+    }
+    for (int j = 0; j < mm; ++j)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        d[i] = __builtin_fmaf(s4[i], a[i], d[i]);
+        a[i] += d[i];
+        q[i] += SAME || j < m ? a[i] : 0.0f;
+      }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float g = (SAME ? t + i < ntu : t + i < ntl) ? q[i] : 0.0f;
+      *sre = __builtin_fmaf(g, e[i].re, *sre);
+      *sim = __builtin_fmaf(g, e[i].im, *sim);
     }
   }
 }
 
 // Decorrelation factor of this lane's bin (time bin tr of the chunk,
-// channels c0 .. c1), as k_decorr forms it.
+// channels c0 .. c1, centre frequency nuk, half channel spacing h or NaN), as
+// k_decorr forms it.
 __device__ __forceinline__ cf32 bin_factor(const ObsView& o, const Chunk& ch, const double* tab, bool in, int tr, int c0,
-                                           int c1, double aknu, double l0, double m0, double lw) {
+                                           int c1, double nuk, double ak, double h, double l0, double m0, double lw) {
 #pragma clang fp contract(off)
+  const double aknu = ak * nuk;
   float sre = 0.f, sim = 0.f;
-  const int64_t first = (ch.t0 + tr) * ch.nt;
-  const int ntl = in ? static_cast<int>(min(static_cast<int64_t>(ch.nt), o.n_t - first)) : 0;
-  for (int cb = c0; __any(in && cb < c1); cb += 4) {
-    const int nch = in ? min(4, c1 - cb) : 0;  // <= 0: none left for this lane
-    double nu[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) nu[j] = o.freq[max(0, min(cb + max(0, min(j, nch - 1)), o.n_ch - 1))];
-    const int nl = nch > 0 ? ntl : 0;
-    if (tab != nullptr) {
-      const uint64_t act = __ballot(nl > 0);
-      if (act == __ballot(nl > 0 && nch == 1)) sum_group<1>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
-      else if (act == __ballot(nl > 0 && nch == 2)) sum_group<2>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
-      else if (act == __ballot(nl > 0 && nch == 4)) sum_group<4>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
-      else sum_group<0>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+  const int ntl = in ? min(ch.nt, ch.left - tr * ch.nt) : 0;
+  if (tab != nullptr && ch.nc == 1) {
+    // one channel: its frequency is the bin's centre
+    const double nu[4] = {nuk, nuk, nuk, nuk};
+    sum_group<1>(tab + tr, ch.rows, ch.nt, ntl, nu, 1, aknu, &sre, &sim);
+  } else if (tab != nullptr && ch.nc >= kEvenMin && ch.nc <= kEvenMax && !__any(in && h != h)) {
+    const int n = c1 - c0, m = (n - 1) >> 1;
+    if (!__any(in && (n != ch.nc || ntl != ch.nt))) {
+      const int mm = (ch.nc - 1) >> 1;
+      sum_even<true>(tab + tr, ch.rows, ch.nt, ntl, nuk * kInvCLight, ak, h, (ch.nc & 1) != 0, mm, mm, &sre, &sim);
     } else {
-      for (int t = 0; t < nl; ++t) {
-        const double* row = o.uvw + 3 * (static_cast<int64_t>(ch.b) * o.n_t + first + t);
-        const double at = row[0] * l0 + row[1] * m0 + row[2] * lw;
-        for (int j = 0; j < nch; ++j) {
-          const cf32 e = expi_turns_hw(-((at * nu[j] - aknu) * kInvCLight));
-          sre += e.re;
-          sim += e.im;
+      sum_even<false>(tab + tr, ch.rows, ch.nt, ntl, nuk * kInvCLight, ak, h, (n & 1) != 0, m, (ch.nc - 1) >> 1, &sre, &sim);
+    }
+    sre *= 2.0f;
+    sim *= 2.0f;
+  } else {
+    for (int cb = c0; __any(in && cb < c1); cb += 4) {
+      const int nch = in ? min(4, c1 - cb) : 0;  // <= 0: none left for this lane
+      double nu[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) nu[j] = o.freq[max(0, min(cb + max(0, min(j, nch - 1)), o.n_ch - 1))];
+      const int nl = nch > 0 ? ntl : 0;
+      if (tab != nullptr) {
+        const uint64_t act = __ballot(nl > 0);
+        if (act == __ballot(nl > 0 && nch == 1)) sum_group<1>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+        else if (act == __ballot(nl > 0 && nch == 2)) sum_group<2>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+        else if (act == __ballot(nl > 0 && nch == 4)) sum_group<4>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+        else sum_group<0>(tab + tr, ch.rows, ch.nt, nl, nu, nch, aknu, &sre, &sim);
+      } else {
+        for (int t = 0; t < nl; ++t) {
+          const double* row = o.uvw + 3 * (static_cast<int64_t>(ch.b) * o.n_t + (ch.t0 + tr) * ch.nt + t);
+          const double at = row[0] * l0 + row[1] * m0 + row[2] * lw;
+          for (int j = 0; j < nch; ++j) {
+            const cf32 e = expi_turns_hw(-((at * nu[j] - aknu) * kInvCLight));
+            sre += e.re;
+            sim += e.im;
+          }
         }
       }
     }
   }
-  const float inv = in ? 1.0f / static_cast<float>(ntl * (c1 - c0)) : 0.f;
+  float inv = ch.inv;
+  const int n = ntl * (c1 - c0);
+  if (__any(in && n != ch.full)) inv = 1.0f / static_cast<float>(max(n, 1));  // short last bins
   return {sre * inv, sim * inv};
+}
+
+// The baseline that owns bin k: the last b with koff[b] <= k, found by the
+// whole wave, 64 candidates at a time.
+__device__ __forceinline__ int owner_of(const int64_t* __restrict__ koff, int n_bl, int64_t k, int lane) {
+  int lo = 0, hi = n_bl;
+  while (hi - lo > 1) {
+    const int step = (hi - lo + 63) >> 6;
+    const int q = lo + lane * step;
+    const uint64_t below = __ballot(q < hi && koff[min(q, n_bl - 1)] <= k);
+    lo += (below != 0 ? last_lane(below) : 0) * step;
+    hi = min(hi, lo + step);
+  }
+  return lo;
+}
+
+// Bins [*ka, *kb) of span i.
+__device__ __forceinline__ void span_bins(const UvGridArgs& a, int i, int64_t* ka, int64_t* kb) {
+  int64_t p, q;
+  if (a.fused) {
+    const int64_t* first = state_of(a, gsrc(0))->first;
+    p = first[i];
+    q = i + 1 < a.n_span ? first[i + 1] : a.o.K;
+  } else {
+    p = span_units(a, i) * a.unit_bins;
+    q = span_units(a, i + 1) * a.unit_bins;
+  }
+  *ka = min(max(p, int64_t(0)), a.o.K);
+  *kb = min(max(q, *ka), a.o.K);
 }
 
 // Waits for this workgroup's LDS traffic only: __syncthreads also waits for
@@ -491,7 +723,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   constexpr Mode MA = row_mode(PREC), MB = col_mode(PREC);
   __shared__ int tre[kTileCells], tim[kTileCells];
   __shared__ __attribute__((aligned(16))) uint8_t stage_raw[kWaves * kStage];
-  __shared__ double tab[FUSED ? kTabRows : 1], tabnu[FUSED ? kTabFreq : 1];
+  __shared__ double tab[FUSED ? kTabRows : 1], tabnu[FUSED ? kTabFreq : 1], tabh[FUSED ? kTabFreq : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   g_lds* st = (g_lds*)stage_raw + wave * kStage;
@@ -508,19 +740,20 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
     dl = s.dir[4];
     dm = s.dir[5];
   }
-  const double n0 = sqrt(1.0 - l0 * l0 - m0 * m0), lw = n0 - 1.0, l0n = l0 / n0, m0n = m0 / n0;
+  // (the same in every lane: kept in scalar registers)
+  const double n0 = sqrt(1.0 - l0 * l0 - m0 * m0), lw = uniform(n0 - 1.0), l0n = uniform(l0 / n0), m0n = uniform(m0 / n0);
   // offsets from the source of the pixels that modes (0, 0) stand for;
   // nothing to shift where they are rounding of a grid centred on the source
-  const double xh = (l_first + (s.nl / 2) * dl) - l0, yh = (m_first + (s.nm / 2) * dm) - m0;
+  const double xh = uniform((l_first + (s.nl / 2) * dl) - l0), yh = uniform((m_first + (s.nm / 2) * dm) - m0);
   const bool shift = !(fabs(xh) <= 1e-12 * fabs(dl) && fabs(yh) <= 1e-12 * fabs(dm));
   UvGridState* state = state_of(a, s);
   const int ecm = max_exponent(s, a.n_init);
   const float to_fixed = ldexpf(1.0f, kTileBits - a.log_tile - kAccBits);
   const Cells cells{cells_of(s), a.ml, a.mm, cell_bits(a.log_k) - (kTileBits - a.log_tile)};
   Tile tile{0, 0, 0, 0};
+  int tab_nc = 0;     // channels per bin that tabnu and tabh are for
   int tile_bins = 0;  // bins folded into the tile since it was last empty
-  double peak = 0.0;  // this lane's share of sum Re c
-  uint32_t fold = mix_word((blockIdx.x * kWaves + wave) * 64 + lane);  // random word of the next fold
+  const bool norm = s.norm != 0;
   for (int q = threadIdx.x; q < kTileCells; q += kThreads) tre[q] = tim[q] = 0;
   lds_barrier();
 
@@ -542,9 +775,13 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
     tile_bins = 0;
   };
 
-  int64_t ka = static_cast<int64_t>(blockIdx.x) * a.wg_bins;
-  const int64_t kb = min(o.K, ka + a.wg_bins);
-  for (int b = ka < kb ? find_baseline(o.koff, o.n_bl, ka) : o.n_bl; ka < kb && b < o.n_bl; ++b) {
+  __shared__ int next_span;
+  int64_t ka, kb;
+  for (int span = blockIdx.x; span < a.n_span;) {
+  span_bins(a, span, &ka, &kb);
+  double peak = 0.0;  // this lane's share of sum Re c
+  uint32_t fold = mix_word((span * kWaves + wave) * 64 + lane);  // random word of the next fold
+  for (int b = owner_of(o.koff, o.n_bl, ka, lane); ka < kb && b < o.n_bl; ++b) {
     Chunk ch;
     ch.b = b;
     ch.base = o.koff[b];
@@ -555,6 +792,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
     ch.nf = 1 + (o.n_ch - 1) / ch.nc;
     ch.la = ka - ch.base;
     ch.lb = kend - ch.base;
+    ch.full = min(ch.nt, o.n_t) * min(ch.nc, o.n_ch);
+    ch.inv = 1.0f / static_cast<float>(ch.full);
     ka = kend;
     const int64_t tb0 = o.tboff[b];
     ch.t0 = ch.la / ch.nf;
@@ -622,7 +861,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
       float best = 3.4e38f;
       for (int q = 0; q <= 6; ++q) {
         const int bt = 1 << q, bf = 64 >> q;
-        const float cost = static_cast<float>(((ch.rows + bt - 1) >> q) * ((ch.nf + bf - 1) / bf)) *
+        const float cost = static_cast<float>(((ch.rows + bt - 1) >> q) * ((ch.nf + bf - 1) >> (6 - q))) *
                            (1.0f + 0.5f * (bt * vt + bf * vf) * (1.0f / kSlack));
         if (cost < best) {
           best = cost;
@@ -648,89 +887,116 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
         }
       }
       tile_bins += nbins;
+      ch.left = static_cast<int>(min(o.n_t - ch.t0 * ch.nt, int64_t(1) << 30));
       const bool use_tab = FUSED && ch.nt <= kTabRows, use_nu = FUSED && ch.nf <= kTabFreq;
       if constexpr (FUSED) {
 #pragma clang fp contract(off)
         if (use_tab) {
-          const int64_t r0 = ch.t0 * ch.nt;
-          const int n = ch.rows * ch.nt;
-          for (int i = threadIdx.x; i < n; i += kThreads) {
-            const double* row = o.uvw + 3 * (static_cast<int64_t>(b) * o.n_t + min(r0 + i, static_cast<int64_t>(o.n_t) - 1));
-            const int tr = i / ch.nt;
-            tab[(i - tr * ch.nt) * ch.rows + tr] = row[0] * l0 + row[1] * m0 + row[2] * lw;
+          const int n = ch.rows * ch.nt;  // at most kTabRows
+          const double* row = o.uvw + 3 * (static_cast<int64_t>(b) * o.n_t + ch.t0 * ch.nt);
+          const float rnt = 1.0f / ch.nt;
+#pragma unroll
+          for (int j = 0; j < kTabRows / kThreads; ++j) {
+            const int i = threadIdx.x + j * kThreads;
+            const int ic = 3 * min(i, min(n, ch.left) - 1);
+            const double at = row[ic] * l0 + row[ic + 1] * m0 + row[ic + 2] * lw;
+            const int tr = static_cast<int>((i + 0.5f) * rnt);  // i / nt: exact for such i
+            if (i < n) tab[(i - tr * ch.nt) * ch.rows + tr] = at;
           }
         }
-        if (use_nu)
-          for (int f = threadIdx.x; f < ch.nf; f += kThreads)
-            tabnu[f] = bin_freq(o.freq, f * ch.nc, f * ch.nc + min(ch.nc, o.n_ch - f * ch.nc));
+        if (use_nu && ch.nc != tab_nc) {
+          tab_nc = ch.nc;
+          for (int f = threadIdx.x; f < ch.nf; f += kThreads) {
+            const int c0 = f * ch.nc, c1 = c0 + min(ch.nc, o.n_ch - c0);
+            tabnu[f] = bin_freq(o.freq, c0, c1);
+            if (ch.nc >= kEvenMin && ch.nc <= kEvenMax) tabh[f] = even_half_step(o.freq, c0, c1, tabnu[f]);
+          }
+        }
       }
       lds_barrier();
 
-      const int nqt = (ch.rows + bt - 1) >> lt, nqf = (ch.nf + bf - 1) / bf;
+      // Everything of a bin within the chunk is 32-bit: e = tr nf + f, the
+      // workgroup's own bins being [elo, ehi).
+      const int64_t first = ch.t0 * ch.nf;
+      const int elo = static_cast<int>(max(ch.la - first, int64_t(0)));
+      const int ehi = static_cast<int>(min(ch.lb - first, static_cast<int64_t>(ch.rows) * ch.nf));
+      const int64_t k0 = ch.base + first;
+      const int nqt = (ch.rows + bt - 1) >> lt, nqf = (ch.nf + bf - 1) >> (6 - lt);
       const int nq = nqt * nqf, per = (nq + kWaves - 1) / kWaves;
       const int q0 = wave * per, q1 = min(nq, q0 + per);
+      const int tlo = lane & (bt - 1), fl0 = lane >> lt;
       g_f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
       int wx = -1, wy = 0;  // the current window's origin, -1: none
       int run = 0;  // batches in the current window's accumulators
-      int qt_now = -1;
       double pt = 0.0, qtv = 0.0, ak = 0.0;  // the time bin's projections (metres)
+      int qt = q0 / nqf, qf = q0 - qt * nqf;
+      bool row_new = true;
+      // the time bin's centre, loaded a rectangle ahead
+      const double* ucs = FUSED ? o.uvw_c + 3 * (tb0 + ch.t0) : nullptr;
+      double uc[3] = {0.0, 0.0, 0.0};
+      if (FUSED && q0 < q1) {
+        const int r = 3 * min((qt << lt) + tlo, ch.rows - 1);
+        for (int i = 0; i < 3; ++i) uc[i] = ucs[r + i];
+      }
       for (int q = q0; q < q1; ++q) {
-        const int qt = q / nqf, qf = q - qt * nqf;
-        const int tr = (qt << lt) + (lane & (bt - 1)), f = qf * bf + (lane >> lt);
-        const int64_t l = (ch.t0 + tr) * ch.nf + f;
-        const bool in = tr < ch.rows && f < ch.nf && l >= ch.la && l < ch.lb;
-        const int64_t k = ch.base + (in ? l : ch.la);
+        const int tr = (qt << lt) + tlo, f = qf * bf + fl0;
+        const int e = tr * ch.nf + f;
+        const bool in = f < ch.nf && static_cast<unsigned>(e - elo) < static_cast<unsigned>(ehi - elo);
+        const int ec = in ? e : elo;
         double up, vp;
         float2 c0;
         if constexpr (FUSED) {
-          const float W = o.W[k];
-          if (qt != qt_now) {
+          const float W = (o.W + k0)[ec];
+          const int trc = min(tr, ch.rows - 1);
+          if (row_new) {
 #pragma clang fp contract(off)
-            const double* uc = o.uvw_c + 3 * (tb0 + ch.t0 + min(tr, ch.rows - 1));
             const double u = uc[0], v = uc[1], w = uc[2];
             ak = u * l0 + v * m0 + w * lw;
             pt = (u - w * l0n) * kInvCLight;
             qtv = (v - w * m0n) * kInvCLight;
-            qt_now = qt;
+            const int r = 3 * min(((qt + 1) << lt) + tlo, ch.rows - 1);
+            for (int i = 0; i < 3; ++i) uc[i] = ucs[r + i];
           }
           const int fc = min(f, ch.nf - 1);
           const int c0i = fc * ch.nc, c1i = c0i + min(ch.nc, o.n_ch - c0i);
           const double nu = use_nu ? tabnu[fc] : bin_freq(o.freq, c0i, c1i);
-          const cf32 D = bin_factor(o, ch, use_tab ? tab : nullptr, in, min(tr, ch.rows - 1), c0i, c1i, ak * nu, l0, m0, lw);
+          const cf32 D = bin_factor(o, ch, use_tab ? tab : nullptr, in, trc, c0i, c1i, nu, ak, use_nu ? tabh[fc] : __builtin_nan(""), l0, m0, lw);
           up = pt * nu;
           vp = qtv * nu;
           c0 = make_float2(W * D.re, W * D.im);
-          if (in) peak += static_cast<double>(c0.x);
+          if (norm && in) peak += static_cast<double>(c0.x);
         } else {
-          up = rec[k].up;
-          vp = rec[k].vp;
-          c0 = cf[k];
+          up = (rec + k0)[ec].up;
+          vp = (rec + k0)[ec].vp;
+          c0 = (cf + k0)[ec];
         }
-        // finite? (u', v' and c: anything else makes the patch NaN)
-        const bool ok = in && isfinite(up) && isfinite(vp) && isfinite(c0.x) && isfinite(c0.y);
-        if (in && !ok) state->poison = 1;
-        int ax = 0, ay = 0;
-        float fx = 0.f, fy = 0.f;
-        cf32 c = {0.f, 0.f};
-        if (ok) {
-          torus(up, dl, a.ml, &ax, &fx);
-          torus(vp, dm, a.mm, &ay, &fy);
-          c = cf32{ldexpf(c0.x, kCoefBits - ecm), ldexpf(c0.y, kCoefBits - ecm)};
-          if (shift) c = cmul(c, expi_turns_hw(up * xh + vp * yh));
+        row_new = ++qf == nqf;
+        if (row_new) {
+          qf = 0;
+          ++qt;
         }
+        int ax, ay;
+        float fx, fy;
+        torus(up, dl, a.ml, &ax, &fx);
+        torus(vp, dm, a.mm, &ay, &fy);
+        cf32 c = {ldexpf(c0.x, kCoefBits - ecm), ldexpf(c0.y, kCoefBits - ecm)};
+        if (shift) c = cmul(c, expi_turns_hw(up * xh + vp * yh));
         ax = wrap(ax - kW / 2, a.ml);
         ay = wrap(ay - kW / 2, a.mm);
         float tx[kW], ty[kW];
         taps(fx, tx);
         taps(fy, ty);
-        uint64_t wait = __ballot(ok);
+        // random words of the bin's row and column taps
+        const uint32_t kw = static_cast<uint32_t>(k0) + ec;
+        const uint32_t rwa = MA == kMSR ? kw * 0xC2B2AE35u : 0u, rwb = MB == kMSR ? mix_word(kw) : 0u;
+        uint64_t wait = __ballot(in);
         while (wait != 0) {
           const int fl = first_lane(wait);
           const int fax = __builtin_amdgcn_readlane(ax, fl), fay = __builtin_amdgcn_readlane(ay, fl);
           if (wx < 0 || run == kRun || wrap(fax - wx, a.ml) > kSlack || wrap(fay - wy, a.mm) > kSlack) {
             run = 0;
             if (wx >= 0) {
-              fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im);
+              fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im, state);
               re = im = g_f32x4{0.f, 0.f, 0.f, 0.f};
             }
             const int ll = last_lane(wait);
@@ -742,8 +1008,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
           const bool go = ((wait >> lane) & 1) != 0 && dx <= kSlack && dy <= kSlack;
           const uint64_t going = __ballot(go);
           wait &= ~going;
-          const uint32_t rwa = MA == kMSR ? static_cast<uint32_t>(k) * 0xC2B2AE35u : 0;
-          const uint32_t rwb = MB == kMSR ? mix_word(static_cast<uint32_t>(k)) : 0;
           stage_clear<MA>(st, lane);
           wave_order();
           if (go) stage_taps<MA>(st, dx, lane, tx, rwa);
@@ -769,24 +1033,31 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
           im = contract_frags<MA, MB>(fa, fi, going, im);
         }
       }
-      if (wx >= 0) fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im);
+      if (wx >= 0) fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im, state);
       ch.t0 += ch.rows;
     }
   }
-  lds_barrier();
-  flush_tile();
-  if constexpr (FUSED) {
-    // sum Re c of the workgroup, in a fixed order
+  // (not asked for earlier: loads issued after an atomic return after it)
+  if (threadIdx.x == 0)
+    next_span = a.levels == 1 ? a.n_span
+                              : a.n_wg + static_cast<int>(__hip_atomic_fetch_add(&state->next, 1u, __ATOMIC_RELAXED,
+                                                                                 __HIP_MEMORY_SCOPE_AGENT));
+  if (FUSED && norm) {
+    // sum Re c of the span, in a fixed order
     for (int q = 32; q > 0; q >>= 1) peak += __shfl_xor(peak, q);
     lds_barrier();
     if (lane == 0) tab[wave] = peak;
-    lds_barrier();
-    if (threadIdx.x == 0) {
-      double p = 0.0;
-      for (int w = 0; w < kWaves; ++w) p += tab[w];
-      state_of(a, s)->peak[blockIdx.x] = p;
-    }
   }
+  lds_barrier();
+  if (FUSED && norm && threadIdx.x == 0) {
+    double p = 0.0;
+    for (int w = 0; w < kWaves; ++w) p += tab[w];
+    state->peak[span] = p;
+  }
+  span = __builtin_amdgcn_readfirstlane(next_span);
+  lds_barrier();
+  }
+  flush_tile();
 }
 
 // In-place inverse DFT (sign +) of the M complex values in `v` (LDS), radix
@@ -862,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_grid_cols(UvGridArgs a) {
   if (norm && a.fused) {
     // 2 sum Re c: the spreading workgroups' sums, in a fixed order
     double p = 0.0;
-    for (int q = threadIdx.x; q < a.n_wg; q += 256) p += state_of(a, s)->peak[q];
+    for (int q = threadIdx.x; q < a.n_span; q += 256) p += state_of(a, s)->peak[q];
     for (int q = 32; q > 0; q >>= 1) p += __shfl_xor(p, q);
     __syncthreads();  // the twiddles are read no more
     if ((threadIdx.x & 63) == 0) tw[threadIdx.x >> 6].x = p;
@@ -928,16 +1199,26 @@ hipError_t launch_grid(int prec, UvGridArgs a, hipStream_t stream) {
   // of frequency bins fits, the number of channels.
   a.log_tile = std::min(14, std::max(9, 10 + (a.log_k - 16) / 2));
   while (a.log_tile < 14 && (1 << a.log_tile) < a.o.n_ch) ++a.log_tile;
-  // contiguous bins per workgroup: a few rounds of the 768 that the chip
-  // runs at once, at least 512 bins each
-  const int64_t want = 3072 / a.n_src;
-  const int64_t span = (K + want - 1) / want;
-  a.wg_bins = span < 512 ? 512 : span;
-  a.n_wg = static_cast<int>((K + a.wg_bins - 1) / a.wg_bins);
+  // As many workgroups as the chip runs at once (three per compute unit); with
+  // fewer than 768 bins each, workgroups of 512 (two rounds of 64 bins per
+  // wave) instead, the last of which follow the first that are done.  One span each below 8192 bins per workgroup (K =
+  // 5.9M of uneven bins: 195 us against 229 with three levels; six patches of
+  // K = 1.45M 1258 against 1356), from there on as many levels as leave the
+  // last at least 1024 bins (K = 23.2M, three sources: 1846 us with six levels,
+  // 1918 with five, 2150 with one).
+  const int resident = 768 / a.n_src;
+  a.n_wg = K / resident < 768 ? static_cast<int>((K + 511) / 512) : resident;
+  a.levels = 1;
+  if (K / a.n_wg >= 8 * kLeastSpan)
+    while (a.levels < kGridMaxLevels && K / a.n_wg >= int64_t(kLeastSpan) << a.levels) ++a.levels;
+  a.n_span = a.levels * a.n_wg;
+  const int units = span_units(a, a.n_span);
+  a.unit_bins = (K + units - 1) / units;
+  static_assert(kGridMaxLevels * 768 <= kGridMaxSpans, "a peak and a first bin for every span");
   const unsigned n_src = static_cast<unsigned>(a.n_src);
   const int64_t words = std::max(static_cast<int64_t>(a.ml) * a.mm, K / (a.fused ? 4 : 2));
   a.n_init = static_cast<int>(std::min<int64_t>(kInitBlocks, (words + 255) / 256));
-  hipLaunchKernelGGL(k_grid_init, dim3(static_cast<unsigned>(a.n_init), n_src), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(k_grid_init, dim3(static_cast<unsigned>(a.n_init + (a.fused ? kCutBlocks : 0)), n_src), dim3(256), 0, stream, a);
   const dim3 sg(static_cast<unsigned>(a.n_wg), n_src);
   switch (prec) {
     case kFP32: launch_spread<kFP32>(a, sg, stream); break;

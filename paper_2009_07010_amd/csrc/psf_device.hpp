@@ -59,6 +59,32 @@ __device__ __forceinline__ cf32 expi_turns(double theta) {
   return z;
 }
 
+// exp(2 pi i theta) for theta in turns, as the polynomials of one half turn:
+// |r| <= 1/4 turn, so the Taylor series run through x^13 and x^14 (truncation
+// below 1e-9); odd half turns change both signs.
+__device__ __forceinline__ cf32 expi_half_turns(double theta) {
+  const double q = rint(2.0 * theta);
+  const float x = static_cast<float>(fma(-0.5, q, theta) * 6.283185307179586);
+  const float x2 = x * x;
+  float s = 1.0f / 6227020800.0f, c = -1.0f / 87178291200.0f;
+  s = __builtin_fmaf(s, x2, -1.0f / 39916800.0f);
+  c = __builtin_fmaf(c, x2, 1.0f / 479001600.0f);
+  s = __builtin_fmaf(s, x2, 1.0f / 362880.0f);
+  c = __builtin_fmaf(c, x2, -1.0f / 3628800.0f);
+  s = __builtin_fmaf(s, x2, -1.0f / 5040.0f);
+  c = __builtin_fmaf(c, x2, 1.0f / 40320.0f);
+  s = __builtin_fmaf(s, x2, 1.0f / 120.0f);
+  c = __builtin_fmaf(c, x2, -1.0f / 720.0f);
+  s = __builtin_fmaf(s, x2, -1.0f / 6.0f);
+  c = __builtin_fmaf(c, x2, 1.0f / 24.0f);
+  c = __builtin_fmaf(c, x2, -0.5f);
+  c = __builtin_fmaf(c, x2, 1.0f);
+  s = __builtin_fmaf(s * x2, x, x);
+  const uint32_t odd = static_cast<uint32_t>(static_cast<int>(q)) << 31;
+  return {__builtin_bit_cast(float, __builtin_bit_cast(uint32_t, c) ^ odd),
+          __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, s) ^ odd)};
+}
+
 // Index of the baseline that owns bin k: largest b with koff[b] <= k.  The
 // wave's first active lane is searched for by bisection in uniform control
 // flow (scalar loads, no dependent vector loads); every lane then steps from
@@ -113,6 +139,19 @@ __device__ __forceinline__ double bin_freq(const double* __restrict__ freq, int 
   double s = 0.0;
   for (int c = c0; c < c1; ++c) s += freq[c];
   return s / static_cast<double>(c1 - c0);
+}
+
+// Half the channel spacing of a bin over c (s/m) where its channels are
+// evenly spaced about nu_k, else NaN.  Within 1e-14 of the frequency, the
+// evenly spaced phases are those of the channels to 1e-8 turns for phases of
+// up to 1e6 turns (a phase itself is rounded to 1e-10 there).
+__device__ __forceinline__ double even_half_step(const double* __restrict__ freq, int c0, int c1, double nu_k) {
+  const int n = c1 - c0;
+  if (n < 2) return 0.0;
+  const double d = (freq[c1 - 1] - freq[c0]) / static_cast<double>(n - 1), first = nu_k - 0.5 * (n - 1) * d;
+  bool even = true;
+  for (int c = c0; c < c1; ++c) even &= fabs(freq[c] - fma(static_cast<double>(c - c0), d, first)) <= 1e-14 * fabs(nu_k);
+  return even ? 0.5 * d * kInvCLight : __builtin_nan("");
 }
 
 // Pack helpers for the split forms: two floats -> two round-to-nearest

@@ -36,7 +36,7 @@ struct UvGridSrc {
   int norm;  // fused: divide by 2 sum Re c, summed here
 };
 
-constexpr int kGridMaxWgs = 4096;  // spreading workgroups per source
+constexpr int kGridMaxSpans = 4608;  // spans of bins per source
 
 struct UvGridArgs {
   ObsView o;
@@ -44,9 +44,10 @@ struct UvGridArgs {
   int ml, mm;  // cells per axis (every source of the launch)
   int fused;
   // filled by launch_grid: ceil(log2 K), log2 of the bins a tile may sum,
-  // spreading workgroups and the contiguous bins of each, init blocks
-  int log_k, log_tile, n_wg, n_init;
-  int64_t wg_bins;
+  // spreading workgroups, levels and number of their spans (per source), init
+  // blocks; bins of the shortest span where all bins cost the same
+  int log_k, log_tile, n_wg, levels, n_span, n_init;
+  int64_t unit_bins;
   UvGridSrc src[kMaxBatch];
 };
 

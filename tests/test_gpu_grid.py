@@ -158,3 +158,44 @@ def test_not_finite_and_zero_weights(pk):
     for f in (2.0 ** 40, 2.0 ** -40):
         Q = pk.patch(pk.DeviceObservation(dataclasses.replace(obs, W=obs.W * np.float32(f))), src, prec="split_fp16")
         assert torch.equal(Q, P * f)
+
+
+@pytest.mark.parametrize("spacing", ["even", "down", "uneven"])
+@pytest.mark.parametrize("nc", [2, 3, 4, 5, 8, 16, 17])
+def test_channels_per_bin(pk, nc, spacing):
+    """Bins of evenly spaced channels are summed by their spacing (3 to 16
+    channels, either direction), others channel by channel; short last bins on
+    both axes, of one channel and of one time."""
+    import dataclasses
+    obs = ps.tiny_random(40 + nc, n_ant=26, n_t=76, n_ch=3 * nc + 1, nt=3, nc=nc, radius_m=1500.0, dt=10.0)
+    f = np.asarray(obs.freq_hz, dtype=np.float64)
+    if spacing == "down":
+        f = f[::-1].copy()
+    if spacing == "uneven":
+        f = f + np.random.default_rng(nc).uniform(-0.3, 0.3, f.size) * abs(f[1] - f[0])
+    obs = dataclasses.replace(obs, freq_hz=f)
+    assert obs.K >= 24576
+    dobs = pk.DeviceObservation(obs)
+    src = _src(65, 100)
+    D = orc.decorr(obs, src.l0, src.m0)
+    ref = orc.patch_factored(obs, src, D)
+    P = pk.patch(dobs, src, prec="fp32").double().cpu().numpy()
+    e, b = float(np.max(np.abs(P - ref))), _bound("fp32", obs, D)
+    print(f"nc {nc} {spacing} K={obs.K}: {e / np.max(np.abs(ref)):.2e} of the peak, {e / b:.2f} of the bound", flush=True)
+    assert e <= b
+
+
+def test_spans(pk):
+    """From one span per workgroup (K / 512 of them) to four each of 768, with
+    baselines that hold from none of a span's first bins to several spans."""
+    for seed, n_ant, n_t, n_ch in ((1, 9, 700, 1), (2, 60, 14, 1), (3, 40, 1050, 1), (4, 4, 45000, 3)):
+        obs = ps.tiny_random(seed, n_ant=n_ant, n_t=n_t, n_ch=n_ch, nt=1, nc=1, radius_m=2500.0, dt=7200.0 / n_t)
+        src = _src(129, 129)  # (smaller patches of so few bins take the dense form)
+        D = orc.decorr(obs, src.l0, src.m0)
+        assert obs.K >= 24576
+        ref = orc.patch_factored(obs, src, D)
+        P = pk.patch(pk.DeviceObservation(obs), src, prec="split_bf16", normalise=True).double().cpu().numpy()
+        peak = 2.0 * float(np.sum(obs.W * D).real)
+        e, b = float(np.max(np.abs(P - ref / peak))), 2 * _bound("split_bf16", obs, D) / abs(peak)
+        print(f"K={obs.K}, {n_ant} antennas: {e / b:.2f} of the bound", flush=True)
+        assert e <= b
