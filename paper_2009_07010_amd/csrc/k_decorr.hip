@@ -49,6 +49,7 @@ namespace {
 // baseline-dependent bins of 1-8 channels); two channels re-read each
 // time row too often (0.196 ms).
 constexpr int kChanChunk = 4;
+constexpr int kEvenBin = 8;  // channels from which the even form pays (12 with windows)
 
 // Sums over one bin's samples: S = sum x e with e = exp(-2 pi i phi) and x
 // the sample's window weight (1 without windows), the window sums of the bin
@@ -63,9 +64,12 @@ struct BinSums {
 
 template <bool kWin, bool kGrad>
 __device__ __forceinline__ BinSums bin_sums(const ObsView& o, const BinRef& r, double l0, double m0, double Lw,
-                                            double A_knu, double nu_k, double uc, double vc, double wc,
+                                            double A_k, double nu_k, double uc, double vc, double wc,
                                             double l0_n0, double m0_n0) {
 #pragma clang fp contract(off)
+  // without derivatives the frequencies are taken over c once per chunk, not
+  // the phase once per sample
+  const double A_knu = kGrad ? A_k * nu_k : A_k * (nu_k * kInvCLight);
   BinSums s{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const double* row = o.uvw + 3 * (static_cast<int64_t>(r.b) * o.n_t);
   const float* win_tb = kWin && o.win_t != nullptr ? o.win_t + static_cast<int64_t>(r.b) * o.n_t : nullptr;
@@ -77,7 +81,7 @@ __device__ __forceinline__ BinSums bin_sums(const ObsView& o, const BinRef& r, d
 #pragma unroll
     for (int j = 0; j < kChanChunk; ++j) {
       const int c = cb + min(j, nch - 1);  // clamped: always a channel of the bin
-      nu[j] = o.freq[c];
+      nu[j] = kGrad ? o.freq[c] : o.freq[c] * kInvCLight;
       xc[j] = kWin && win_cb != nullptr ? win_cb[c] : 1.f;
     }
     if constexpr (kWin) {
@@ -98,7 +102,7 @@ __device__ __forceinline__ BinSums bin_sums(const ObsView& o, const BinRef& r, d
       for (int j = 0; j < kChanChunk; ++j) {
         if (j < nch) {
           const double nu_c = nu[j];
-          const double phi = (A_t * nu_c - A_knu) * kInvCLight;
+          const double phi = kGrad ? (A_t * nu_c - A_knu) * kInvCLight : A_t * nu_c - A_knu;
           const cf32 e = expi_turns_hw(-phi);
           const float x = kWin ? xt * xc[j] : 1.f;
           if constexpr (kWin) {
@@ -133,6 +137,119 @@ __device__ __forceinline__ BinSums bin_sums(const ObsView& o, const BinRef& r, d
     }
   }
   return s;
+}
+
+// cos and sin of 2 pi theta (theta in turns) in FP64, to about 1e-9: the
+// Taylor series of one half turn through x^14 and x^13.
+__device__ __forceinline__ void cos_sin_turns(double theta, double* c, double* s) {
+  const double q = rint(2.0 * theta);
+  const double x = fma(-0.5, q, theta) * 6.283185307179586;
+  const double x2 = x * x;
+  double p = 1.0 / 6227020800.0, r = -1.0 / 87178291200.0;
+  p = fma(p, x2, -1.0 / 39916800.0);
+  r = fma(r, x2, 1.0 / 479001600.0);
+  p = fma(p, x2, 1.0 / 362880.0);
+  r = fma(r, x2, -1.0 / 3628800.0);
+  p = fma(p, x2, -1.0 / 5040.0);
+  r = fma(r, x2, 1.0 / 40320.0);
+  p = fma(p, x2, 1.0 / 120.0);
+  r = fma(r, x2, -1.0 / 720.0);
+  p = fma(p, x2, -1.0 / 6.0);
+  r = fma(r, x2, 1.0 / 24.0);
+  r = fma(r, x2, -0.5);
+  r = fma(r, x2, 1.0);
+  p = fma(p * x2, x, x);
+  const bool odd = (static_cast<int>(q) & 1) != 0;
+  *c = odd ? -r : r;
+  *s = odd ? -p : p;
+}
+
+// The sums of bin_sums (no derivatives) for a bin of evenly spaced channels
+// (half spacing h, in s/m): the channels of a time row are a polynomial in
+// z = exp(-4 pi i A_t h) with the channel windows as coefficients, times the
+// factor of the row's first channel.  It is summed by Clenshaw's recurrence
+// b_j = x_j + 2 Re(z) b_{j+1} - b_{j+2}, sum_j x_j z^j = b_0 - conj(z) b_1:
+// two real operations per sample instead of a sine-cosine pair and eight more.
+// In FP64, whose rate is that of FP32 here, because the recurrence loses
+// digits with the square of the channels at small angles.  Windowed bins take
+// kLen channels at a time, their windows in registers (0 beyond the last;
+// read from memory for every row instead: 753 against 542 us for bins of
+// 20 x 40); without windows all channels at once.
+template <bool kWin, int kLen>
+__device__ __forceinline__ BinSums even_sums(const ObsView& o, const BinRef& r, double l0, double m0, double Lw,
+                                             double A_k, double nu_k, double h) {
+#pragma clang fp contract(off)
+  BinSums s{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const double* row = o.uvw + 3 * (static_cast<int64_t>(r.b) * o.n_t);
+  const float* win_tb = kWin && o.win_t != nullptr ? o.win_t + static_cast<int64_t>(r.b) * o.n_t : nullptr;
+  const float* win_cb = kWin && o.win_c != nullptr ? o.win_c + static_cast<int64_t>(r.b) * o.n_ch : nullptr;
+  const double A_knu = A_k * nu_k;
+  for (int cb = r.c0; cb < r.c1; cb += kWin ? kLen : r.c1 - r.c0) {
+    const int nch = kWin ? min(kLen, r.c1 - cb) : r.c1 - cb;
+    float x[kLen];
+    if constexpr (kWin) {
+#pragma unroll
+      for (int j = 0; j < kLen; ++j) {
+        const float w = win_cb != nullptr ? win_cb[cb + min(j, nch - 1)] : 1.f;
+        x[j] = j < nch ? w : 0.f;
+        if (j < nch) s.sc += w;
+      }
+    }
+    const double nu = o.freq[cb];
+    double u = row[3 * r.t0], v = row[3 * r.t0 + 1], w = row[3 * r.t0 + 2];
+    float xt = kWin && win_tb != nullptr ? win_tb[r.t0] : 1.f;
+    for (int t = r.t0; t < r.t1; ++t) {
+      const int tn = min(t + 1, r.t1 - 1);
+      const double un = row[3 * tn], vn = row[3 * tn + 1], wn = row[3 * tn + 2];
+      const float xtn = kWin && win_tb != nullptr ? win_tb[tn] : 1.f;
+      if (kWin && cb == r.c0) s.st += xt;
+      const double A_t = u * l0 + v * m0 + w * Lw;
+      const cf32 e = expi_half_turns((A_knu - A_t * nu) * kInvCLight);
+      double zc, zs;
+      cos_sin_turns(2.0 * (A_t * h), &zc, &zs);
+      const double c2 = 2.0 * zc;
+      double b0 = 0.0, b1 = 0.0;
+      auto step = [&](double xj) {
+        const double b = fma(c2, b0, xj - b1);
+        b1 = b0;
+        b0 = b;
+      };
+      if constexpr (kWin) {
+#pragma unroll
+        for (int j = kLen - 1; j >= 0; --j) {
+          asm("" : "+v"(x[j]));  // converted for every row: 40 registers less than the FP64 values
+          step(x[j]);
+        }
+      } else {
+#pragma unroll 4
+        for (int j = 0; j < nch; ++j) step(1.0);
+      }
+      const float gr = xt * static_cast<float>(fma(-b1, zc, b0)), gi = -xt * static_cast<float>(b1 * zs);
+      s.sre = __builtin_fmaf(gr, e.re, __builtin_fmaf(-gi, e.im, s.sre));
+      s.sim = __builtin_fmaf(gr, e.im, __builtin_fmaf(gi, e.re, s.sim));
+      u = un;
+      v = vn;
+      w = wn;
+      xt = xtn;
+    }
+  }
+  return s;
+}
+
+// The sums by whichever of the two is the faster: a row costs the recurrence
+// as much as 8 samples by bin_sums, or 12 with windows.
+template <bool kWin>
+__device__ __forceinline__ BinSums wide_sums(const ObsView& o, const BinRef& r, double l0, double m0, double Lw,
+                                             double A_k, double nu_k, double uc, double vc, double wc, double l0_n0,
+                                             double m0_n0) {
+  const int nc = r.c1 - r.c0;
+  const double h = nc >= (kWin ? 12 : kEvenBin) && r.t1 - r.t0 > 1 ? even_half_step(o.freq, r.c0, r.c1, nu_k)
+                                                                  : __builtin_nan("");
+  if (h == h) {
+    if (kWin && nc <= 20) return even_sums<kWin, 20>(o, r, l0, m0, Lw, A_k, nu_k, h);
+    return even_sums<kWin, 40>(o, r, l0, m0, Lw, A_k, nu_k, h);
+  }
+  return bin_sums<kWin, false>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
 }
 }  // namespace
 
@@ -204,8 +321,14 @@ __device__ __forceinline__ void finish_bin(const ObsView& o, int64_t k, double l
 // is read from device memory at dirs + y * dir_stride (l0, m0 as the first
 // two doubles) when dirs is given, and whose records start y * rec_stride
 // elements into rec_out and c_out.
-template <bool kGrad>
-__global__ __launch_bounds__(256) void k_decorr(ObsView o, double l0, double m0, double dl, double dm,
+//
+// wide: wide_sums, for observations that may hold bins it is good for (72
+// registers for boxcar averaging, 128 with windows; bin_sums alone takes 70).
+// Bins of 20 x 40 samples, K = 2.2M: 1087 -> 349 us, with windows 1574 -> 542
+// (arithmetic: 2 or 3 FP64 operations per sample and about 100 per row).
+enum Wide { kNotWide, kWideBoxcar, kWideWindow };
+template <bool kGrad, Wide wide>
+__global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(ObsView o, double l0, double m0, double dl, double dm,
                                                 const double* __restrict__ dirs, int64_t dir_stride,
                                                 int64_t rec_stride,
                                                 const float2* __restrict__ D_in,
@@ -240,20 +363,21 @@ __global__ __launch_bounds__(256) void k_decorr(ObsView o, double l0, double m0,
     dim = d.y;
   } else {
     const double A_k = uc * l0 + vc * m0 + wc * Lw;
-    const double A_knu = A_k * nu_k;
     const double l0_n0 = l0 / n0, m0_n0 = m0 / n0;
     float inv;
     BinSums bs;
-    if (o.win_t != nullptr || o.win_c != nullptr) {
+    if (wide == kWideWindow || (wide == kNotWide && (o.win_t != nullptr || o.win_c != nullptr))) {
       // Windowed averaging: sample weight x = win_t[b][t] win_c[b][c], the
       // mean normalised by the window's sum over the bin (D = 0 for a
       // window that sums to 0).  Separable, so the normaliser is the
       // product of the two axis sums.
-      bs = bin_sums<true, kGrad>(o, r, l0, m0, Lw, A_knu, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      if constexpr (wide != kNotWide) bs = wide_sums<true>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      else bs = bin_sums<true, kGrad>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
       const float norm = bs.st * bs.sc;
       inv = norm != 0.f ? 1.0f / norm : 0.f;
     } else {
-      bs = bin_sums<false, kGrad>(o, r, l0, m0, Lw, A_knu, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      if constexpr (wide != kNotWide) bs = wide_sums<false>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      else bs = bin_sums<false, kGrad>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
       inv = 1.0f / static_cast<float>((r.t1 - r.t0) * (r.c1 - r.c0));
     }
     dre = bs.sre * inv;
@@ -354,6 +478,16 @@ bool use_wave_bins(const ObsView& o) {
   return o.K > 0 && o.K < 512 * 64 && samples >= 64.0 * static_cast<double>(o.K);
 }
 
+// The kernel without derivatives: wide where there are channels enough, with
+// windows only from 128 samples per bin on average (the bins' own sizes are on
+// the device), since that form takes 128 registers to the other's 70.
+static decltype(&k_decorr<false, kNotWide>) decorr_kernel(const ObsView& o) {
+  if (o.n_ch < kEvenBin) return k_decorr<false, kNotWide>;
+  if (o.win_t == nullptr && o.win_c == nullptr) return k_decorr<false, kWideBoxcar>;
+  const bool many = static_cast<double>(o.n_bl) * o.n_t * o.n_ch >= 128.0 * static_cast<double>(o.K);
+  return many ? k_decorr<false, kWideWindow> : k_decorr<false, kNotWide>;
+}
+
 hipError_t launch_decorr(const ObsView& o, double l0, double m0, double dl, double dm, const float2* D_in,
                          float2* D_out, BinRec* rec_out, float2* c_out, float2* coef_out, hipStream_t stream,
                          const double* dir) {
@@ -370,11 +504,11 @@ hipError_t launch_decorr(const ObsView& o, double l0, double m0, double dl, doub
     return hipGetLastError();
   }
   if (coef_out != nullptr && D_in == nullptr)
-    hipLaunchKernelGGL(k_decorr<true>, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0, stream, o, l0, m0,
+    hipLaunchKernelGGL((k_decorr<true, kNotWide>), dim3(static_cast<unsigned>(blocks)), dim3(threads), 0, stream, o, l0, m0,
                        dl, dm, dir, int64_t(0), int64_t(0), D_in, D_out, rec_out, c_out, coef_out);
   else
-    hipLaunchKernelGGL(k_decorr<false>, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0, stream, o, l0, m0,
-                       dl, dm, dir, int64_t(0), int64_t(0), D_in, D_out, rec_out, c_out, nullptr);
+    hipLaunchKernelGGL(decorr_kernel(o),
+                       dim3(static_cast<unsigned>(blocks)), dim3(threads), 0, stream, o, l0, m0, dl, dm, dir, int64_t(0), int64_t(0), D_in, D_out, rec_out, c_out, nullptr);
   return hipGetLastError();
 }
 
@@ -388,8 +522,8 @@ hipError_t launch_decorr_sources(const ObsView& o, const double* dirs, int64_t d
                        c_out, nullptr);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(k_decorr<false>, dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(n_src)), dim3(threads), 0,
-                     stream, o, 0.0, 0.0, 0.0, 0.0, dirs, dir_stride, rec_stride, nullptr, nullptr, rec_out, c_out,
+  hipLaunchKernelGGL(decorr_kernel(o),
+                     dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(n_src)), dim3(threads), 0, stream, o, 0.0, 0.0, 0.0, 0.0, dirs, dir_stride, rec_stride, nullptr, nullptr, rec_out, c_out,
                      nullptr);
   return hipGetLastError();
 }
