@@ -15,9 +15,18 @@
 //   dPsi = 2 pi omega_E (-v0 l0 + u0 m0) dt,  dPhi = 2 pi (dnu/nu) |l0| |u0|,
 //   D^ = sinc(dPsi/2) sinc(dPhi/2).
 //
-// FFTs: radix-2 Stockham (self-sorting) on one line per workgroup, held in
-// LDS (two buffers of N complex floats), FP32 with twiddles exp(+-2 pi i
-// p/n) from sincospi of an exactly representable argument.
+// FFTs: Stockham (self-sorting) of radix 4, with a last pass of radix 2 where
+// N is an odd power, FP32, twiddles exp(+-2 pi i k/N) from sincospif of an
+// exactly representable argument, once per workgroup.  A workgroup holds
+// several lines in LDS, so that column passes read and write whole 64- or
+// 128-byte pieces of rows.  The patch is the real part of the transform, which
+// depends on the Hermitian part of F{P_eff} D^ only: rows a <= N/2 of that
+// are formed (with the model, in the kernel that transforms them), and two of
+// the real columns share one complex transform of the second pass, which
+// writes the patch.  16 sources at N = 512: 34 us in two launches, against 176
+// us in four with one radix-2 line per workgroup (50 MB of traffic instead of
+// 250; bound now by the model's FP64 arithmetic, half of the first kernel, and
+// by the latency of passes through LDS).
 #include <algorithm>
 #include <cmath>
 
@@ -30,83 +39,219 @@ namespace {
 constexpr double kOmegaEarth = 7.2921150e-5;  // rad / s, sidereal
 constexpr int kChunk = 16;                    // sources per launch
 constexpr int kFftThreads = 256;
+constexpr int kPad = 4;  // per line: 8 lines x 4 elements fall on different LDS banks
 
-__global__ __launch_bounds__(kFftThreads) void k_fft_lines(float2* __restrict__ data, int N, int logN,
-                                                           int64_t elem_stride, int64_t line_stride,
-                                                           int64_t batch_stride, float sign) {
-  extern __shared__ float2 lds[];
-  float2* base = data + blockIdx.y * batch_stride + blockIdx.x * line_stride;
-  for (int n = threadIdx.x; n < N; n += kFftThreads) lds[n] = base[n * elem_stride];
-  __syncthreads();
-  int cur = 0;
-  for (int pass = 0; pass < logN; ++pass) {
-    const int n_sz = N >> pass, m = n_sz >> 1, ls = pass;  // stride s = 2^pass
-    const float2* in = lds + cur * N;
-    float2* out = lds + (cur ^ 1) * N;
-    for (int t = threadIdx.x; t < (N >> 1); t += kFftThreads) {
-      const int p = t >> ls, q = t - (p << ls);
-      float sn, cs;
-      sincospif(sign * 2.0f * static_cast<float>(p) / static_cast<float>(n_sz), &sn, &cs);
-      const float2 a = in[q + (p << ls)];
-      const float2 b = in[q + ((p + m) << ls)];
-      out[q + ((2 * p) << ls)] = make_float2(a.x + b.x, a.y + b.y);
-      const float dx = a.x - b.x, dy = a.y - b.y;
-      out[q + ((2 * p + 1) << ls)] = make_float2(dx * cs - dy * sn, dx * sn + dy * cs);
-    }
-    __syncthreads();
-    cur ^= 1;
+// patches and workspace may begin at any element
+typedef float m2_f32x2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef float m2_f32x4 __attribute__((ext_vector_type(4), aligned(8)));
+
+// Complex elements per workgroup: kFly radix-4 butterflies per thread.
+template <int kFly>
+constexpr int kElems = 4 * kFftThreads * kFly;
+
+// tw[k] = exp(sign 2 pi i k / N), k < 3 N / 4
+__device__ __forceinline__ void twiddles(float2* tw, int N, float sign) {
+  for (int k = threadIdx.x; k < 3 * N / 4; k += kFftThreads) {
+    float sn, cs;
+    sincospif(sign * 2.0f * static_cast<float>(k) / static_cast<float>(N), &sn, &cs);
+    tw[k] = make_float2(cs, sn);
   }
-  for (int n = threadIdx.x; n < N; n += kFftThreads) base[n * elem_stride] = lds[cur * N + n];
 }
 
-// Centred real image (row pitch `pitch` >= N) -> DFT order complex:
-// buf[(i + N/2) % N][(j + N/2) % N] = P[i][j].
-__global__ __launch_bounds__(256) void k_m2_load(const float* __restrict__ P, int pitch, float2* __restrict__ buf,
-                                                 int N) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (e >= static_cast<int64_t>(N) * N) return;
-  const int i = static_cast<int>(e / N), j = static_cast<int>(e - static_cast<int64_t>(i) * N);
-  const int h = N >> 1, msk = N - 1;
-  buf[static_cast<int64_t>((i + h) & msk) * N + ((j + h) & msk)] =
-      make_float2(P[static_cast<int64_t>(i) * pitch + j], 0.0f);
+__device__ __forceinline__ float2 times(float2 a, float2 w) {
+  return make_float2(a.x * w.x - a.y * w.y, a.x * w.y + a.y * w.x);
+}
+
+// DFTs of the kElems / N lines in v (pitch N + kPad), sign as the twiddles'.
+// Enters and leaves with all of v written and visible.
+template <int kFly>
+__device__ __forceinline__ void fft_block(float2* v, const float2* tw, int N, int logN, float sign) {
+  const int quarter = N >> 2, lq = logN - 2;
+  int ls = 0;  // log2 of the stride
+  for (; ls + 2 <= logN; ls += 2) {
+    float2 x[kFly][4];
+#pragma unroll
+    for (int f = 0; f < kFly; ++f) {
+      const int g = threadIdx.x + f * kFftThreads;
+      const float2* in = v + (g >> lq) * (N + kPad) + (g & (quarter - 1));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[f][k] = in[k * quarter];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int f = 0; f < kFly; ++f) {
+      const int g = threadIdx.x + f * kFftThreads;
+      const int t = g & (quarter - 1), p = t >> ls, q = t - (p << ls);
+      const float2 a = x[f][0], b = x[f][1], c = x[f][2], d = x[f][3];
+      const float2 s0 = make_float2(a.x + c.x, a.y + c.y), s1 = make_float2(a.x - c.x, a.y - c.y);
+      const float2 s2 = make_float2(b.x + d.x, b.y + d.y);
+      const float2 s3 = make_float2(-sign * (b.y - d.y), sign * (b.x - d.x));  // sign i (b - d)
+      float2* out = v + (g >> lq) * (N + kPad) + q + (p << (ls + 2));
+      out[0] = make_float2(s0.x + s2.x, s0.y + s2.y);
+      out[1 << ls] = times(make_float2(s1.x + s3.x, s1.y + s3.y), tw[p << ls]);
+      out[2 << ls] = times(make_float2(s0.x - s2.x, s0.y - s2.y), tw[2 * p << ls]);
+      out[3 << ls] = times(make_float2(s1.x - s3.x, s1.y - s3.y), tw[3 * p << ls]);
+    }
+    __syncthreads();
+  }
+  if (ls < logN) {
+    const int half = N >> 1;
+#pragma unroll
+    for (int f = 0; f < 2 * kFly; ++f) {
+      const int g = threadIdx.x + f * kFftThreads;
+      float2* in = v + (g >> (logN - 1)) * (N + kPad) + (g & (half - 1));
+      const float2 a = in[0], b = in[half];
+      in[0] = make_float2(a.x + b.x, a.y + b.y);
+      in[half] = make_float2(a.x - b.x, a.y - b.y);
+    }
+    __syncthreads();
+  }
+}
+
+// Forward transform of the rows of a centred real image (row pitch `pitch` >=
+// N), image centre to index 0, rows likewise: S[(i + N/2) % N][b].
+template <int kFly>
+__global__ __launch_bounds__(kFftThreads) void k_m2_image_rows(const float* __restrict__ P, int pitch,
+                                                               float2* __restrict__ S, int N, int logN) {
+  extern __shared__ float2 lds[];
+  const int lines = kElems<kFly> >> logN, h = N >> 1, msk = N - 1;
+  float2 *v = lds, *tw = lds + lines * (N + kPad);
+  const int i0 = blockIdx.x * lines;
+  twiddles(tw, N, -1.0f);
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e >> logN, j = e & msk, i = i0 + line;
+    v[line * (N + kPad) + ((j + h) & msk)] = make_float2(i < N ? P[static_cast<int64_t>(i) * pitch + j] : 0.f, 0.f);
+  }
+  __syncthreads();
+  fft_block<kFly>(v, tw, N, logN, -1.0f);
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e >> logN, b = e & msk, i = i0 + line;
+    if (i < N) S[static_cast<int64_t>((i + h) & msk) * N + b] = v[line * (N + kPad) + b];
+  }
+}
+
+// Forward transform of the columns, in place.
+template <int kFly>
+__global__ __launch_bounds__(kFftThreads) void k_m2_image_cols(float2* __restrict__ S, int N, int logN) {
+  extern __shared__ float2 lds[];
+  const int ll = 2 * 5 + (kFly == 4 ? 2 : 1) - logN, lines = 1 << ll;  // log2 of the lines
+  float2 *v = lds, *tw = lds + lines * (N + kPad);
+  const int b0 = blockIdx.x * lines;
+  twiddles(tw, N, -1.0f);
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e & (lines - 1), a = e >> ll;
+    v[line * (N + kPad) + a] =
+        b0 + line < N ? S[static_cast<int64_t>(a) * N + b0 + line] : make_float2(0.f, 0.f);
+  }
+  __syncthreads();
+  fft_block<kFly>(v, tw, N, logN, -1.0f);
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e & (lines - 1), a = e >> ll;
+    if (b0 + line < N) S[static_cast<int64_t>(a) * N + b0 + line] = v[line * (N + kPad) + a];
+  }
 }
 
 struct Dirs {
   double l0[kChunk], m0[kChunk];
 };
 
-// work[s][a][b] = S[a][b] D^(a' du, b' du; l0_s, m0_s); the direction of
-// a one-source launch read from device memory (l0, m0 at ddir) when ddir
-// is not null.
-__global__ __launch_bounds__(256) void k_m2_dhat(const float2* __restrict__ S, float2* __restrict__ work, int N,
-                                                 double du, double dt, double frac_bw, Dirs d,
-                                                 const double* __restrict__ ddir) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t NN = static_cast<int64_t>(N) * N;
-  if (e >= NN) return;
-  const int s = blockIdx.y;
-  const int a = static_cast<int>(e / N), b = static_cast<int>(e - static_cast<int64_t>(a) * N);
-  const double u0 = (a < N / 2 ? a : a - N) * du, v0 = (b < N / 2 ? b : b - N) * du;
-  const double l0 = ddir != nullptr ? ddir[0] : d.l0[s], m0 = ddir != nullptr ? ddir[1] : d.m0[s];
-  const double hpsi = M_PI * kOmegaEarth * (-v0 * l0 + u0 * m0) * dt;  // dPsi / 2
-  const double hphi = M_PI * frac_bw * sqrt(l0 * l0 + m0 * m0) * sqrt(u0 * u0 + v0 * v0);
-  const double sp = hpsi == 0.0 ? 1.0 : sin(hpsi) / hpsi;
-  const double sf = hphi == 0.0 ? 1.0 : sin(hphi) / hphi;
-  const float dh = static_cast<float>(sp * sf);
-  const float2 v = S[e];
-  work[s * NN + e] = make_float2(v.x * dh, v.y * dh);
+// sin(pi y) / (pi y) in FP64 to about 1e-11: the Taylor series over half a
+// turn through x^15, the reciprocal by one Newton step.
+__device__ __forceinline__ double sinc_pi(double y) {
+  const double q = rint(y), x = (y - q) * M_PI, x2 = x * x;
+  double p = -1.0 / 1307674368000.0;
+  p = fma(p, x2, 1.0 / 6227020800.0);
+  p = fma(p, x2, -1.0 / 39916800.0);
+  p = fma(p, x2, 1.0 / 362880.0);
+  p = fma(p, x2, -1.0 / 5040.0);
+  p = fma(p, x2, 1.0 / 120.0);
+  p = fma(p, x2, -1.0 / 6.0);
+  p = fma(p * x2, x, x);
+  const double z = M_PI * y, r = __builtin_amdgcn_rcp(z);
+  const double v = p * fma(r, fma(-z, r, 1.0), r);
+  const bool odd = 0.5 * q != rint(0.5 * q);
+  return fabs(y) < 1e-9 ? 1.0 : odd ? -v : v;
 }
 
-// P[s][i][j] = Re work[s][(i + N/2) % N][(j + N/2) % N] / N^2
-__global__ __launch_bounds__(256) void k_m2_store(const float2* __restrict__ work, float* __restrict__ P, int N,
-                                                  float scale) {
-  const int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t NN = static_cast<int64_t>(N) * N;
-  if (e >= NN) return;
-  const int s = blockIdx.y;
-  const int i = static_cast<int>(e / N), j = static_cast<int>(e - static_cast<int64_t>(i) * N);
+// D^(a' du, b' du) of one direction: fac = omega_E dt, fbw = (dnu / nu) |l0|
+__device__ __forceinline__ float d_hat(int a, int b, int N, double du, double l0, double m0, double fac, double fbw) {
+  const double u0 = (a < N / 2 ? a : a - N) * du, v0 = (b < N / 2 ? b : b - N) * du;
+  const double psi = fac * (-v0 * l0 + u0 * m0);  // dPsi / (2 pi)
+  const double phi = fbw * sqrt(u0 * u0 + v0 * v0);
+  return static_cast<float>(sinc_pi(psi) * sinc_pi(phi));
+}
+
+// Rows a = 0 .. N/2 of the Hermitian part of S D^, inverse transformed:
+// work[s][a][(j + N/2) % N].  The direction of a one-source launch is read
+// from device memory (l0, m0 at ddir) when ddir is not null.
+template <int kFly>
+__global__ __launch_bounds__(kFftThreads) void k_m2_rows(const float2* __restrict__ S, float2* __restrict__ work, int N,
+                                                         int logN, double du, double dt, double frac_bw, Dirs d,
+                                                         const double* __restrict__ ddir) {
+  extern __shared__ float2 lds[];
+  const int lines = kElems<kFly> >> logN, h = N >> 1, msk = N - 1;
+  float2 *v = lds, *tw = lds + lines * (N + kPad);
+  const int s = blockIdx.y, a0 = blockIdx.x * lines;
+  const double l0 = ddir != nullptr ? ddir[0] : d.l0[s], m0 = ddir != nullptr ? ddir[1] : d.m0[s];
+  const double fac = kOmegaEarth * dt, fbw = frac_bw * sqrt(l0 * l0 + m0 * m0);
+  twiddles(tw, N, 1.0f);
+#pragma unroll 2
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e >> logN, b = e & msk, a = a0 + line;
+    float2 x = make_float2(0.f, 0.f);
+    if (a <= h) {
+      const int an = (N - a) & msk, bn = (N - b) & msk;  // the cell of -a', -b'
+      const float2 p = S[static_cast<int64_t>(a) * N + b], q = S[static_cast<int64_t>(an) * N + bn];
+      const float dp = d_hat(a, b, N, du, l0, m0, fac, fbw);
+      // the model is even, but where a' or b' = -N/2 stands for both signs
+      const float dq = a == h || b == h ? d_hat(an, bn, N, du, l0, m0, fac, fbw) : dp;
+      x = make_float2(0.5f * (p.x * dp + q.x * dq), 0.5f * (p.y * dp - q.y * dq));
+    }
+    v[line * (N + kPad) + b] = x;
+  }
+  __syncthreads();
+  fft_block<kFly>(v, tw, N, logN, 1.0f);
+  float2* out = work + static_cast<int64_t>(s) * (h + 1) * N;
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e >> logN, j = e & msk, a = a0 + line;
+    if (a <= h) out[static_cast<int64_t>(a) * N + ((j + h) & msk)] = v[line * (N + kPad) + j];
+  }
+}
+
+// The patches: columns 2 c and 2 c + 1 as real and imaginary part of one
+// inverse transform over a.  (Rows 0 and N/2 are real in exact arithmetic.)
+template <int kFly>
+__global__ __launch_bounds__(kFftThreads) void k_m2_cols(const float2* __restrict__ work, float* __restrict__ P, int N,
+                                                         int logN, float scale) {
+  extern __shared__ float2 lds[];
+  const int ll = 2 * 5 + (kFly == 4 ? 2 : 1) - logN, lines = 1 << ll;  // log2 of the lines
   const int h = N >> 1, msk = N - 1;
-  P[s * NN + e] = work[s * NN + static_cast<int64_t>((i + h) & msk) * N + ((j + h) & msk)].x * scale;
+  float2 *v = lds, *tw = lds + lines * (N + kPad);
+  const int s = blockIdx.y, c0 = blockIdx.x * lines;
+  const m2_f32x4* in = reinterpret_cast<const m2_f32x4*>(work + static_cast<int64_t>(s) * (h + 1) * N);
+  twiddles(tw, N, 1.0f);
+  for (int e = threadIdx.x; e < (h + 1) << ll; e += kFftThreads) {
+    const int line = e & (lines - 1), a = e >> ll;
+    m2_f32x4 y = {0.f, 0.f, 0.f, 0.f};
+    if (c0 + line < h) y = in[static_cast<int64_t>(a) * h + c0 + line];
+    float2* z = v + line * (N + kPad);
+    if (a == 0 || a == h) {
+      z[a] = make_float2(y.x, y.z);
+    } else {
+      z[a] = make_float2(y.x - y.w, y.y + y.z);
+      z[N - a] = make_float2(y.x + y.w, y.z - y.y);
+    }
+  }
+  __syncthreads();
+  fft_block<kFly>(v, tw, N, logN, 1.0f);
+  float* out = P + static_cast<int64_t>(s) * N * N;
+  for (int e = threadIdx.x; e < kElems<kFly>; e += kFftThreads) {
+    const int line = e & (lines - 1), i = e >> ll;
+    const float2 p = v[line * (N + kPad) + i];
+    if (c0 + line < h)
+      *reinterpret_cast<m2_f32x2*>(out + static_cast<int64_t>((i + h) & msk) * N + 2 * (c0 + line)) =
+          m2_f32x2{p.x * scale, p.y * scale};
+  }
 }
 
 int log2_exact(int N) {
@@ -122,17 +267,41 @@ int validate_grid(int32_t N, double cell) {
   return PSF_OK;
 }
 
-// 2-D FFT of n_batch N x N complex arrays in place: rows, then columns.
-int fft2(float2* data, int N, int n_batch, float sign, hipStream_t s) {
-  const int logN = log2_exact(N);
-  const size_t lds = 2 * static_cast<size_t>(N) * sizeof(float2);
-  const int64_t NN = static_cast<int64_t>(N) * N;
-  hipLaunchKernelGGL(k_fft_lines, dim3(N, n_batch), dim3(kFftThreads), lds, s, data, N, logN, int64_t(1),
-                     int64_t(N), NN, sign);
-  hipLaunchKernelGGL(k_fft_lines, dim3(N, n_batch), dim3(kFftThreads), lds, s, data, N, logN, int64_t(N),
-                     int64_t(1), NN, sign);
-  hipError_t e = hipGetLastError();
-  return e == hipSuccess ? PSF_OK : hip_fail(e, "k_fft_lines launch");
+// Butterflies per thread: 2 where a line fits (N <= 2048), 4 for N = 4096.
+size_t fft_lds_bytes(int N, int fly) {
+  return (static_cast<size_t>(4 * kFftThreads * fly / N) * (N + kPad) + 3 * N / 4) * sizeof(float2);
+}
+
+unsigned fft_blocks(int lines, int N, int fly) {
+  const int per = 4 * kFftThreads * fly / N;
+  return static_cast<unsigned>((lines + per - 1) / per);
+}
+
+template <int kFly>
+void launch_spectrum(const float* P, int pitch, float2* S, int N, hipStream_t s) {
+  const size_t lds = fft_lds_bytes(N, kFly);
+  const dim3 g(fft_blocks(N, N, kFly)), b(kFftThreads);
+  hipLaunchKernelGGL(k_m2_image_rows<kFly>, g, b, lds, s, P, pitch, S, N, log2_exact(N));
+  hipLaunchKernelGGL(k_m2_image_cols<kFly>, g, b, lds, s, S, N, log2_exact(N));
+}
+
+template <int kFly>
+void launch_sources(const float2* S, float2* work, float* P, int N, int nq, double du, double dt, double frac_bw,
+                    const Dirs& d, const double* ddir, hipStream_t s) {
+  const size_t lds = fft_lds_bytes(N, kFly);
+  hipLaunchKernelGGL(k_m2_rows<kFly>, dim3(fft_blocks(N / 2 + 1, N, kFly), nq), dim3(kFftThreads), lds, s, S, work, N,
+                     log2_exact(N), du, dt, frac_bw, d, ddir);
+  hipLaunchKernelGGL(k_m2_cols<kFly>, dim3(fft_blocks(N / 2, N, kFly), nq), dim3(kFftThreads), lds, s, work, P, N,
+                     log2_exact(N), static_cast<float>(1.0 / (static_cast<double>(N) * N)));
+}
+
+int run_sources(const float2* S, float2* work, float* P, int N, int nq, double cell, double dt, double frac_bw,
+                const Dirs& d, const double* ddir, hipStream_t s) {
+  const double du = 1.0 / (N * cell);
+  if (N <= 2048) launch_sources<2>(S, work, P, N, nq, du, dt, frac_bw, d, ddir, s);
+  else launch_sources<4>(S, work, P, N, nq, du, dt, frac_bw, d, ddir, s);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? PSF_OK : hip_fail(e, "k_m2_rows launch");
 }
 
 // The grid the effective PSF is contracted on: offsets -N/2 .. N/2 - 1, or
@@ -170,19 +339,7 @@ size_t patch_m2_workspace(int32_t N, int32_t n_src) {
 // N^2 complex values).
 int method2_patch_device_dir(int32_t N, double cell, const float* S, const double* d_dir, double dt_bin,
                              double dnu_bin, double nu, float* P, float2* work, hipStream_t s) {
-  const int64_t NN = static_cast<int64_t>(N) * N;
-  const unsigned nb = static_cast<unsigned>((NN + 255) / 256);
-  const double du = 1.0 / (N * cell);
-  hipLaunchKernelGGL(k_m2_dhat, dim3(nb, 1), dim3(256), 0, s, reinterpret_cast<const float2*>(S), work, N, du,
-                     dt_bin, dnu_bin / nu, Dirs{}, d_dir);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return hip_fail(e, "k_m2_dhat launch");
-  int st;
-  if ((st = fft2(work, N, 1, 1.0f, s)) != PSF_OK) return st;
-  hipLaunchKernelGGL(k_m2_store, dim3(nb, 1), dim3(256), 0, s, work, P, N,
-                     static_cast<float>(1.0 / static_cast<double>(NN)));
-  e = hipGetLastError();
-  return e == hipSuccess ? PSF_OK : hip_fail(e, "k_m2_store launch");
+  return run_sources(reinterpret_cast<const float2*>(S), work, P, N, 1, cell, dt_bin, dnu_bin / nu, Dirs{}, d_dir, s);
 }
 
 }  // namespace psf
@@ -228,15 +385,14 @@ int psf_method2_spectrum(const psf_obs* obs, int32_t N, double cell, int prec, f
   float* partial = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(c) +
                                             align_up(static_cast<size_t>(obs->K) * sizeof(float2), 256));
   float* Peff = reinterpret_cast<float*>(w + L.Peff);
-  hipError_t e;
   // At the phase centre every sample's phase difference is exactly 0, so
   // D_k = 1 and u' = u: the effective PSF.
   if ((st = patch_of(obs, &g, plan, prec, rec, c, partial, Peff, s)) != PSF_OK) return st;
-  const int64_t NN = static_cast<int64_t>(N) * N;
   float2* Sc = reinterpret_cast<float2*>(S);
-  hipLaunchKernelGGL(k_m2_load, dim3(static_cast<unsigned>((NN + 255) / 256)), dim3(256), 0, s, Peff, g.nm, Sc, N);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_m2_load launch");
-  return fft2(Sc, N, 1, -1.0f, s);
+  if (N <= 2048) launch_spectrum<2>(Peff, g.nm, Sc, N, s);
+  else launch_spectrum<4>(Peff, g.nm, Sc, N, s);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? PSF_OK : hip_fail(e, "k_m2_image_rows launch");
 }
 
 int psf_method2_patch(int32_t N, double cell, const float* S, int32_t n_src, const double* h_dirs, double dt_bin,
@@ -261,8 +417,6 @@ int psf_method2_patch(int32_t N, double cell, const float* S, int32_t n_src, con
   const hipStream_t s = static_cast<hipStream_t>(stream);
   float2* work = static_cast<float2*>(ws);
   const int64_t NN = static_cast<int64_t>(N) * N;
-  const unsigned nb = static_cast<unsigned>((NN + 255) / 256);
-  const double du = 1.0 / (N * cell);
   for (int q0 = 0; q0 < n_src; q0 += kChunk) {
     const int nq = std::min(kChunk, n_src - q0);
     Dirs d{};
@@ -270,14 +424,9 @@ int psf_method2_patch(int32_t N, double cell, const float* S, int32_t n_src, con
       d.l0[q] = h_dirs[2 * (q0 + q)];
       d.m0[q] = h_dirs[2 * (q0 + q) + 1];
     }
-    hipLaunchKernelGGL(k_m2_dhat, dim3(nb, nq), dim3(256), 0, s, reinterpret_cast<const float2*>(S), work, N, du,
-                       dt_bin, dnu_bin / nu, d, static_cast<const double*>(nullptr));
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "k_m2_dhat launch");
-    if ((st = fft2(work, N, nq, 1.0f, s)) != PSF_OK) return st;
-    hipLaunchKernelGGL(k_m2_store, dim3(nb, nq), dim3(256), 0, s, work, P + q0 * NN, N,
-                       static_cast<float>(1.0 / static_cast<double>(NN)));
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_m2_store launch");
+    if ((st = run_sources(reinterpret_cast<const float2*>(S), work, P + q0 * NN, N, nq, cell, dt_bin, dnu_bin / nu, d,
+                          nullptr, s)) != PSF_OK)
+      return st;
   }
   return PSF_OK;
 }

@@ -157,3 +157,24 @@ def test_method2_error_against_exact_psf_grows_with_radius(pk):
         print(f"method 2 vs exact at {r_deg} deg: {e:.3e} ({10 * math.log10(e):.1f} dB); "
               f"effective PSF vs exact {e0:.3e} ({10 * math.log10(e0):.1f} dB)", flush=True)
     assert errs[0] < errs[1] < errs[2]
+
+
+@pytest.mark.parametrize("N", [16, 32, 64, 512, 1024, 2048, 4096])
+def test_patches_of_any_spectrum(pk, N):
+    """Every grid size (radix-4 passes alone or with one of radix 2, one line
+    per workgroup to many) from a spectrum that is not Hermitian, of which the
+    patch is the real part.  Bound: an FFT of n levels in FP32 is off by
+    2^-24 sqrt(n) of the result's rms, one standard deviation; twelve."""
+    g = np.random.default_rng(N)
+    S = (g.standard_normal((N, N)) + 1j * g.standard_normal((N, N))).astype(np.complex64)
+    cell = 3.0 * ps.ARCSEC
+    dirs = [(0.01, -0.005), (0.0, 0.0), (-0.02, 0.03)]
+    P = pk.method2_patches(torch.as_tensor(S, device="cuda"), cell, dirs, DT, DNU, NU).cpu().numpy()
+    for q, (l0, m0) in enumerate(dirs):
+        a = np.fft.fftfreq(N, cell)[:, None]
+        b = np.fft.fftfreq(N, cell)[None, :]
+        dh = np.sinc(7.2921150e-5 * (-b * l0 + a * m0) * DT) * np.sinc(DNU / NU * np.hypot(l0, m0) * np.hypot(a, b))
+        ref = np.fft.fftshift(np.fft.ifft2(S * dh).real)
+        e, bound = float(np.max(np.abs(P[q] - ref))), 12 * 2.0 ** -24 * np.sqrt(2 * np.log2(N)) * float(np.sqrt(np.mean(ref * ref)))
+        print(f"N {N} direction {q}: {e / bound:.2f} of the bound", flush=True)
+        assert e <= bound
