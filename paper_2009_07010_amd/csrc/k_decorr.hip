@@ -488,12 +488,21 @@ static decltype(&k_decorr<false, kNotWide>) decorr_kernel(const ObsView& o) {
   return many ? k_decorr<false, kWideWindow> : k_decorr<false, kNotWide>;
 }
 
+// Without derivatives also for observations of few bins: one wave per bin
+// where all of them run at once and a bin has samples for a quarter of the
+// lanes (420 bins of 30 samples: 8.5 us with one lane each, whose loads follow
+// one another, 4.5 with a wave each).
+static bool few_bins(const ObsView& o) {
+  const double samples = static_cast<double>(o.n_bl) * o.n_t * o.n_ch;
+  return use_wave_bins(o) || (o.K > 0 && o.K <= 8192 && samples >= 16.0 * static_cast<double>(o.K));
+}
+
 hipError_t launch_decorr(const ObsView& o, double l0, double m0, double dl, double dm, const float2* D_in,
                          float2* D_out, BinRec* rec_out, float2* c_out, float2* coef_out, hipStream_t stream,
                          const double* dir) {
   const int threads = 256;
   const int64_t blocks = (o.K + threads - 1) / threads;
-  if (D_in == nullptr && use_wave_bins(o)) {
+  if (D_in == nullptr && (coef_out != nullptr ? use_wave_bins(o) : few_bins(o))) {
     const dim3 g(static_cast<unsigned>((o.K + 3) / 4));
     if (coef_out != nullptr)
       hipLaunchKernelGGL(k_decorr_wave<true>, g, dim3(256), 0, stream, o, l0, m0, dl, dm, dir, int64_t(0),
@@ -516,7 +525,7 @@ hipError_t launch_decorr_sources(const ObsView& o, const double* dirs, int64_t d
                                  BinRec* rec_out, float2* c_out, int64_t rec_stride, hipStream_t stream) {
   const int threads = 256;
   const int64_t blocks = (o.K + threads - 1) / threads;
-  if (use_wave_bins(o)) {
+  if (few_bins(o)) {
     hipLaunchKernelGGL(k_decorr_wave<false>, dim3(static_cast<unsigned>((o.K + 3) / 4), static_cast<unsigned>(n_src)),
                        dim3(256), 0, stream, o, 0.0, 0.0, 0.0, 0.0, dirs, dir_stride, rec_stride, nullptr, rec_out,
                        c_out, nullptr);

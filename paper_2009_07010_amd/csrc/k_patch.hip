@@ -965,9 +965,12 @@ void k_patch(BatchArgs a) {
   }
 }
 
-// Sum over the k-slices of one element (row i, column j of the
-// contraction's output) of a source's partial slabs, in slice order.
-__device__ __forceinline__ float slab_sum(karg_plan& p, int i, int j) {
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// Sum over the k-slices of four elements (rows i .. i + 3, i a multiple of 4,
+// column j of the contraction's output; together in a slab) of a source's
+// partial slabs, in slice order: of part g of G of the slices.
+__device__ __forceinline__ f32x4 slab_sum(karg_plan& p, int i, int j, int g, int G) {
   const auto& t = p.tp;
   const int span_i = t.ti_a * 16 * t.tbi[0], span_j = t.tj_a * 16 * t.tbj[0];
   const int r = i < span_i ? 0 : 1, c = j < span_j ? 0 : 1;
@@ -979,22 +982,21 @@ __device__ __forceinline__ float slab_sum(karg_plan& p, int i, int j) {
   // slab layout [block][lane][4]: block (li/16, lj/16), lane = col + 16 (row/4), element row % 4
   const int blk = (li >> 4) * t.tbj[c] + (lj >> 4);
   const int rr = li & 15, cc = lj & 15;
-  const float* q = p.partial + tile_first_elem(t, ti, tj) + (static_cast<int64_t>(blk) * 64 + cc + 16 * (rr >> 2)) * 4 +
-                   (rr & 3);
-  const int64_t slab = slab_elems(t, r, c);
-  // slices added in order; 16 loads are issued before their adds so that
-  // their latencies overlap (same sum, bit for bit)
-  const int nsl = t.ns[r][c];
-  float sum = 0.f;
-  int n = 0;
-  for (; n + 16 <= nsl; n += 16) {
-    float v[16];
+  const f32x4* q = reinterpret_cast<const f32x4*>(p.partial + tile_first_elem(t, ti, tj)) +
+                   static_cast<int64_t>(blk) * 64 + cc + 16 * (rr >> 2);
+  const int64_t slab = slab_elems(t, r, c) / 4;
+  // slices added in order; 8 loads are issued before their adds so that their
+  // latencies overlap (the last of them repeated where fewer are left)
+  const int nsl = t.ns[r][c], n1 = (g + 1) * nsl / G;
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+  for (int n = g * nsl / G; n < n1; n += 8) {
+    f32x4 v[8];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = q[(n + u) * slab];
+    for (int u = 0; u < 8; ++u) v[u] = q[min(n + u, n1 - 1) * slab];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) sum += v[u];
+    for (int u = 0; u < 8; ++u)
+      if (n + u < n1) sum += v[u];
   }
-  for (; n < nsl; ++n) sum += q[n * slab];
   return sum;
 }
 
@@ -1004,29 +1006,85 @@ __device__ __forceinline__ float normalised(float v, double peak) {
   return peak != 0.0 ? static_cast<float>(static_cast<double>(v) / peak) : 0.0f;
 }
 
-// K-f: P = 2 * sum over the k-slices of the pixel's tile, in slice order.
-// Grid row y is source y of the launch.
+// Output quads of a source: four rows of one column, or in the symmetric form
+// the centre row alone and then four rows on either side of it.
+template <class Plan>
+__host__ __device__ inline int finalize_quads(const Plan& p) {
+  return p.nm * (p.sym ? 1 + ((p.nl - 1) / 2 + 3) / 4 : (p.nl + 3) / 4);
+}
+
+// Threads per quad of a source's finalise, each for its part of the slices:
+// small patches of many slices leave the chip to a few long chains of loads
+// otherwise.  Of the source alone, so that a patch does not depend on the
+// others of its launch.
+template <class Plan>
+__host__ __device__ inline int finalize_threads(const Plan& p) {
+  int ns = 0;
+  for (int r = 0; r < 2; ++r)
+    for (int c = 0; c < 2; ++c) {
+      const bool used = (r == 0 ? p.tp.ti_a : p.tp.ti_b) > 0 && (c == 0 ? p.tp.tj_a : p.tp.tj_b) > 0;
+      if (used && p.tp.ns[r][c] > ns) ns = p.tp.ns[r][c];
+    }
+  int G = 1;
+  while (G < 32 && ns >= 4 * G && finalize_quads(p) * G < 131072) G *= 2;
+  return G;
+}
+
+// K-f: P = 2 * sum over the k-slices of the pixel's tile, G parts of them each
+// in slice order, then the parts in order.  Grid row y is source y of the
+// launch.  Bound by the latency of the loads, of which a slab's are 16 bytes
+// per lane and contiguous along a row: 33 x 33 pixels of 256 slices 16 -> 5.5 us,
+// 129 x 129 35 -> 7, against one thread per pixel and 4-byte loads.
 __global__ __launch_bounds__(256) void k_finalize(BatchArgs a) {
   (void)a;
   typedef const __attribute__((address_space(4))) uint8_t karg_byte;
   karg_plan& p = ((karg_plan*)((karg_byte*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(BatchArgs, src)))[blockIdx.y];
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<int64_t>(p.nl) * p.nm) return;
-  const int i = static_cast<int>(idx / p.nm), j = static_cast<int>(idx - static_cast<int64_t>(i) * p.nm);
-  if (p.sym) {
-    // symmetric form: row i has offset s = i - h from the grid's centre row;
-    // C row |s| + 15 and S row 16 CB + |s| - 1 of the contraction give
-    // P(+-|s|) = 2 (C -+ S)
-    const int h = (p.nl - 1) / 2, cb = h / 16 + 1;
-    const int s = i - h, as = s < 0 ? -s : s;
-    const float c = slab_sum(p, as + 15, j);
-    const float sn = as > 0 ? slab_sum(p, 16 * cb + as - 1, j) : 0.f;
-    const float v = 2.0f * (s >= 0 ? c - sn : c + sn);
-    p.P[idx] = p.peak == nullptr ? v : normalised(v, *p.peak);
-    return;
+  __shared__ f32x4 part[2][256];
+  const int G = finalize_threads(p), units = 256 / G;
+  const int g = threadIdx.x / units, lx = threadIdx.x - g * units;
+  const int idx = static_cast<int>(blockIdx.x) * units + lx;
+  const bool ok = idx < finalize_quads(p);
+  const int quad = idx / p.nm, j = idx - quad * p.nm;
+  // symmetric form: row i has offset s = i - h from the grid's centre row;
+  // C row |s| + 15 and S row 16 CB + |s| - 1 of the contraction give
+  // P(+-|s|) = 2 (C -+ S)
+  const int h = (p.nl - 1) / 2, cb = h / 16 + 1;
+  f32x4 c = {0.f, 0.f, 0.f, 0.f}, sn = {0.f, 0.f, 0.f, 0.f};
+  if (ok) {
+    c = slab_sum(p, p.sym ? 12 + 4 * quad : 4 * quad, j, g, G);
+    if (p.sym && quad > 0) sn = slab_sum(p, 16 * cb + 4 * (quad - 1), j, g, G);
   }
-  const float v = 2.0f * slab_sum(p, i, j);
-  p.P[idx] = p.peak == nullptr ? v : normalised(v, *p.peak);
+  if (G > 1) {
+    part[0][threadIdx.x] = c;
+    part[1][threadIdx.x] = sn;
+    __syncthreads();
+    if (g > 0) return;
+    for (int q = 1; q < G; ++q) {
+      c += part[0][q * units + lx];
+      sn += part[1][q * units + lx];
+    }
+  }
+  if (!ok) return;
+  const double* peak = p.peak;
+  const double pk = peak == nullptr ? 1.0 : *peak;
+  auto put = [&](int i, float v) {
+    p.P[static_cast<int64_t>(i) * p.nm + j] = peak == nullptr ? v : normalised(v, pk);
+  };
+  if (!p.sym) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (4 * quad + u < p.nl) put(4 * quad + u, 2.0f * c[u]);
+  } else if (quad == 0) {
+    put(h, 2.0f * c[3]);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int s = 4 * (quad - 1) + u + 1;
+      if (s > h) break;
+      put(h + s, 2.0f * (c[u] - sn[u]));
+      put(h - s, 2.0f * (c[u] + sn[u]));
+    }
+  }
 }
 
 // a6: one block per range of K; FP64 sum of Re c in a fixed order
@@ -1149,11 +1207,12 @@ hipError_t launch_patch(int prec, const BatchArgs& a, int64_t n_wg, hipStream_t 
 }
 
 hipError_t launch_finalize(const BatchArgs& a, hipStream_t stream) {
-  int64_t n = 0;
-  for (int s = 0; s < a.n_src; ++s) n = max(n, static_cast<int64_t>(a.src[s].nl) * a.src[s].nm);
-  const int threads = 256;
-  hipLaunchKernelGGL(k_finalize, dim3(static_cast<unsigned>((n + threads - 1) / threads), a.n_src),
-                     dim3(threads), 0, stream, a);
+  int64_t blocks = 0;
+  for (int s = 0; s < a.n_src; ++s) {
+    const int units = 256 / finalize_threads(a.src[s]);
+    blocks = max(blocks, (static_cast<int64_t>(finalize_quads(a.src[s])) + units - 1) / units);
+  }
+  hipLaunchKernelGGL(k_finalize, dim3(static_cast<unsigned>(blocks), a.n_src), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

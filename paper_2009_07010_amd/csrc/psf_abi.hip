@@ -168,6 +168,11 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
   for (int r = 0; r < 2; ++r)
     for (int c = 0; c < 2; ++c) {
       int64_t n = static_cast<int64_t>(std::llround(cost[r][c] * static_cast<double>(chunks) / item_work));
+      // few chunks: slices of c of them take c times a chunk, and their slabs
+      // (written and read, 1 ps per byte) chunks / c times a slab
+      const double slab = 1024.0 * t.tbi[r] * t.tbj[c] * 1e-12;
+      const double least = std::sqrt(static_cast<double>(chunks) * slab * 2.1e9 / cost[r][c]);
+      n = std::min(n, static_cast<int64_t>(static_cast<double>(chunks) / std::max(1.0, std::floor(least))));
       n = std::min<int64_t>(std::max<int64_t>(1, n), chunks);
       t.ns[r][c] = static_cast<int>(n);
       t.kps[r][c] = ((chunks + n - 1) / n) * ch;
@@ -176,16 +181,20 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
   return p;
 }
 
-// Which patches run gridded.  Measured (MI355X, us per psf_patch call): the
-// dense form costs 40 us (60 in its symmetric families, whose many slices few
-// threads sum) plus its contraction, in split-BF16 0.09 ns per bin at 65 x 65,
-// 0.34 at 257 x 257 and 5.3 at 600 x 600 (patch_work at 256 CUs and 2.1 GHz
-// follows these within 40%); the gridded form 45 us, 0.06 ns per bin whatever
-// the patch, and 0.03-0.08 ns per cell.  At K = 30400 the two meet (dense 39
-// against gridded 55 us at 33 x 33, 82 against 66 at 257 x 257), below 24576
-// bins the dense call is the shorter.  PSF_PLAIN_BF16, a negative control,
-// stays dense; the mixed and stochastic arithmetics exist in the gridded form
-// only.
+// Which patches run gridded.  Measured (MI355X, us per psf_patch call, boxcar
+// bins of 3 x 4 samples, split-BF16; patch_work at 256 CUs and 2.1 GHz follows
+// the dense form within 40%):
+//   pixels        33        65       129       200       257       300
+//   K =  27k   30 | 48   26 | 48   34 | 49   48 | 56   47 | 56   76 | 77   dense | gridded
+//   K =  51k   34 | 41   29 | 40   40 | 43   70 | 48   57 | 50  123 | 70
+//   K = 152k   57 | 45   42 | 45   56 | 46  166 | 53   90 | 54  327 | 73
+//   K = 302k   93 | 52   52 | 52   77 | 53  304 | 59  150 | 58  623 | 76
+// Below 24576 bins the dense call is the shorter.  The line is drawn with 40 us
+// (60 in the symmetric families) for the dense form beside its contraction, 10
+// to 25 more than it takes, so that a patch near the line runs gridded: within
+// 10 us of the other, and with a third of its error.  PSF_PLAIN_BF16, a
+// negative control, stays dense; the mixed and stochastic arithmetics exist in
+// the gridded form only.
 GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec) {
   constexpr int64_t kMinBins = 24576;
   GridPlan g;

@@ -99,3 +99,27 @@ def test_precision_split_forms_against_fp32_every_pixel(runs):
             line += f"  {emax:.2e}  {math.sqrt(float(np.mean(d * d))):.2e}"
         print(line, flush=True)
     assert worst <= 2 * TOL
+
+
+@pytest.mark.parametrize("nl,nm,n_t", [(65, 65, 3), (65, 65, 200), (129, 40, 400), (257, 33, 100), (33, 33, 400),
+                                       (34, 47, 7), (300, 290, 60), (1, 1, 400), (2, 500, 90)])
+def test_slices_of_small_patches(pk, nl, nm, n_t):
+    """The dense form from one slice of bins to as many as there are workgroups,
+    summed by 1 to 32 threads per four rows, in the symmetric families (65, 129,
+    257 rows) and others, rows and columns short of their blocks.  FP32: within
+    1e-6 of sum |c|; two runs give the same bits."""
+    import oracle as orc
+    obs = ps.tiny_random(70 + nl, n_ant=8, n_t=n_t, n_ch=2, nt=1, nc=1, radius_m=2000.0, dt=3600.0 / n_t)
+    assert obs.K < 24576
+    dobs = pk.DeviceObservation(obs)
+    l0, m0 = ps.direction(0.8 * ps.DEG, 1.1)
+    cell = 1.5 * ps.ARCSEC
+    src = ps.Source(l0=l0, m0=m0, l_first=l0 - 0.5 * (nl - 1) * cell, m_first=m0 - 0.5 * (nm - 1) * cell, dl=cell,
+                    dm=cell, nl=nl, nm=nm)
+    D = orc.decorr(obs, l0, m0)
+    ref = orc.patch_factored(obs, src, D)
+    P = pk.patch(dobs, src, prec="fp32")
+    assert torch.equal(P, pk.patch(dobs, src, prec="fp32"))
+    e, b = float(np.max(np.abs(P.double().cpu().numpy() - ref))), 1e-6 * 2.0 * float(np.sum(np.abs(obs.W * D)))
+    print(f"K={obs.K} {nl}x{nm}: {e / b:.2f} of the bound", flush=True)
+    assert e <= b
