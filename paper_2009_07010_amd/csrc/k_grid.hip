@@ -74,6 +74,7 @@ constexpr int kTabRows = 1024;    // samples of a chunk whose projections sit in
 constexpr int kTabFreq = 512;     // frequency bins whose centre frequencies do
 constexpr int kGridMaxLevels = 6, kLeastSpan = 1024;  // of spans
 constexpr int kCutBlocks = 8;     // workgroups that cut the bins into spans
+constexpr int kSparse = 512;      // bins that make a tile worth while
 constexpr int kEvenMin = 3, kEvenMax = 16;  // channels per bin summed as evenly spaced
 constexpr int kRun = 8;           // batches of 64 bins summed in FP32 before a window is folded (2^9 bins)
 constexpr int kInitBlocks = 512;
@@ -842,9 +843,13 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
       ch.rows = nt;
       float vt;  // cells per time bin
       const float vf = fmaxf(fabsf(__shfl(x, 1)), fabsf(__shfl(y, 1))) / max(1, ch.nf - 1);  // per frequency bin
-      if (fits & 1) {
-        const int sl = last_lane(fits), ss = sl >> 1;
-        ch.rows = static_cast<int>((static_cast<int64_t>(nt - 1) * ss) / 31) + 1;
+      const int sl = fits & 1 ? last_lane(fits) : 0, ss = sl >> 1;
+      if (fits & 1) ch.rows = static_cast<int>((static_cast<int64_t>(nt - 1) * ss) / 31) + 1;
+      // Where the track leaves a tile within kSparse bins (long baselines, wide
+      // bands, long steps in time), a tile saves no atomics: then none, and
+      // the chunk as long as it may be (K = 216k of 40 antennas to 8 km, two
+      // channels 400 MHz apart, 14 s steps, 150 x 150 pixels: 334 -> 77 us).
+      if ((fits & 1) && (ch.rows == nt || ch.rows * ch.nf >= kSparse)) {
         vt = fmaxf(fabsf(__shfl(x, 2 * ss)), fabsf(__shfl(y, 2 * ss))) / max(1, ch.rows - 1);
         box.bx = __builtin_amdgcn_readfirstlane(static_cast<int>(__shfl(ex, sl)));
         box.by = __builtin_amdgcn_readfirstlane(static_cast<int>(__shfl(ey, sl)));
@@ -853,6 +858,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
         box.ox = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(fx - floor(fx / a.ml) * a.ml), 0), a.ml - 1));
         box.oy = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(fy - floor(fy / a.mm) * a.mm), 0), a.mm - 1));
       } else {
+        ch.rows = nt;
         vt = fmaxf(fabsf(__shfl(x, 62)), fabsf(__shfl(y, 62))) / max(1, nt - 1);
       }
       ch.rows = __builtin_amdgcn_readfirstlane(ch.rows);

@@ -199,3 +199,19 @@ def test_spans(pk):
         e, b = float(np.max(np.abs(P - ref / peak))), 2 * _bound("split_bf16", obs, D) / abs(peak)
         print(f"K={obs.K}, {n_ant} antennas: {e / b:.2f} of the bound", flush=True)
         assert e <= b
+
+
+@pytest.mark.parametrize("n_t,n_ch,dt", [(60, 2, 600.0), (1500, 2, 25.0), (30, 64, 900.0)])
+def test_sparse_tracks(pk, n_t, n_ch, dt):
+    """Long baselines over a wide band in long steps: tracks that leave a tile
+    within a few bins, so that windows are folded into the grid itself, and
+    ones that do so in part."""
+    obs = ps.tiny_random(5, n_ant=30 if n_t < 100 else 9, n_t=n_t, n_ch=n_ch, nt=1, nc=1, radius_m=6000.0, dt=dt, nu_lo=0.9e9, nu_hi=1.7e9)
+    assert obs.K >= 24576
+    src = _src(140, 129)
+    D = orc.decorr(obs, src.l0, src.m0)
+    ref = orc.patch_factored(obs, src, D)
+    P = pk.patch(pk.DeviceObservation(obs), src, prec="fp32").double().cpu().numpy()
+    e, b = float(np.max(np.abs(P - ref))), _bound("fp32", obs, D)
+    print(f"K={obs.K}: {e / b:.2f} of the bound", flush=True)
+    assert e <= b
