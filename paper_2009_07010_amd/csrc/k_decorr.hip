@@ -49,7 +49,11 @@ namespace {
 // baseline-dependent bins of 1-8 channels); two channels re-read each
 // time row too often (0.196 ms).
 constexpr int kChanChunk = 4;
-constexpr int kEvenBin = 8;  // channels from which the even form pays (12 with windows)
+// Channels from which the even form pays: it is level with the other at 8 (10
+// x 8 samples, K = 1.5M: 74 us either way, with windows 108 against 88), but
+// slower there where few long bins wait for their chains (64 x 8 among smaller
+// ones: 65 against 44 us).
+constexpr int kEvenBin = 12;
 
 // Sums over one bin's samples: S = sum x e with e = exp(-2 pi i phi) and x
 // the sample's window weight (1 without windows), the window sums of the bin
@@ -237,14 +241,14 @@ __device__ __forceinline__ BinSums even_sums(const ObsView& o, const BinRef& r, 
 }
 
 // The sums by whichever of the two is the faster: a row costs the recurrence
-// as much as 8 samples by bin_sums, or 12 with windows.
+// as much as 8 to 12 samples by bin_sums.
 template <bool kWin>
 __device__ __forceinline__ BinSums wide_sums(const ObsView& o, const BinRef& r, double l0, double m0, double Lw,
                                              double A_k, double nu_k, double uc, double vc, double wc, double l0_n0,
                                              double m0_n0) {
   const int nc = r.c1 - r.c0;
-  const double h = nc >= (kWin ? 12 : kEvenBin) && r.t1 - r.t0 > 1 ? even_half_step(o.freq, r.c0, r.c1, nu_k)
-                                                                  : __builtin_nan("");
+  const double h =
+      nc >= kEvenBin && r.t1 - r.t0 > 1 ? even_half_step(o.freq, r.c0, r.c1, nu_k) : __builtin_nan("");
   if (h == h) {
     if (kWin && nc <= 20) return even_sums<kWin, 20>(o, r, l0, m0, Lw, A_k, nu_k, h);
     return even_sums<kWin, 40>(o, r, l0, m0, Lw, A_k, nu_k, h);

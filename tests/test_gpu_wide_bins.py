@@ -158,8 +158,7 @@ def test_long_bins_decorr_patch_and_gradient(pk, windowed, uneven):
 @pytest.mark.parametrize("nc", [7, 8, 11, 12, 20, 21, 40, 41])
 def test_many_channels(pk, nc, window):
     """Bins of many channels, one lane each: evenly spaced channels are summed
-    by a recurrence (boxcar from 8 channels, windows from 12, 20 or 40 at a
-    time), unevenly spaced ones one by one; last bins of one channel and of
+    by a recurrence (from 12 channels, with windows 20 or 40 at a time), unevenly spaced ones one by one; last bins of one channel and of
     one time.  Bound: the factors of a row or sample are good to 1e-6 and a
     sum of n terms in FP32 to n / 2 roundings."""
     import dataclasses
@@ -174,7 +173,7 @@ def test_many_channels(pk, nc, window):
             f[1::3] += 0.2 * (f[1] - f[0])
             obs = dataclasses.replace(obs, freq_hz=f)
         D = pk.decorr(pk.DeviceObservation(obs), l0, m0).cpu().numpy()
-        rows = not uneven and nc >= (12 if window else 8)
+        rows = not uneven and nc >= 12
         e, b = float(np.max(np.abs(D - orc.decorr(obs, l0, m0)))), 1e-6 + 6e-8 / 2 * 16 * (1 if rows else nc)
         print(f"nc {nc} window {window} uneven {uneven}: {e:.2e}, bound {b:.1e}", flush=True)
         assert e <= b
