@@ -8,22 +8,25 @@ per-baseline bins of floor(B_max/|b|) clamped to 1-64 samples x 1-8
 channels: K = 265,127,960 averaged visibilities) with 256 sources at
 0.05-3 deg whose patches are 65, 129 or 257 pixels square at 1.5".  One
 step = one replay of a captured HIP graph holding one psf_patch_batched
-call over 16 of the sources (decorrelation, phase factors, contraction
-and finalise of each); steps cycle through the 16 slices, so 16 steps
+call over 16 of the sources (decorrelation factors, spreading onto a uv
+grid and transform of each); steps cycle through the 16 slices, so 16 steps
 cover all 256 sources.  The value is vis.pixel terms/s (K x nl x nm
 one-sided terms per PSF) over the timed steps, in the stochastic FP16
-arithmetic (rows and columns one stochastically rounded FP16 value each:
-one matrix-core product per term product), whose error against the FP64
+arithmetic (a bin's row and column taps one stochastically rounded FP16
+value each: one matrix-core product per tap product), whose error against the FP64
 oracle at the stored pixels is part of the line.
+
+Every workload here has bins enough for the gridded form, whose work is
+per bin and not per term: terms count what a direct evaluation would do.
 
 Also printed, as keyed sub-entries: the headline in split-BF16 (three
 products); one PSF of the uniform-bin workload (K = 5.8M, 257^2) in the
 headline arithmetic, split-BF16 and plain FP32; the precision workload
 (K = 23.2M, 64 sources of 257^2) in split-BF16, split-FP16, mixed-FP16
 (rows stochastically rounded, columns split: two products), stochastic-FP16
-and FP32; the
-roofline of the contraction kernel from HIP events on its launch stream;
-the paper's two approximations, CLEAN, windows, exact w, the adjoint; and
+and FP32; the roofline of the gridded kernels from HIP events on their launch
+stream (the bytes they cannot do without over the HBM peak; vector issue
+bounds them first); the paper's two approximations, CLEAN, windows, exact w, the adjoint; and
 the FP64 CPU reference timed on a bounded sample of the headline workload.
 """
 import argparse
@@ -35,16 +38,7 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"split_bf16": 2516.6, "split_fp16": 2516.6, "mixed_fp16": 2516.6, "sr_fp16": 2516.6,
-               "plain_bf16": 2516.6, "fp32": 157.3}
-# algorithmic work per useful one-sided term: 2 real multiply-adds
-# (Re c a Re b - Im c a Im b), 4 flops, whatever the arithmetic
-ALG_FLOPS_PER_TERM = 4.0
-# matrix-core products per term product: 3 for the split forms (hi hi, hi lo, lo hi),
-# 2 for the mixed form (rows once, columns hi and lo), 1 for the stochastic form
-# (the last two for the symmetric form and K >= 2^18, else they run split-FP16)
-PRODUCTS = {"split_bf16": 3, "split_fp16": 3, "mixed_fp16": 2, "sr_fp16": 1, "plain_bf16": 1, "fp32": 1}
-MIXED_MIN_K = 1 << 18
+HBM_PEAK_GBPS = 8000.0
 DTYPE = {"split_bf16": "bf16", "split_fp16": "fp16", "mixed_fp16": "fp16", "sr_fp16": "fp16", "plain_bf16": "bf16",
          "fp32": "f32"}
 
@@ -54,7 +48,7 @@ def parse():
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=20)
     ap.add_argument("--warmup", type=int, default=5)
-    ap.add_argument("--prec", default="sr_fp16", choices=list(PEAK_TFLOPS))
+    ap.add_argument("--prec", default="sr_fp16", choices=list(DTYPE))
     ap.add_argument("--seed", type=int, default=0)
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-baselines", type=int, default=72,
@@ -73,15 +67,15 @@ def parse():
     return ap.parse_args()
 
 
-KERNEL_SRC = os.path.join(ROOT, "paper_2009_07010_amd", "csrc", "k_patch.hip")
+KERNEL_SRC = os.path.join(ROOT, "paper_2009_07010_amd", "csrc", "k_grid.hip")
 
 
 def measured_traffic(prec, workload="meerkat257"):
-    """HBM bytes per contraction launch from the committed counter summary
+    """HBM bytes per patch of the spreading kernel from the committed counter summary
     of this workload and precision, or None when there is none or the kernel
     source has changed since the counters were taken."""
     import hashlib
-    path = os.path.join(ROOT, "profiles", f"k_patch_traffic_{workload}_{prec}.txt")
+    path = os.path.join(ROOT, "profiles", f"k_grid_traffic_{workload}_{prec}.txt")
     try:
         kv = {}
         with open(path) as f:
@@ -93,7 +87,7 @@ def measured_traffic(prec, workload="meerkat257"):
             sha = hashlib.sha256(f.read()).hexdigest()
         if kv.get("source_sha256") != sha or kv.get("precision") != prec:
             return None
-        return float(kv["traffic_bytes_per_launch"])
+        return float(kv["traffic_bytes_per_patch"])
     except (OSError, KeyError, ValueError):
         return None
 
@@ -168,7 +162,7 @@ def time_windows_fullw(pk, torch, ps, obs, dobs, src, prec, ws, reps=5):
     del dw
     out = torch.empty((src.nl, src.nm), dtype=torch.float32, device="cuda")
     n_terms = pk.patch_fullw(dobs, src, prec=prec, out=out, workspace=ws)[1]
-    torch.cuda.synchronize()  # the warm-up's contractions are still queued when it returns
+    torch.cuda.synchronize()  # the warm-up's patches are still queued when it returns
     t0 = time.perf_counter()
     for _ in range(reps):
         pk.patch_fullw(dobs, src, prec=prec, out=out, workspace=ws)
@@ -310,9 +304,9 @@ def golden_pixels(names):
 def headline_bda(pk, torch, ps, obs, srcs, prec, steps, warmup, ws, per_slice=16):
     """One graph per 16-source slice of the headline workload, each holding
     one psf_patch_batched call; `steps` replays cycling through the slices
-    are timed.  Returns the line's timing fields, the roofline of the
-    contraction kernel from an eager pass over every slice with HIP events
-    on its launch stream, and the error of the timed output at the stored
+    are timed.  Returns the line's timing fields, the gridded kernels' time
+    from an eager pass over every slice with HIP events on their launch
+    stream, and the error of the timed output at the stored
     oracle pixels."""
     import numpy as np
     dobs = pk.DeviceObservation(obs)
@@ -358,7 +352,7 @@ def headline_bda(pk, torch, ps, obs, srcs, prec, steps, warmup, ws, per_slice=16
             continue
         P = pk.split_patches(outs[q], slices[q])[r].cpu().numpy().astype(np.float64)
         errs[str(i)] = float(np.max(np.abs(P[ii, jj] - ref)) / abs(peak))
-    # the contraction kernel's launches, timed with events on its stream
+    # the gridded kernels' launches, timed with events on their stream
     pk.psf_timing_read()
     pk.psf_timing_enable(True)
     t1 = time.perf_counter()
@@ -379,43 +373,24 @@ def headline_bda(pk, torch, ps, obs, srcs, prec, steps, warmup, ws, per_slice=16
                                              for n in sorted({s.nl for s in srcs})}}
 
 
-SYM_SIZES = {(257, 17), (129, 9), (65, 5)}  # (rows, column blocks) with the symmetric form
+def compulsory_bytes(obs, srcs):
+    """Bytes the gridded form of these patches cannot do without, each patch
+    on its own: the sample and bin-centre uvw, the weights and the patch."""
+    per_source = 24.0 * obs.n_bl * obs.n_t + 24.0 * len(obs.uvw_c_m) + 4.0 * obs.K + 8.0 * obs.n_ch
+    return sum(per_source + 4.0 * s.nl * s.nm for s in srcs)
 
 
-def executed_flops(K, srcs, prec):
-    """Matrix-core flops the contraction executes for these patches: per
-    visibility (16 nbi) x (16 nbj) multiply-adds over one real inner value in
-    the symmetric form (C and S rows of 16-row blocks), two (re, im) in the
-    general form, times the split products."""
-    tot = 0.0
-    for s in srcs:
-        nbi, nbj = (s.nl + 15) // 16, (s.nm + 15) // 16
-        sym = (s.nl, nbj) in SYM_SIZES
-        inner = 1 if sym else 2
-        prods = PRODUCTS[prec]
-        if prec in ("mixed_fp16", "sr_fp16") and not (sym and K >= MIXED_MIN_K):
-            prods = PRODUCTS["split_fp16"]
-        tot += float(K) * inner * (16 * nbi) * (16 * nbj) * 2.0 * prods
-    return tot
-
-
-def roofline(prec, terms, kernel_ms, launches, traffic=None, kernel="k_patch", exec_flops=None):
-    """Useful matrix-core work (4 flops per term) per launch over the
-    kernel's average launch time, against the dense peak of its arithmetic;
-    the executed work (split products, the symmetric form and tile padding
-    counted) beside it."""
-    per_launch_ms = kernel_ms / max(launches, 1)
-    per_launch_flops = ALG_FLOPS_PER_TERM * terms / max(launches, 1)
-    achieved = per_launch_flops / (per_launch_ms * 1e-3) / 1e12
-    peak = PEAK_TFLOPS[prec]
-    out = {"bound": "mfma", "kernel": f"{kernel}<{prec}>", "achieved": achieved, "peak": peak,
-           "unit": "TFLOP/s", "frac": achieved / peak, "traffic": traffic,
-           "kernel_ms": per_launch_ms, "launches": launches,
-           "per_unit": f"{ALG_FLOPS_PER_TERM:g} flops per useful one-sided term (2 real multiply-adds), "
-                       f"{terms / max(launches, 1):.4g} terms per launch on average"}
-    if exec_flops is not None:
-        out["frac_executed"] = exec_flops / max(launches, 1) / (per_launch_ms * 1e-3) / 1e12 / peak
-    return out
+def roofline(prec, obs, srcs, kernel_ms, launches, traffic=None):
+    """Compulsory bytes of these patches over the kernels' time, against the
+    HBM peak.  Not the nearest bound: the spreading kernel is held by vector
+    issue (taps, operand conversions, the samples' factors), LDS and latency.
+    traffic: HBM bytes of the spreading kernel per patch, from counters."""
+    achieved = compulsory_bytes(obs, srcs) / (kernel_ms * 1e-3) / 1e9
+    kernel = "k_patch" if prec == "plain_bf16" else "k_grid_spread"
+    return {"bound": "hbm", "kernel": f"{kernel}<{prec}>", "achieved": achieved, "peak": HBM_PEAK_GBPS,
+            "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS, "traffic": traffic, "kernel_ms": kernel_ms / max(launches, 1),
+            "launches": launches, "bins_per_s": float(obs.K) * len(srcs) / (kernel_ms * 1e-3),
+            "per_unit": f"compulsory bytes of {len(srcs)} patches, {compulsory_bytes(obs, srcs) / len(srcs):.4g} each"}
 
 
 def precision_workload(pk, torch, ps, ws, seed=0):
@@ -445,8 +420,7 @@ def precision_workload(pk, torch, ps, ws, seed=0):
         err = max((float(np.max(np.abs(parts[i].cpu().numpy().astype(np.float64)[ii, jj] - ref)) / abs(peak))
                    for i, (ii, jj, ref, peak) in gold.items()), default=None)
         out[prec] = {"s": dt, "terms_per_s": terms / dt, "psfs_per_s": len(srcs) / dt,
-                     "contraction_tflops_useful": ALG_FLOPS_PER_TERM * terms / (kms * 1e-3) / 1e12,
-                     "frac_useful": ALG_FLOPS_PER_TERM * terms / (kms * 1e-3) / 1e12 / PEAK_TFLOPS[prec],
+                     "bins_per_s": float(obs.K) * len(srcs) / (kms * 1e-3),
                      "max_err_at_oracle_pixels": err}
     out["split_bf16_over_fp32"] = out["fp32"]["s"] / out["split_bf16"]["s"]
     del dobs
@@ -532,11 +506,8 @@ def main():
             for _ in range(a.profile_steps):
                 pk.patch_backward(dobs, srcs, G, a.prec, workspace=ws)
         elif a.profile_workload.startswith("decorr"):
-            # the decorrelation as the patch path runs it (factors, records and
-            # W D written per bin), here ahead of a small 65 x 65 contraction
-            small = ps.Source.centred(src.l0, src.m0, 65, src.dl)
             for _ in range(a.profile_steps):
-                pk.patch(dobs, small, prec=a.prec, workspace=ws)
+                pk.decorr(dobs, src.l0, src.m0)
         else:
             for _ in range(a.profile_steps):
                 pk.patch(dobs, src, prec=a.prec, workspace=ws)
@@ -553,8 +524,7 @@ def main():
         return
     print("timing the headline workload", file=sys.stderr, flush=True)
     h = headline_bda(pk, torch, ps, obs5, srcs5, a.prec, a.steps, a.warmup, ws)
-    rf = roofline(a.prec, h["all_terms"], h["kernel_ms_total"], h["kernel_launches"],
-                  measured_traffic(a.prec, "bda256"), exec_flops=executed_flops(obs5.K, srcs5, a.prec))
+    rf = roofline(a.prec, obs5, srcs5, h["kernel_ms_total"], h["kernel_launches"], measured_traffic(a.prec, "bda256"))
     line = {
         "metric": "PSF vis·pixel terms/s at ≤1e-5 rel err vs FP64; PSFs/s, split-BF16 vs FP32",
         "value": h["terms_per_s"],
@@ -587,9 +557,8 @@ def main():
             "ms_per_step": hb["ms_per_step"], "terms_per_s": hb["terms_per_s"], "psfs_per_s": hb["psfs_per_s"],
             "steps": 16, "warmup": 2, "max_rel_err_vs_fp64": max(hb["errors"].values()) if hb["errors"] else None,
             "errors_at_oracle_pixels": hb["errors"],
-            "roofline": roofline("split_bf16", hb["all_terms"], hb["kernel_ms_total"], hb["kernel_launches"],
-                                 measured_traffic("split_bf16", "bda256"),
-                                 exec_flops=executed_flops(obs5.K, srcs5, "split_bf16"))}
+            "roofline": roofline("split_bf16", obs5, srcs5, hb["kernel_ms_total"], hb["kernel_launches"],
+                                 measured_traffic("split_bf16", "bda256"))}
     print("uniform-bin workload", file=sys.stderr, flush=True)
     obs = ps.observation(2, seed=a.seed)
     src = ps.sources(2, seed=a.seed)[0]
@@ -602,14 +571,11 @@ def main():
         "workload": "64 antennas (2016 baselines), 3600 x 2 s, 32 ch over 1.3-1.5 GHz, 20 s x 4 ch bins "
                     "(K=5,806,080), 1 source at 1 deg, 257x257 at 1.5 arcsec, one psf_patch call per PSF",
         "K": obs.K, "terms_per_s": terms / (ms * 1e-3), "ms_per_psf": ms, "psfs_per_s": 1e3 / ms,
-        "roofline": roofline(a.prec, float(terms), kms, 1, measured_traffic(a.prec),
-                             exec_flops=executed_flops(obs.K, [src], a.prec)),
+        "roofline": roofline(a.prec, obs, [src], kms, 1, measured_traffic(a.prec)),
         "fp32": {"ms_per_psf": ms32, "terms_per_s": terms / (ms32 * 1e-3),
-                 "roofline": roofline("fp32", float(terms), kms32, 1,
-                                      exec_flops=executed_flops(obs.K, [src], "fp32"))},
+                 "roofline": roofline("fp32", obs, [src], kms32, 1)},
         "split_bf16": {"ms_per_psf": msb, "terms_per_s": terms / (msb * 1e-3),
-                       "roofline": roofline("split_bf16", float(terms), kmsb, 1, measured_traffic("split_bf16"),
-                                            exec_flops=executed_flops(obs.K, [src], "split_bf16"))}}
+                       "roofline": roofline("split_bf16", obs, [src], kmsb, 1, measured_traffic("split_bf16"))}}
     print("extras", file=sys.stderr, flush=True)
     line["method1"] = time_method1(pk, torch, dobs, src, a.prec, ws)
     line["clean"] = time_clean(pk, torch, ps, dobs, src, a.prec, ws)
