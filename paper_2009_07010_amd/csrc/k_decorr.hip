@@ -143,31 +143,6 @@ __device__ __forceinline__ BinSums bin_sums(const ObsView& o, const BinRef& r, d
   return s;
 }
 
-// cos and sin of 2 pi theta (theta in turns) in FP64, to about 1e-9: the
-// Taylor series of one half turn through x^14 and x^13.
-__device__ __forceinline__ void cos_sin_turns(double theta, double* c, double* s) {
-  const double q = rint(2.0 * theta);
-  const double x = fma(-0.5, q, theta) * 6.283185307179586;
-  const double x2 = x * x;
-  double p = 1.0 / 6227020800.0, r = -1.0 / 87178291200.0;
-  p = fma(p, x2, -1.0 / 39916800.0);
-  r = fma(r, x2, 1.0 / 479001600.0);
-  p = fma(p, x2, 1.0 / 362880.0);
-  r = fma(r, x2, -1.0 / 3628800.0);
-  p = fma(p, x2, -1.0 / 5040.0);
-  r = fma(r, x2, 1.0 / 40320.0);
-  p = fma(p, x2, 1.0 / 120.0);
-  r = fma(r, x2, -1.0 / 720.0);
-  p = fma(p, x2, -1.0 / 6.0);
-  r = fma(r, x2, 1.0 / 24.0);
-  r = fma(r, x2, -0.5);
-  r = fma(r, x2, 1.0);
-  p = fma(p * x2, x, x);
-  const bool odd = (static_cast<int>(q) & 1) != 0;
-  *c = odd ? -r : r;
-  *s = odd ? -p : p;
-}
-
 // The sums of bin_sums (no derivatives) for a bin of evenly spaced channels
 // (half spacing h, in s/m): the channels of a time row are a polynomial in
 // z = exp(-4 pi i A_t h) with the channel windows as coefficients, times the

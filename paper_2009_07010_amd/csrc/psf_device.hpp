@@ -85,6 +85,31 @@ __device__ __forceinline__ cf32 expi_half_turns(double theta) {
           __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, s) ^ odd)};
 }
 
+// cos and sin of 2 pi theta (theta in turns) in FP64, to about 1e-9: the
+// Taylor series of one half turn through x^14 and x^13.
+__device__ __forceinline__ void cos_sin_turns(double theta, double* c, double* s) {
+  const double q = rint(2.0 * theta);
+  const double x = fma(-0.5, q, theta) * 6.283185307179586;
+  const double x2 = x * x;
+  double p = 1.0 / 6227020800.0, r = -1.0 / 87178291200.0;
+  p = fma(p, x2, -1.0 / 39916800.0);
+  r = fma(r, x2, 1.0 / 479001600.0);
+  p = fma(p, x2, 1.0 / 362880.0);
+  r = fma(r, x2, -1.0 / 3628800.0);
+  p = fma(p, x2, -1.0 / 5040.0);
+  r = fma(r, x2, 1.0 / 40320.0);
+  p = fma(p, x2, 1.0 / 120.0);
+  r = fma(r, x2, -1.0 / 720.0);
+  p = fma(p, x2, -1.0 / 6.0);
+  r = fma(r, x2, 1.0 / 24.0);
+  r = fma(r, x2, -0.5);
+  r = fma(r, x2, 1.0);
+  p = fma(p * x2, x, x);
+  const bool odd = (static_cast<int>(q) & 1) != 0;
+  *c = odd ? -r : r;
+  *s = odd ? -p : p;
+}
+
 // Index of the baseline that owns bin k: largest b with koff[b] <= k.  The
 // wave's first active lane is searched for by bisection in uniform control
 // flow (scalar loads, no dependent vector loads); every lane then steps from

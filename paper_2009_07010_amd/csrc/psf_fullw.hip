@@ -21,6 +21,7 @@
 // kTruncation (1e-7 of the coefficient sum, below the contraction's own
 // rounding); Y is limited to kMaxY so that the terms (together up to e^Y of
 // the patch) do not amplify the contraction's rounding past 1e-5.
+#include <algorithm>
 #include <cmath>
 
 #include "psf_device.hpp"
@@ -81,39 +82,46 @@ __global__ __launch_bounds__(256) void k_wmax_final(const double* __restrict__ p
   if (threadIdx.x == 0) out[0] = w * f * kInvCLight;
 }
 
-// Per bin: z_k = w_k / s and c~_k = c_k exp(i z_k ybar) (FP64 phase).
-__global__ __launch_bounds__(256) void k_fullw_prep(ObsView o, const float2* __restrict__ c, double inv_s,
-                                                    double ybar, float2* __restrict__ ct, float* __restrict__ z) {
+// Orders of the expansion per gridded launch, each a source of it: four small
+// kernels and one coefficient kernel per launch instead of per order (129 x
+// 129, K = 2.9M, four orders: 647 -> 509 us with the coefficients formed from
+// c in one kernel).  One order at a time where their coefficients would take
+// more than 1 GiB, and in the dense form.
+constexpr int kOrders = 4;
+
+struct Scales {
+  float s[kOrders];
+};
+
+// c^(r)_k = c_k exp(i z_k ybar) (i z_k)^r Y^r / r!, z_k = w_k / s (phase in
+// FP64), for n orders from r0 on; order r0 + q to out + q K.
+__global__ __launch_bounds__(256) void k_fullw_coef(ObsView o, const float2* __restrict__ c, double inv_s, double ybar,
+                                                    int r0, int n, Scales scale, float2* __restrict__ out) {
   const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (k >= o.K) return;
-  const BinRef r = locate_bin(o.koff, o.tboff, o.bl_bin, o.n_bl, o.n_t, o.n_ch, k);
-  const double w = o.uvw_c[3 * r.tb + 2] * bin_freq(o.freq, r.c0, r.c1) * kInvCLight;
-  const double zk = w * inv_s;
-  double sn, cs;
-  sincos(zk * ybar, &sn, &cs);
+  const BinRef b = locate_bin(o.koff, o.tboff, o.bl_bin, o.n_bl, o.n_t, o.n_ch, k);
+  const double w = o.uvw_c[3 * b.tb + 2] * bin_freq(o.freq, b.c0, b.c1) * kInvCLight;
+  const double zd = w * inv_s;
+  double cs, sn;
+  cos_sin_turns(zd * ybar * (0.5 / M_PI), &cs, &sn);
   const float2 ck = c[k];
-  const float cr = static_cast<float>(cs), ci = static_cast<float>(sn);
-  ct[k] = make_float2(ck.x * cr - ck.y * ci, ck.x * ci + ck.y * cr);
-  z[k] = static_cast<float>(zk);
-}
-
-// c^(r)_k = c~_k (i z_k)^r scale, scale = Y^r / r!
-__global__ __launch_bounds__(256) void k_fullw_coef(const float2* __restrict__ ct, const float* __restrict__ z,
-                                                    int64_t K, int r, float scale, float2* __restrict__ out) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  float p = scale;
-  const float zk = z[k];
-  for (int q = 0; q < r; ++q) p *= zk;
-  const float2 a = ct[k];
-  float2 v;
-  switch (r & 3) {
-    case 0: v = make_float2(a.x, a.y); break;
-    case 1: v = make_float2(-a.y, a.x); break;
-    case 2: v = make_float2(-a.x, -a.y); break;
-    default: v = make_float2(a.y, -a.x); break;
+  const float cr = static_cast<float>(cs), ci = static_cast<float>(sn), zk = static_cast<float>(zd);
+  const float2 a = make_float2(ck.x * cr - ck.y * ci, ck.x * ci + ck.y * cr);
+#pragma unroll
+  for (int q = 0; q < kOrders; ++q) {
+    if (q >= n) break;
+    const int r = r0 + q;
+    float p = scale.s[q];
+    for (int t = 0; t < r; ++t) p *= zk;
+    float2 v;
+    switch (r & 3) {
+      case 0: v = make_float2(a.x, a.y); break;
+      case 1: v = make_float2(-a.y, a.x); break;
+      case 2: v = make_float2(-a.x, -a.y); break;
+      default: v = make_float2(a.y, -a.x); break;
+    }
+    out[q * o.K + k] = make_float2(v.x * p, v.y * p);
   }
-  out[k] = make_float2(v.x * p, v.y * p);
 }
 
 struct GridArgs {
@@ -131,36 +139,40 @@ __host__ __device__ inline double q_of(double l0, double m0, double n0, double x
   return dn + (l0 * x + m0 * y) / n0;
 }
 
-// out (+)= (delta_ij / Y)^r P^(r)_ij
-__global__ __launch_bounds__(256) void k_fullw_accum(GridArgs g, int r, const float* __restrict__ Pr,
+// out (+)= sum over the n orders from r0 on of (delta_ij / Y)^r P^(r)_ij
+// (order r0 + q at Pr + q pixels; r0 = 0 starts the sum)
+__global__ __launch_bounds__(256) void k_fullw_accum(GridArgs g, int r0, int n, const float* __restrict__ Pr,
                                                      float* __restrict__ out) {
-  const int64_t n = static_cast<int64_t>(g.nl) * g.nm;
+  const int64_t pixels = static_cast<int64_t>(g.nl) * g.nm;
   const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  if (r == 0) {
-    out[p] = Pr[p];
-    return;
-  }
+  if (p >= pixels) return;
   const int i = static_cast<int>(p / g.nm), j = static_cast<int>(p - static_cast<int64_t>(i) * g.nm);
   const double x = (g.l_first + i * g.dl) - g.l0, y = (g.m_first + j * g.dm) - g.m0;
   const double d = (g.two_pi_s * q_of(g.l0, g.m0, g.n0, x, y) - g.ybar) * g.inv_Y;
+  float sum = r0 == 0 ? 0.f : out[p];
   double dr = 1.0;
-  for (int q = 0; q < r; ++q) dr *= d;
-  out[p] += static_cast<float>(dr) * Pr[p];
+  for (int q = 0; q < r0; ++q) dr *= d;
+  for (int q = 0; q < n; ++q, dr *= d) {
+    const float v = Pr[q * pixels + p];
+    sum = r0 + q == 0 ? v : sum + static_cast<float>(dr) * v;
+  }
+  out[p] = sum;
 }
 
 struct FullwLayout {
-  size_t ct, z, cr, Pr, s, total;
+  int orders;  // per launch
+  size_t cr, Pr, grids, grid, s, total;
 };
 
 FullwLayout fullw_layout(const psf_obs* o, const psf_src* src, const PatchPlan& plan) {
   FullwLayout L;
   const size_t K = static_cast<size_t>(o->K);
-  L.ct = align_up(patch_workspace(o, plan), 256);
-  L.z = L.ct + align_up(K * sizeof(float2), 256);
-  L.cr = L.z + align_up(K * sizeof(float), 256);
-  L.Pr = L.cr + align_up(K * sizeof(float2), 256);
-  L.s = L.Pr + align_up(static_cast<size_t>(src->nl) * src->nm * sizeof(float), 256);
+  L.orders = plan.grid.ml > 0 && K * sizeof(float2) * kOrders <= (size_t(1) << 30) ? kOrders : 1;
+  L.cr = align_up(patch_workspace(o, plan), 256);
+  L.Pr = L.cr + align_up(L.orders * K * sizeof(float2), 256);
+  L.grids = L.Pr + align_up(L.orders * static_cast<size_t>(src->nl) * src->nm * sizeof(float), 256);
+  L.grid = plan.grid.ml > 0 ? align_up(grid_bytes(plan.grid, src->nm), 256) : 0;
+  L.s = L.grids + (L.orders - 1) * L.grid;
   L.total = L.s + align_up((2 * kWmaxBlocks + 1) * sizeof(double), 256);
   return L;
 }
@@ -219,8 +231,6 @@ int psf_patch_fullw(const psf_obs* obs, const psf_src* h_src, int prec, float* P
   float2* c = reinterpret_cast<float2*>(w + align_up(static_cast<size_t>(obs->K) * sizeof(BinRec), 256));
   float* partial = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(c) +
                                             align_up(static_cast<size_t>(obs->K) * sizeof(float2), 256));
-  float2* ct = reinterpret_cast<float2*>(w + L.ct);
-  float* z = reinterpret_cast<float*>(w + L.z);
   float2* cr = reinterpret_cast<float2*>(w + L.cr);
   float* Pr = reinterpret_cast<float*>(w + L.Pr);
   double* d_s = reinterpret_cast<double*>(w + L.s);
@@ -255,8 +265,6 @@ int psf_patch_fullw(const psf_obs* obs, const psf_src* h_src, int prec, float* P
   if (obs->K == 0 || smax == 0.0 || R == 0) return contract(obs, h_src, plan, prec, rec, c, partial, P, s);
 
   const unsigned kb = static_cast<unsigned>((obs->K + 255) / 256);
-  hipLaunchKernelGGL(k_fullw_prep, dim3(kb), dim3(256), 0, s, view(obs), c, 1.0 / smax, ybar, ct, z);
-  if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_fullw_prep launch");
   GridArgs g;
   g.l_first = h_src->l_first;
   g.m_first = h_src->m_first;
@@ -273,12 +281,26 @@ int psf_patch_fullw(const psf_obs* obs, const psf_src* h_src, int prec, float* P
   const int64_t npix = static_cast<int64_t>(h_src->nl) * h_src->nm;
   const unsigned pb = static_cast<unsigned>((npix + 255) / 256);
   double scale = 1.0;  // Y^r / r!
-  for (int r = 0; r <= R; ++r) {
-    if (r > 0) scale *= Y / r;
-    hipLaunchKernelGGL(k_fullw_coef, dim3(kb), dim3(256), 0, s, ct, z, obs->K, r, static_cast<float>(scale), cr);
+  for (int r0 = 0; r0 <= R; r0 += L.orders) {
+    const int n = std::min(L.orders, R + 1 - r0);
+    Scales sc{};
+    for (int q = 0; q < n; ++q) {
+      if (r0 + q > 0) scale *= Y / (r0 + q);
+      sc.s[q] = static_cast<float>(scale);
+    }
+    hipLaunchKernelGGL(k_fullw_coef, dim3(kb), dim3(256), 0, s, view(obs), c, 1.0 / smax, ybar, r0, n, sc, cr);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_fullw_coef launch");
-    if ((st = contract(obs, h_src, plan, prec, rec, cr, partial, Pr, s)) != PSF_OK) return st;
-    hipLaunchKernelGGL(k_fullw_accum, dim3(pb), dim3(256), 0, s, g, r, Pr, P);
+    if (plan.grid.ml > 0) {
+      UvGridArgs ga = grid_args(obs, plan.grid, false);
+      ga.n_src = n;
+      for (int q = 0; q < n; ++q)
+        ga.src[q] = grid_src(h_src, rec, cr + q * obs->K,
+                             q == 0 ? static_cast<void*>(partial) : w + L.grids + (q - 1) * L.grid, Pr + q * npix, nullptr);
+      if ((st = run_grid(launch_prec(prec, obs->K, plan.sym), ga, s)) != PSF_OK) return st;
+    } else if ((st = contract(obs, h_src, plan, prec, rec, cr, partial, Pr, s)) != PSF_OK) {
+      return st;
+    }
+    hipLaunchKernelGGL(k_fullw_accum, dim3(pb), dim3(256), 0, s, g, r0, n, Pr, P);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "k_fullw_accum launch");
   }
   return PSF_OK;
