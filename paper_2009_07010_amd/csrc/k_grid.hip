@@ -1207,13 +1207,16 @@ hipError_t launch_grid(int prec, UvGridArgs a, hipStream_t stream) {
   while (a.log_tile < 14 && (1 << a.log_tile) < a.o.n_ch) ++a.log_tile;
   // As many workgroups as the chip runs at once (three per compute unit); with
   // fewer than 768 bins each, workgroups of 512 (two rounds of 64 bins per
-  // wave) instead, the last of which follow the first that are done.  One span each below 8192 bins per workgroup (K =
+  // wave) instead, the last of which follow the first that are done, or of 256
+  // while those leave compute units idle (K = 26k to 76k: 48-50 -> 39-43 us
+  // for 33 to 129 pixels; with 128 bins 39-46).  One span each below 8192 bins per workgroup (K =
   // 5.9M of uneven bins: 195 us against 229 with three levels; six patches of
   // K = 1.45M 1258 against 1356), from there on as many levels as leave the
   // last at least 1024 bins (K = 23.2M, three sources: 1846 us with six levels,
   // 1918 with five, 2150 with one).
   const int resident = 768 / a.n_src;
-  a.n_wg = K / resident < 768 ? static_cast<int>((K + 511) / 512) : resident;
+  const int least = K * a.n_src < 512 * 256 ? 256 : 512;
+  a.n_wg = K / resident < 768 ? static_cast<int>((K + least - 1) / least) : resident;
   a.levels = 1;
   if (K / a.n_wg >= 8 * kLeastSpan)
     while (a.levels < kGridMaxLevels && K / a.n_wg >= int64_t(kLeastSpan) << a.levels) ++a.levels;

@@ -185,10 +185,10 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
 // bins of 3 x 4 samples, split-BF16; patch_work at 256 CUs and 2.1 GHz follows
 // the dense form within 40%):
 //   pixels        33        65       129       200       257       300
-//   K =  27k   30 | 48   26 | 48   34 | 49   48 | 56   47 | 56   76 | 77   dense | gridded
-//   K =  51k   34 | 41   29 | 40   40 | 43   70 | 48   57 | 50  123 | 70
-//   K = 152k   57 | 45   42 | 45   56 | 46  166 | 53   90 | 54  327 | 73
-//   K = 302k   93 | 52   52 | 52   77 | 53  304 | 59  150 | 58  623 | 76
+//   K =  27k   30 | 39   26 | 38   34 | 41   48 | 46   47 | 47   76 | 67   dense | gridded
+//   K =  51k   34 | 39   29 | 39   40 | 41   70 | 45   57 | 46  123 | 67
+//   K = 152k   57 | 46   42 | 47   56 | 46  166 | 54   90 | 55  327 | 74
+//   K = 302k   93 | 53   52 | 52   77 | 53  304 | 60  150 | 59  623 | 77
 // Below 24576 bins the dense call is the shorter.  The line is drawn with 40 us
 // (60 in the symmetric families) for the dense form beside its contraction, 10
 // to 25 more than it takes, so that a patch near the line runs gridded: within
