@@ -25,8 +25,9 @@
 // the real columns share one complex transform of the second pass, which
 // writes the patch.  16 sources at N = 512: 34 us in two launches, against 176
 // us in four with one radix-2 line per workgroup (50 MB of traffic instead of
-// 250; bound now by the model's FP64 arithmetic, half of the first kernel, and
-// by the latency of passes through LDS).
+// 250; bound now by latency, of loads from other dies' caches and of passes
+// through LDS, with vector issue at 42% of the cycles of the first kernel, most
+// of it the model in FP64, and 24% of the second's).
 #include <algorithm>
 #include <cmath>
 
