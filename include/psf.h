@@ -66,10 +66,13 @@ typedef enum {
  *  - gridded, for many bins (from K = 24576 on, patches of up to 1044 pixels
  *    a side): the same sum as a non-uniform Fourier transform, each bin
  *    spread onto a uv grid with a kernel of 9 x 9 cells (products in the
- *    arithmetic below, sums in FP32 and fixed point), then FP64 transforms.
- *    Aliasing is at most 3.8e-8 of a term; measured errors are 5e-9 rms and
- *    up to 1.5e-7 of the peak, below the dense form's.  A bin whose W D or
- *    u', v' is not finite makes every pixel NaN.
+ *    arithmetic below, sums in FP32 and 64-bit fixed point), then FP64
+ *    transforms.  A bin's taps are off by at most 1.3e-7 of it per axis (5.1e-8
+ *    of that aliasing), at the patch's edges, and independently from bin to
+ *    bin: a patch is off by less than 1e-6 sum |c_k| besides the products'
+ *    own errors below, whatever the spread of the weights, and where they are
+ *    alike by 1e-8 rms and up to 1e-7 of the peak, less than the dense form.
+ *    A bin whose W D or u', v' is not finite makes every pixel NaN.
  * PSF_PLAIN_BF16 is always dense, PSF_MIXED_FP16 and PSF_SR_FP16 always
  * gridded.
  * Accuracy of the split forms: an operand value v is carried as hi + lo

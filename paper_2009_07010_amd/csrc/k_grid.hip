@@ -12,9 +12,9 @@
 // Kernel: Kaiser-Bessel of width 9 and shape parameter 2.3 x 9, as a
 // polynomial of degree 8 in the bin's offset from its cell per tap (even and
 // odd parts shared by mirrored taps).  The transform divided out is that of
-// the polynomials as coded, so only aliasing remains: at most 3.8e-8 of a
-// term over the whole patch (and 1.2e-7 with the FP32 evaluation, 2.5e-8
-// rms, which differs from bin to bin and averages out).
+// the polynomials as coded, so only aliasing remains: per axis at most 5.1e-8
+// of a term (at the patch's edges; 1.3e-7 with the FP32 evaluation, 6e-8 rms),
+// which differs from bin to bin and averages out.
 //
 //   k_grid_init    zero cells; largest |c| (scales the fixed point and the FP16
 //                  operands)
@@ -32,9 +32,11 @@
 // two windows usually hold; bins outside the current window wait for the
 // next one, so any track is spread correctly.  Windows are folded into a
 // tile of the workgroup's part of the track in LDS, tiles into the grid, in
-// fixed point: integer sums do not depend on their order, so the result is
-// the same on every run although the workgroups meet in the grid through
-// atomics.
+// 64-bit fixed point: integer sums do not depend on their order, so the result
+// is the same on every run although the workgroups meet in the grid through
+// atomics.  The unit is 2^-61 of (a power of two above) sum |c|, which bounds
+// every cell: finer than the FP32 sums of a window whatever the weights'
+// spread, so what remains is those sums' own rounding.
 //
 // FUSED, the boxcar case, forms D_k in the same kernel: bins leave no records
 // in memory (40 bytes each way, 10.6 GB per source at K = 265M).
@@ -66,10 +68,11 @@ typedef __attribute__((address_space(3))) uint8_t g_lds;
 constexpr int kW = 9;             // taps per axis
 constexpr int kWin = 16;          // cells per axis of a window
 constexpr int kSlack = kWin - kW; // a window holds anchors 0 .. kSlack past its origin
-constexpr int kTileCells = 2048;  // cells of a workgroup's LDS tile
+constexpr int kTileCells = 1024;  // cells of a workgroup's LDS tile (16 bytes each)
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kTileSide = 45;     // a tile grows to about this side when its chunk leaves room
+constexpr int kTileSide = 32;     // a tile grows to about this side when its chunk leaves room
+constexpr int kChunkBins = 1 << 14;  // bins of a chunk, at most (one row of frequency bins may be longer)
 constexpr int kTabRows = 1024;    // samples of a chunk whose projections sit in LDS
 constexpr int kTabFreq = 512;     // frequency bins whose centre frequencies do
 constexpr int kGridMaxLevels = 6, kLeastSpan = 1024;  // of spans
@@ -106,23 +109,30 @@ constexpr double kInvHat[12] = {4.05856101315633433e-01, 4.66157209092129265e-01
                                 2.61583858432692246e-03, 5.72886663654686968e-04, 1.06769820665924113e-04,
                                 2.69661860537872370e-05, 1.03610339097734577e-07, 1.69455818779958946e-06};
 
-// Cells hold c / 2^ecm (|.| <= sqrt 2) times the taps in fixed point:
-// kAccBits fractional bits in a window's accumulators (two tap scales and
-// the coefficients' own), kTileBits - log_tile in a tile of at most 2^log_tile
-// bins.
+// Windows hold c / 2^ecm times the taps in FP32, kAccBits above their value
+// (two tap scales and the coefficients' own); cells hold c in units of
+// 2^(esum - kCellBits).  2^ecm exceeds every |Re c|, |Im c|, 2^esum their sum.
 constexpr int kCoefBits = 4;
 constexpr int kAccBits = 8 + 8 + kCoefBits;
-constexpr int kTileBits = 30;
-__host__ __device__ constexpr int cell_bits(int log_k) { return 61 - log_k; }
+constexpr int kCellBits = 61;
+
+}  // namespace
+
+struct UvGridScale {
+  uint32_t maxima[kInitBlocks];  // the init blocks' largest |.|, as bits
+  double sums[kInitBlocks];      // and sums of |.|
+};
+
+namespace {
 
 // State of one source, behind its grids: whether a bin was not finite (the
-// patch is then NaN); the init blocks' maxima; the spreading workgroups' sums
+// patch is then NaN); the init blocks' maxima and sums; the spreading workgroups' sums
 // of Re c (fused form).
 struct UvGridState {
   uint32_t poison;
-  uint32_t pad[63];
-  uint32_t maxima[kInitBlocks];
   uint32_t next;  // spans handed out beyond the workgroups' first
+  uint32_t pad[62];
+  UvGridScale scale;
   double peak[kGridMaxSpans];
   int64_t first[kGridMaxSpans];  // source 0, fused: first bin of every span
 };
@@ -182,13 +192,28 @@ __device__ __forceinline__ UvGridState* state_of(const UvGridArgs& a, karg_gsrc&
                                                    sizeof(double2));
 }
 
-// The exponent e for which 2^e exceeds every |Re c|, |Im c| of a source; each
-// wave for itself.
-__device__ __forceinline__ int max_exponent(karg_gsrc& s, int n) {
+// ecm and esum of a source; each wave for itself.
+struct Exponents {
+  int ecm, esum;
+};
+__device__ __forceinline__ Exponents exponents(karg_gsrc& s, int n) {
   uint32_t m = 0;
-  for (int q = threadIdx.x & 63; q < n; q += 64) m = max(m, s.maxima[q]);
-  for (int o = 32; o > 0; o >>= 1) m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
-  return static_cast<int>(__builtin_amdgcn_readfirstlane(m) >> 23) - 126;
+  double sum = 0.0;
+  // (a fixed count, so that the loads are under way together)
+#pragma unroll
+  for (int r = 0; r < kInitBlocks / 64; ++r) {
+    const int q = (threadIdx.x & 63) + 64 * r, qc = min(q, n - 1);
+    m = max(m, s.scale->maxima[qc]);
+    sum += q < n ? s.scale->sums[qc] : 0.0;
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
+    sum += __shfl_xor(sum, o);
+  }
+  const int ecm = static_cast<int>(__builtin_amdgcn_readfirstlane(m) >> 23) - 126;
+  // (no exponent of its own where the sum is 0 or not finite: the patch is 0 or NaN)
+  const int esum = sum > 0.0 && sum < 1e300 ? __builtin_amdgcn_frexp_exp(sum) : ecm;
+  return {ecm, __builtin_amdgcn_readfirstlane(esum)};
 }
 
 }  // namespace
@@ -295,10 +320,10 @@ __device__ void cut_spans(const UvGridArgs& a, int block, int64_t* first) {
 
 }  // namespace
 
-// Zeroes the cells and finds the largest |.| of the n floats that scale a
-// source: its coefficients' parts, or in the fused form the weights (|D| <= 1;
-// one pass, by source 0's blocks, for all sources).  Block q leaves its
-// largest as bits in maxima[q]; later kernels take the largest of those.
+// Zeroes the cells and finds the largest and the sum of the |.| of the n
+// floats that scale a source: its coefficients' parts, or in the fused form
+// the weights (|D| <= 1; one pass, by source 0's blocks, for all sources).
+// Block q leaves its own in maxima[q] and sums[q], which later kernels join.
 __global__ __launch_bounds__(256) void k_grid_init(UvGridArgs a) {
   karg_gsrc& s = gsrc(blockIdx.y);
   if (static_cast<int>(blockIdx.x) >= a.n_init) {  // kCutBlocks more where fused
@@ -314,6 +339,12 @@ __global__ __launch_bounds__(256) void k_grid_init(UvGridArgs a) {
   const uint32_t* c = reinterpret_cast<const uint32_t*>(a.fused ? a.o.W : reinterpret_cast<const float*>(s.c));
   const int64_t n = a.fused ? a.o.K : 2 * a.o.K;
   uint32_t m = 0;
+  double sum = 0.0;
+  auto take = [&](uint32_t v) {
+    v &= 0x7fffffffu;
+    m = max(m, v);
+    sum += static_cast<double>(__builtin_bit_cast(float, v));
+  };
   // 16 bytes per load where the array allows, its last n mod 4 words apart
   const bool wide = (reinterpret_cast<uintptr_t>(c) & 15) == 0;
   const int64_t n4 = wide ? n / 4 : 0;
@@ -321,14 +352,24 @@ __global__ __launch_bounds__(256) void k_grid_init(UvGridArgs a) {
 #pragma unroll 8
   for (int64_t k = id; k < n4; k += step) {
     const g_u32x4 v = c4[k];
-    m = max(max(max(m, v[0] & 0x7fffffffu), max(v[1] & 0x7fffffffu, v[2] & 0x7fffffffu)), v[3] & 0x7fffffffu);
+    for (int q = 0; q < 4; ++q) take(v[q]);
   }
-  for (int64_t k = 4 * n4 + id; k < n; k += step) m = max(m, c[k] & 0x7fffffffu);
-  for (int o = 32; o > 0; o >>= 1) m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
+  for (int64_t k = 4 * n4 + id; k < n; k += step) take(c[k]);
+  for (int o = 32; o > 0; o >>= 1) {
+    m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), o)));
+    sum += __shfl_xor(sum, o);
+  }
   __shared__ uint32_t w[4];
-  if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = m;
+  __shared__ double ws[4];
+  if ((threadIdx.x & 63) == 0) {
+    w[threadIdx.x >> 6] = m;
+    ws[threadIdx.x >> 6] = sum;
+  }
   __syncthreads();
-  if (threadIdx.x == 0) s.maxima[blockIdx.x] = max(max(w[0], w[1]), max(w[2], w[3]));
+  if (threadIdx.x == 0) {
+    s.scale->maxima[blockIdx.x] = max(max(w[0], w[1]), max(w[2], w[3]));
+    s.scale->sums[blockIdx.x] = (ws[0] + ws[1]) + (ws[2] + ws[3]);
+  }
 }
 
 namespace {
@@ -467,30 +508,31 @@ struct Tile {
 
 struct Cells {
   unsigned long long* g;
-  int ml, mm, shift;
+  int ml, mm;
 };
 
-__device__ __forceinline__ void add_cell(const Cells& c, int i, int j, int part, int v) {
+__device__ __forceinline__ void add_cell(const Cells& c, int i, int j, int part, unsigned long long v) {
   if (v == 0) return;
-  const int64_t w = static_cast<int64_t>(v) << c.shift;
-  __hip_atomic_fetch_add(&c.g[2 * (static_cast<int64_t>(i) * c.mm + j) + part], static_cast<unsigned long long>(w),
-                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_fetch_add(&c.g[2 * (static_cast<int64_t>(i) * c.mm + j) + part], v, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// x to fixed point, up or down at random with x as the mean (h: random word).
-// Rounded to nearest, the smallest cells of a window, the kernel's tails,
-// would lose up to half a unit each time, always towards zero.
-__device__ __forceinline__ int to_int(float x, float scale, uint32_t h) {
-  const float r = __builtin_bit_cast(float, (h >> 9) | 0x3f800000u);  // [1, 2)
-  return static_cast<int>(floorf(__builtin_fmaf(x, scale, r))) - 1;
+// x scale 2^32 as a 64-bit integer (two's complement), |x scale| < 2^31: the
+// FP32 value's own bits, but for values below 2^32, whose fraction is rounded
+// to 2^8.
+__device__ __forceinline__ unsigned long long to_fixed(float x, float scale) {
+  const float y = x * scale;
+  const uint32_t hi = static_cast<uint32_t>(static_cast<int>(floorf(y)));
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_fractf(y) * 4294967296.0f);
+  return static_cast<unsigned long long>(hi) << 32 | lo;
 }
 
 // A window's accumulators (origin wx, wy) into the tile, cells outside the
-// tile straight into the grid.  h: a random word of the fold.  A bin whose
-// u', v' or c is not finite leaves some accumulator so: the source is poisoned.
-__device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, int* tre, int* tim, int wx, int wy,
-                                            float to_fixed, int lane, uint32_t h, const g_f32x4& re, const g_f32x4& im,
-                                            UvGridState* state) {
+// tile straight into the grid.  A bin whose u', v' or c is not finite leaves
+// some accumulator so: the source is poisoned.
+__device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, unsigned long long* tre,
+                                            unsigned long long* tim, int wx, int wy, float scale, int lane,
+                                            const g_f32x4& re, const g_f32x4& im, UvGridState* state) {
   const int j = lane & 15, i0 = 4 * (lane >> 4);
   const int rx = wrap(wx - t.ox, cells.ml), ry = wrap(wy - t.oy, cells.mm);
   float all = 0.f;  // 0 unless one is not finite
@@ -499,8 +541,7 @@ __device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, i
   if (all != 0.f) state->poison = 1;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const int vr = to_int(re[e], to_fixed, h), vi = to_int(im[e], to_fixed, h + 0x9E3779B1u);
-    h += 2 * 0x9E3779B1u;
+    const unsigned long long vr = to_fixed(re[e], scale), vi = to_fixed(im[e], scale);
     const int ti = rx + i0 + e, tj = ry + j;
     if (ti < t.bx && tj < t.by) {
       __hip_atomic_fetch_add(&tre[ti * t.by + tj], vr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -722,7 +763,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int PREC, bool FUSED>
 __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   constexpr Mode MA = row_mode(PREC), MB = col_mode(PREC);
-  __shared__ int tre[kTileCells], tim[kTileCells];
+  __shared__ unsigned long long tre[kTileCells], tim[kTileCells];
   __shared__ __attribute__((aligned(16))) uint8_t stage_raw[kWaves * kStage];
   __shared__ double tab[FUSED ? kTabRows : 1], tabnu[FUSED ? kTabFreq : 1], tabh[FUSED ? kTabFreq : 1];
   const int lane = threadIdx.x & 63;
@@ -748,12 +789,12 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   const double xh = uniform((l_first + (s.nl / 2) * dl) - l0), yh = uniform((m_first + (s.nm / 2) * dm) - m0);
   const bool shift = !(fabs(xh) <= 1e-12 * fabs(dl) && fabs(yh) <= 1e-12 * fabs(dm));
   UvGridState* state = state_of(a, s);
-  const int ecm = max_exponent(s, a.n_init);
-  const float to_fixed = ldexpf(1.0f, kTileBits - a.log_tile - kAccBits);
-  const Cells cells{cells_of(s), a.ml, a.mm, cell_bits(a.log_k) - (kTileBits - a.log_tile)};
+  const Exponents ex2 = exponents(s, a.n_init);
+  const int ecm = ex2.ecm;
+  const float fold_scale = ldexpf(1.0f, ecm - ex2.esum + kCellBits - kAccBits - 32);
+  const Cells cells{cells_of(s), a.ml, a.mm};
   Tile tile{0, 0, 0, 0};
-  int tab_nc = 0;     // channels per bin that tabnu and tabh are for
-  int tile_bins = 0;  // bins folded into the tile since it was last empty
+  int tab_nc = 0;  // channels per bin that tabnu and tabh are for
   const bool norm = s.norm != 0;
   for (int q = threadIdx.x; q < kTileCells; q += kThreads) tre[q] = tim[q] = 0;
   lds_barrier();
@@ -773,7 +814,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
         tre[e] = tim[e] = 0;
       }
     }
-    tile_bins = 0;
   };
 
   __shared__ int next_span;
@@ -781,7 +821,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   for (int span = blockIdx.x; span < a.n_span;) {
   span_bins(a, span, &ka, &kb);
   double peak = 0.0;  // this lane's share of sum Re c
-  uint32_t fold = mix_word((span * kWaves + wave) * 64 + lane);  // random word of the next fold
   for (int b = owner_of(o.koff, o.n_bl, ka, lane); ka < kb && b < o.n_bl; ++b) {
     Chunk ch;
     ch.b = b;
@@ -801,10 +840,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
     const int64_t t1 = (ch.lb + ch.nf - 1) / ch.nf;
     while (ch.t0 < t1) {
       // Sample the track: 32 times x both ends of the band; the longest
-      // prefix whose extent fits the tile is this chunk (at most as many
-      // bins as the tile's fixed point allows and rows as the table holds).
+      // prefix whose extent fits the tile is this chunk (of at most kChunkBins
+      // bins and as many rows as the table holds).
       int64_t left = t1 - ch.t0;
-      left = min(left, static_cast<int64_t>(max(1, (1 << a.log_tile) / ch.nf)));
+      left = min(left, static_cast<int64_t>(max(1, kChunkBins / ch.nf)));
       if (FUSED && ch.nt <= kTabRows) left = min(left, static_cast<int64_t>(kTabRows / ch.nt));
       const int nt = static_cast<int>(left);
       const int smp = lane >> 1;
@@ -838,7 +877,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
         }
       }
       const float ex = ceilf(xhi - xlo) + (kW + 1 + 2 * kMargin), ey = ceilf(yhi - ylo) + (kW + 1 + 2 * kMargin);
-      const uint64_t fits = __ballot(ex * ey <= kTileCells && ex <= a.ml && ey <= a.mm && ch.nf <= (1 << a.log_tile));
+      const uint64_t fits = __ballot(ex * ey <= kTileCells && ex <= a.ml && ey <= a.mm);
       Tile box{0, 0, 0, 0};
       ch.rows = nt;
       float vt;  // cells per time bin
@@ -878,11 +917,10 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
       const int bt = 1 << lt, bf = 64 >> lt;
 
       lds_barrier();  // the previous chunk's folds and table reads are done
-      // keep the tile while the chunk lies inside it and its sums cannot
-      // overflow; else empty it and lay a new one around the chunk
+      // keep the tile while the chunk lies inside it; else empty it and lay a
+      // new one around the chunk
       const int rx = wrap(box.ox - tile.ox, a.ml), ry = wrap(box.oy - tile.oy, a.mm);
-      const int nbins = box.bx == 0 ? 0 : ch.rows * ch.nf;
-      if (box.bx == 0 || rx + box.bx > tile.bx || ry + box.by > tile.by || tile_bins + nbins > (1 << a.log_tile)) {
+      if (box.bx == 0 || rx + box.bx > tile.bx || ry + box.by > tile.by) {
         flush_tile();
         tile = box;
         if (box.bx > 0) {
@@ -892,7 +930,6 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
           tile.oy = wrap(box.oy - (tile.by - box.by) / 2, a.mm);
         }
       }
-      tile_bins += nbins;
       ch.left = static_cast<int>(min(o.n_t - ch.t0 * ch.nt, int64_t(1) << 30));
       const bool use_tab = FUSED && ch.nt <= kTabRows, use_nu = FUSED && ch.nf <= kTabFreq;
       if constexpr (FUSED) {
@@ -1002,7 +1039,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
           if (wx < 0 || run == kRun || wrap(fax - wx, a.ml) > kSlack || wrap(fay - wy, a.mm) > kSlack) {
             run = 0;
             if (wx >= 0) {
-              fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im, state);
+              fold_window(cells, tile, tre, tim, wx, wy, fold_scale, lane, re, im, state);
               re = im = g_f32x4{0.f, 0.f, 0.f, 0.f};
             }
             const int ll = last_lane(wait);
@@ -1039,7 +1076,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
           im = contract_frags<MA, MB>(fa, fi, going, im);
         }
       }
-      if (wx >= 0) fold_window(cells, tile, tre, tim, wx, wy, to_fixed, lane, fold += 0x85EBCA6Bu, re, im, state);
+      if (wx >= 0) fold_window(cells, tile, tre, tim, wx, wy, fold_scale, lane, re, im, state);
       ch.t0 += ch.rows;
     }
   }
@@ -1132,7 +1169,7 @@ __global__ __launch_bounds__(256) void k_grid_cols(UvGridArgs a) {
   fft_twiddles(tw, M);
   __syncthreads();
   fft_lds(v, tw, M);
-  double scale = ldexp(2.0, max_exponent(s, a.n_init) - cell_bits(a.log_k));
+  double scale = ldexp(2.0, exponents(s, a.n_init).esum - kCellBits);
   if (state_of(a, s)->poison != 0) scale = __builtin_nan("");
   const bool norm = a.fused ? s.norm != 0 : s.peak != nullptr;
   double peak = 1.0;
@@ -1186,25 +1223,14 @@ hipError_t launch_grid(int prec, UvGridArgs a, hipStream_t stream) {
   for (int s = 0; s < a.n_src; ++s) {
     if (a.src[s].nl > a.ml || a.src[s].nm > a.mm) return hipErrorInvalidValue;
     nm = a.src[s].nm > nm ? a.src[s].nm : nm;
-    // every source of the fused form is scaled by the weights' maximum
+    // every source of the fused form is scaled by the weights
     const int m = a.fused ? 0 : s;
-    a.src[s].maxima = reinterpret_cast<UvGridState*>(
+    a.src[s].scale = &reinterpret_cast<UvGridState*>(
                           a.src[m].work +
                           (static_cast<size_t>(a.ml) * a.mm + static_cast<size_t>(a.ml) * a.src[m].nm) * sizeof(double2))
-                          ->maxima;
+                          ->scale;
   }
   const int64_t K = a.o.K;
-  a.log_k = 0;
-  while ((int64_t(1) << a.log_k) < K) ++a.log_k;
-  // Bins a tile may sum: the fewer, the finer its fixed point (a fold is off
-  // by a third of 2^(log_tile - 30) of the largest |c| per cell, at random, so
-  // the patch by about 2^log_tile / sqrt(K) in the same unit); the more, the
-  // fewer tiles are emptied into the grid.  With 2^10 at K = 2^16 and twice as
-  // many per fourfold K this stays near 1e-8 of sum |c| (2^14 throughout:
-  // 1.3e-7 at K = 76760).  At least what kRun batches hold and, so that a row
-  // of frequency bins fits, the number of channels.
-  a.log_tile = std::min(14, std::max(9, 10 + (a.log_k - 16) / 2));
-  while (a.log_tile < 14 && (1 << a.log_tile) < a.o.n_ch) ++a.log_tile;
   // As many workgroups as the chip runs at once (three per compute unit); with
   // fewer than 768 bins each, workgroups of 512 (two rounds of 64 bins per
   // wave) instead, the last of which follow the first that are done, or of 256

@@ -233,7 +233,7 @@ UvGridSrc grid_src(const psf_src* h_src, const BinRec* rec, const float2* c, voi
   s.P = P;
   s.peak = peak;
   s.norm = 0;
-  s.maxima = nullptr;
+  s.scale = nullptr;
   s.dir = dir;
   s.l0 = h_src->l0;
   s.m0 = h_src->m0;

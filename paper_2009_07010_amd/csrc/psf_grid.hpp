@@ -20,6 +20,8 @@ int grid_axis(int n);
 // Bytes of one source's grid, half-transformed grid and state.
 size_t grid_bytes(const GridPlan& g, int nm);
 
+struct UvGridScale;  // what scales a source's fixed point (k_grid.hip)
+
 // Per-source part of a gridded launch; direction and grid as in SrcPlan.
 // Fused launches form the decorrelation factors from the observation; others
 // read records and coefficients.
@@ -30,7 +32,7 @@ struct UvGridSrc {
   float* P;
   const double* peak;  // not fused: see SrcPlan
   const double* dir;
-  uint32_t* maxima;  // filled by launch_grid
+  UvGridScale* scale;  // filled by launch_grid
   double l0, m0, l_first, m_first, dl, dm;
   int nl, nm;
   int norm;  // fused: divide by 2 sum Re c, summed here
@@ -43,10 +45,10 @@ struct UvGridArgs {
   int n_src;
   int ml, mm;  // cells per axis (every source of the launch)
   int fused;
-  // filled by launch_grid: ceil(log2 K), log2 of the bins a tile may sum,
-  // spreading workgroups, levels and number of their spans (per source), init
-  // blocks; bins of the shortest span where all bins cost the same
-  int log_k, log_tile, n_wg, levels, n_span, n_init;
+  // filled by launch_grid: spreading workgroups, levels and number of their
+  // spans (per source), init blocks; bins of the shortest span where all bins
+  // cost the same
+  int n_wg, levels, n_span, n_init;
   int64_t unit_bins;
   UvGridSrc src[kMaxBatch];
 };
