@@ -31,8 +31,11 @@
  *  - Every call is asynchronous on `stream` (a hipStream_t passed as void*,
  *    NULL = the null stream), performs no host<->device synchronisation and
  *    no allocation, and clears what it needs with kernels (no memset
- *    nodes), so it may be captured into a HIP graph.  psf_autotune and
- *    psf_timing_* are the exceptions and say so.
+ *    nodes), so it may be captured into a HIP graph; the exceptions say so.
+ *    The first launch of a kernel may be a captured one, but for
+ *    PSF_PLAIN_BF16 patches and CLEAN, whose contraction and peak search hold
+ *    registers in scratch memory that the runtime allocates at their first
+ *    launch: make one such call before capturing them.
  *  - Scalar and shape checks run on the host before anything is launched.
  *    A failed check returns PSF_EINVAL (or PSF_EWORKSPACE) and launches
  *    nothing; psf_last_error() then holds a message (thread-local).

@@ -198,13 +198,16 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_adjoint(AdjArgs a) {
     dl = a.dir[4];
     dm = a.dir[5];
   }
+  // (the same in every lane: scalar registers)
+  l0 = uniform(l0), m0 = uniform(m0), l_first = uniform(l_first), m_first = uniform(m_first);
+  dl = uniform(dl), dm = uniform(dm);
   // y offsets of the grid: |y_j| < 2^e for all j, so y 2^-e lies in (-1, 1)
   double y_scale = 1.0;
   {
     const double ymax = fmax(fabs(m_first - m0), fabs(m_first + (a.nm - 1) * dm - m0));
     int e = 0;
     if (ymax > 0.0) frexp(ymax, &e);
-    y_scale = ldexp(1.0, -e);
+    y_scale = uniform(ldexp(1.0, -e));
   }
   // folded columns: offsets t dm from the centre column c, |t dm| t_scale < 1,
   // and the centre column's offset from the source
@@ -214,20 +217,21 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_adjoint(AdjArgs a) {
     const double tmax = fabs(cc * dm);
     int e = 0;
     if (tmax > 0.0) frexp(tmax, &e);
-    t_scale = ldexp(1.0, -e);
+    t_scale = uniform(ldexp(1.0, -e));
   }
-  const double delta_m = (m_first + cc * dm) - m0;
-  const float inv_t = static_cast<float>(1.0 / t_scale), tds = static_cast<float>(dm * t_scale);
+  const double delta_m = uniform((m_first + cc * dm) - m0);
+  const float inv_t = uniform(static_cast<float>(1.0 / t_scale)), tds = uniform(static_cast<float>(dm * t_scale));
   (void)inv_t;
   (void)tds;
-  const float inv_y = static_cast<float>(1.0 / y_scale);
-  // first column of the lane: 8 jg (16-bit operands), jg (FP32 operands)
-  const double y_lane = (m_first + (PREC == kFP32 ? jg : 8 * jg) * dm) - m0;
-  const double x_lane = (l_first + (16 * rb0 + 4 * jg) * dl) - l0;  // row 16 rb0 + 4 jg
-  const float ys0 = static_cast<float>(y_lane * y_scale), ystep = static_cast<float>(dm * y_scale);
-  const float xs0 = static_cast<float>(x_lane), xstep = static_cast<float>(dl);
+  const float inv_y = uniform(static_cast<float>(1.0 / y_scale));
+  const float ystep = uniform(static_cast<float>(dm * y_scale)), xstep = uniform(static_cast<float>(dl));
   double gl = 0.0, gm = 0.0;
   for (int64_t k0 = kb + 16 * wave; k0 < ke; k0 += 16 * (kAdjThreads / 64)) {
+    // (formed anew every time: the products leave no registers for them)
+    const int jo = opaque(lane) >> 4;
+    // first column of the lane: 8 jg (16-bit operands), jg (FP32 operands)
+    const double y_lane = (m_first + (PREC == kFP32 ? jo : 8 * jo) * dm) - m0;
+    const float ys0 = static_cast<float>(y_lane * y_scale);
     const int64_t kk = k0 + n;
     const bool ok = kk < ke;
     const BinRec* r = a.rec + (ok ? kk : ke - 1);
@@ -257,6 +261,7 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_adjoint(AdjArgs a) {
             acc[rb][2] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, yr, acc[rb][2], 0, 0, 0);
             acc[rb][3] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, yi, acc[rb][3], 0, 0, 0);
           }
+          if (NRB >= 8) __builtin_amdgcn_sched_barrier(0);  // G's loads of all eight steps at once do not fit
         }
       }
     }
@@ -365,6 +370,8 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_adjoint(AdjArgs a) {
       __builtin_amdgcn_s_setprio(0);
     }
     // H, Hx, Hy over this lane's rows 16 rb + 4 jg + e
+    const double x_lane = (l_first + (16 * rb0 + 4 * (opaque(lane) >> 4)) * dl) - l0;  // row 16 rb0 + 4 jg
+    const float xs0 = static_cast<float>(x_lane);
     cf32 za = expi_turns(up * x_lane);
     const cf32 t1 = expi_turns(up * dl), t13 = expi_turns(up * (13.0 * dl));
     float h1r = 0.f, h1i = 0.f, hxr = 0.f, hxi = 0.f, hyr = 0.f, hyi = 0.f;
@@ -387,13 +394,14 @@ __global__ __launch_bounds__(kAdjThreads, 2) void k_adjoint(AdjArgs a) {
       }
     }
     // the four lane groups of a visibility hold disjoint rows
+    const int ln = opaque(lane);
     for (int o = 16; o <= 32; o <<= 1) {
-      h1r += __shfl_xor(h1r, o);
-      h1i += __shfl_xor(h1i, o);
-      hxr += __shfl_xor(hxr, o);
-      hxi += __shfl_xor(hxi, o);
-      hyr += __shfl_xor(hyr, o);
-      hyi += __shfl_xor(hyi, o);
+      h1r += from_lane(h1r, ln ^ o);
+      h1i += from_lane(h1i, ln ^ o);
+      hxr += from_lane(hxr, ln ^ o);
+      hxi += from_lane(hxi, ln ^ o);
+      hyr += from_lane(hyr, ln ^ o);
+      hyi += from_lane(hyi, ln ^ o);
     }
     if (jg == 0 && ok) {
       if constexpr (FOLD) {

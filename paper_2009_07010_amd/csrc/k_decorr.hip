@@ -151,13 +151,17 @@ __device__ __forceinline__ BinSums bin_sums(const ObsView& o, const BinRef& r, d
 // two real operations per sample instead of a sine-cosine pair and eight more.
 // In FP64, whose rate is that of FP32 here, because the recurrence loses
 // digits with the square of the channels at small angles.  Windowed bins take
-// kLen channels at a time, their windows in registers (0 beyond the last;
-// read from memory for every row instead: 753 against 542 us for bins of
-// 20 x 40); without windows all channels at once.
+// kLen channels at a time, the windows (0 beyond the last) of the first
+// kWinReg in registers, of the others in this thread's part of LDS (win; the
+// registers of four waves per SIMD do not hold 40); without windows all
+// channels at once.
+constexpr int kWinLen = 40, kWinReg = 20, kWinLds = (kWinLen - kWinReg) / 4;
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 template <bool kWin, int kLen>
 __device__ __forceinline__ BinSums even_sums(const ObsView& o, const BinRef& r, double l0, double m0, double Lw,
-                                             double A_k, double nu_k, double h) {
+                                             double A_k, double nu_k, double h, f32x4_t (*win)[256]) {
 #pragma clang fp contract(off)
+  constexpr int kReg = kLen < kWinReg ? kLen : kWinReg;
   BinSums s{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   const double* row = o.uvw + 3 * (static_cast<int64_t>(r.b) * o.n_t);
   const float* win_tb = kWin && o.win_t != nullptr ? o.win_t + static_cast<int64_t>(r.b) * o.n_t : nullptr;
@@ -165,13 +169,21 @@ __device__ __forceinline__ BinSums even_sums(const ObsView& o, const BinRef& r, 
   const double A_knu = A_k * nu_k;
   for (int cb = r.c0; cb < r.c1; cb += kWin ? kLen : r.c1 - r.c0) {
     const int nch = kWin ? min(kLen, r.c1 - cb) : r.c1 - cb;
-    float x[kLen];
+    float x[kReg];
     if constexpr (kWin) {
-#pragma unroll
-      for (int j = 0; j < kLen; ++j) {
+      auto window = [&](int j) {
         const float w = win_cb != nullptr ? win_cb[cb + min(j, nch - 1)] : 1.f;
-        x[j] = j < nch ? w : 0.f;
         if (j < nch) s.sc += w;
+        return j < nch ? w : 0.f;
+      };
+#pragma unroll
+      for (int j = 0; j < kReg; ++j) x[j] = window(j);
+#pragma unroll
+      for (int q = 0; q < (kLen - kReg) / 4; ++q) {
+        f32x4_t v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = window(kReg + 4 * q + j);
+        win[q][threadIdx.x] = v;
       }
     }
     const double nu = o.freq[cb];
@@ -194,8 +206,15 @@ __device__ __forceinline__ BinSums even_sums(const ObsView& o, const BinRef& r, 
         b0 = b;
       };
       if constexpr (kWin) {
+        const int slot = opaque(threadIdx.x);  // read for every row, not held
 #pragma unroll
-        for (int j = kLen - 1; j >= 0; --j) {
+        for (int q = (kLen - kReg) / 4 - 1; q >= 0; --q) {
+          const f32x4_t v = win[q][slot];
+#pragma unroll
+          for (int j = 3; j >= 0; --j) step(v[j]);
+        }
+#pragma unroll
+        for (int j = kReg - 1; j >= 0; --j) {
           asm("" : "+v"(x[j]));  // converted for every row: 40 registers less than the FP64 values
           step(x[j]);
         }
@@ -220,13 +239,13 @@ __device__ __forceinline__ BinSums even_sums(const ObsView& o, const BinRef& r, 
 template <bool kWin>
 __device__ __forceinline__ BinSums wide_sums(const ObsView& o, const BinRef& r, double l0, double m0, double Lw,
                                              double A_k, double nu_k, double uc, double vc, double wc, double l0_n0,
-                                             double m0_n0) {
+                                             double m0_n0, f32x4_t (*win)[256]) {
   const int nc = r.c1 - r.c0;
   const double h =
       nc >= kEvenBin && r.t1 - r.t0 > 1 ? even_half_step(o.freq, r.c0, r.c1, nu_k) : __builtin_nan("");
   if (h == h) {
-    if (kWin && nc <= 20) return even_sums<kWin, 20>(o, r, l0, m0, Lw, A_k, nu_k, h);
-    return even_sums<kWin, 40>(o, r, l0, m0, Lw, A_k, nu_k, h);
+    if (kWin && nc <= kWinReg) return even_sums<kWin, kWinReg>(o, r, l0, m0, Lw, A_k, nu_k, h, win);
+    return even_sums<kWin, kWinLen>(o, r, l0, m0, Lw, A_k, nu_k, h, win);
   }
   return bin_sums<kWin, false>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
 }
@@ -301,10 +320,13 @@ __device__ __forceinline__ void finish_bin(const ObsView& o, int64_t k, double l
 // two doubles) when dirs is given, and whose records start y * rec_stride
 // elements into rec_out and c_out.
 //
-// wide: wide_sums, for observations that may hold bins it is good for (72
-// registers for boxcar averaging, 128 with windows; bin_sums alone takes 70).
-// Bins of 20 x 40 samples, K = 2.2M: 1087 -> 349 us, with windows 1574 -> 542
+// wide: wide_sums, for observations that may hold bins it is good for (54
+// registers for boxcar averaging, 126 with windows; bin_sums alone takes 68).
+// Bins of 20 x 40 samples, K = 2.2M: 1087 -> 331 us, with windows 1574 -> 507
 // (arithmetic: 2 or 3 FP64 operations per sample and about 100 per row).
+// Nothing is spilled: the windowed kernel held 44 registers in scratch memory,
+// which a kernel must have been launched once to have (534 us; with three
+// waves per SIMD instead 600).
 enum Wide { kNotWide, kWideBoxcar, kWideWindow };
 template <bool kGrad, Wide wide>
 __global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(ObsView o, double l0, double m0, double dl, double dm,
@@ -318,6 +340,7 @@ __global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(Obs
   // No fused multiply-add in this kernel: the two products of the phase
   // difference must round alike so that identical rows cancel exactly.
 #pragma clang fp contract(off)
+  __shared__ f32x4_t win[wide == kWideWindow ? kWinLds : 1][256];
   const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (k >= o.K) return;
   if (dirs != nullptr) {
@@ -326,13 +349,14 @@ __global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(Obs
     dl = dirs[blockIdx.y * dir_stride + 4];
     dm = dirs[blockIdx.y * dir_stride + 5];
   }
+  // (the same in every lane: scalar registers)
+  l0 = uniform(l0), m0 = uniform(m0), dl = uniform(dl), dm = uniform(dm);
   if (rec_out != nullptr) rec_out += blockIdx.y * rec_stride;
   if (c_out != nullptr) c_out += blockIdx.y * rec_stride;
   const BinRef r = locate_bin(o.koff, o.tboff, o.bl_bin, o.n_bl, o.n_t, o.n_ch, k);
-  const double n0 = sqrt(1.0 - l0 * l0 - m0 * m0);
-  const double Lw = n0 - 1.0;
+  const double n0 = uniform(sqrt(1.0 - l0 * l0 - m0 * m0)), Lw = uniform(n0 - 1.0);
   const double nu_k = bin_freq(o.freq, r.c0, r.c1);
-  const double uc = o.uvw_c[3 * r.tb + 0], vc = o.uvw_c[3 * r.tb + 1], wc = o.uvw_c[3 * r.tb + 2];
+  double uc = o.uvw_c[3 * r.tb + 0], vc = o.uvw_c[3 * r.tb + 1], wc = o.uvw_c[3 * r.tb + 2];
 
   float dre = 0.f, dim = 0.f;
   float dDl_re = 0.f, dDl_im = 0.f, dDm_re = 0.f, dDm_im = 0.f;
@@ -342,7 +366,7 @@ __global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(Obs
     dim = d.y;
   } else {
     const double A_k = uc * l0 + vc * m0 + wc * Lw;
-    const double l0_n0 = l0 / n0, m0_n0 = m0 / n0;
+    const double l0_n0 = uniform(l0 / n0), m0_n0 = uniform(m0 / n0);
     float inv;
     BinSums bs;
     if (wide == kWideWindow || (wide == kNotWide && (o.win_t != nullptr || o.win_c != nullptr))) {
@@ -350,12 +374,19 @@ __global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(Obs
       // mean normalised by the window's sum over the bin (D = 0 for a
       // window that sums to 0).  Separable, so the normaliser is the
       // product of the two axis sums.
-      if constexpr (wide != kNotWide) bs = wide_sums<true>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
-      else bs = bin_sums<true, kGrad>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      if constexpr (wide != kNotWide) {
+        bs = wide_sums<true>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0, win);
+        // (read again, so that the sums have the registers)
+        int64_t tb = r.tb;
+        asm volatile("" : "+v"(tb));
+        uc = o.uvw_c[3 * tb], vc = o.uvw_c[3 * tb + 1], wc = o.uvw_c[3 * tb + 2];
+      } else {
+        bs = bin_sums<true, kGrad>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      }
       const float norm = bs.st * bs.sc;
       inv = norm != 0.f ? 1.0f / norm : 0.f;
     } else {
-      if constexpr (wide != kNotWide) bs = wide_sums<false>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
+      if constexpr (wide != kNotWide) bs = wide_sums<false>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0, win);
       else bs = bin_sums<false, kGrad>(o, r, l0, m0, Lw, A_k, nu_k, uc, vc, wc, l0_n0, m0_n0);
       inv = 1.0f / static_cast<float>((r.t1 - r.t0) * (r.c1 - r.c0));
     }
@@ -369,7 +400,9 @@ __global__ __launch_bounds__(256, wide == kWideWindow ? 4 : 1) void k_decorr(Obs
       dDm_im = bs.gmi * sc;
     }
   }
-  finish_bin<kGrad>(o, k, l0, m0, n0, dl, dm, nu_k, uc, vc, wc, dre, dim, dDl_re, dDl_im, dDm_re, dDm_im,
+  // (formed anew: no registers are held for it)
+  const int64_t kf = static_cast<int64_t>(blockIdx.x) * blockDim.x + opaque(threadIdx.x);
+  finish_bin<kGrad>(o, kf, l0, m0, n0, dl, dm, nu_k, uc, vc, wc, dre, dim, dDl_re, dDl_im, dDm_re, dDm_im,
                     D_in == nullptr, D_out, rec_out, c_out, coef_out);
 }
 
@@ -459,7 +492,7 @@ bool use_wave_bins(const ObsView& o) {
 
 // The kernel without derivatives: wide where there are channels enough, with
 // windows only from 128 samples per bin on average (the bins' own sizes are on
-// the device), since that form takes 128 registers to the other's 70.
+// the device), since that form takes 126 registers to the other's 68.
 static decltype(&k_decorr<false, kNotWide>) decorr_kernel(const ObsView& o) {
   if (o.n_ch < kEvenBin) return k_decorr<false, kNotWide>;
   if (o.win_t == nullptr && o.win_c == nullptr) return k_decorr<false, kWideBoxcar>;

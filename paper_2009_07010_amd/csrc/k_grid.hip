@@ -556,13 +556,6 @@ __device__ __forceinline__ void fold_window(const Cells& cells, const Tile& t, u
   }
 }
 
-__device__ __forceinline__ double uniform(double x) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b)));
-  const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(b >> 32)));
-  return __builtin_bit_cast(double, hi << 32 | lo);
-}
-
 __device__ __forceinline__ int first_lane(uint64_t m) { return __builtin_ctzll(m); }
 __device__ __forceinline__ int last_lane(uint64_t m) { return 63 - __builtin_clzll(m); }
 
@@ -744,8 +737,8 @@ __device__ __forceinline__ void span_bins(const UvGridArgs& a, int i, int64_t* k
     p = span_units(a, i) * a.unit_bins;
     q = span_units(a, i + 1) * a.unit_bins;
   }
-  *ka = min(max(p, int64_t(0)), a.o.K);
-  *kb = min(max(q, *ka), a.o.K);
+  *ka = uniform(min(max(p, int64_t(0)), a.o.K));
+  *kb = uniform(min(max(q, *ka), a.o.K));
 }
 
 // Waits for this workgroup's LDS traffic only: __syncthreads also waits for
@@ -759,7 +752,10 @@ __device__ __forceinline__ void lds_barrier() {
 }  // namespace
 
 // FUSED: the decorrelation factors are formed here from the samples (boxcar
-// averaging), else u', v' and c come from records.
+// averaging), else u', v' and c come from records.  Three waves per SIMD, and
+// no scratch memory (what is the same in every lane sits in scalar registers):
+// a kernel that spills needs an eager launch before it can be captured, to
+// have its scratch allocated.
 template <int PREC, bool FUSED>
 __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   constexpr Mode MA = row_mode(PREC), MB = col_mode(PREC);
@@ -783,6 +779,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
     dm = s.dir[5];
   }
   // (the same in every lane: kept in scalar registers)
+  l0 = uniform(l0), m0 = uniform(m0), dl = uniform(dl), dm = uniform(dm);
   const double n0 = sqrt(1.0 - l0 * l0 - m0 * m0), lw = uniform(n0 - 1.0), l0n = uniform(l0 / n0), m0n = uniform(m0 / n0);
   // offsets from the source of the pixels that modes (0, 0) stand for;
   // nothing to shift where they are rounding of a grid centred on the source
@@ -791,7 +788,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   UvGridState* state = state_of(a, s);
   const Exponents ex2 = exponents(s, a.n_init);
   const int ecm = ex2.ecm;
-  const float fold_scale = ldexpf(1.0f, ecm - ex2.esum + kCellBits - kAccBits - 32);
+  const float fold_scale = uniform(ldexpf(1.0f, ecm - ex2.esum + kCellBits - kAccBits - 32));
   const Cells cells{cells_of(s), a.ml, a.mm};
   Tile tile{0, 0, 0, 0};
   int tab_nc = 0;  // channels per bin that tabnu and tabh are for
@@ -824,18 +821,18 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   for (int b = owner_of(o.koff, o.n_bl, ka, lane); ka < kb && b < o.n_bl; ++b) {
     Chunk ch;
     ch.b = b;
-    ch.base = o.koff[b];
-    const int64_t kend = b + 1 < o.n_bl ? min(kb, o.koff[b + 1]) : kb;
+    ch.base = uniform(o.koff[b]);
+    const int64_t kend = uniform(b + 1 < o.n_bl ? min(kb, o.koff[b + 1]) : kb);
     if (kend <= ka) continue;
-    ch.nt = max(1, o.bl_bin[2 * b]);
-    ch.nc = max(1, o.bl_bin[2 * b + 1]);
+    ch.nt = uniform(max(1, o.bl_bin[2 * b]));
+    ch.nc = uniform(max(1, o.bl_bin[2 * b + 1]));
     ch.nf = 1 + (o.n_ch - 1) / ch.nc;
     ch.la = ka - ch.base;
     ch.lb = kend - ch.base;
     ch.full = min(ch.nt, o.n_t) * min(ch.nc, o.n_ch);
     ch.inv = 1.0f / static_cast<float>(ch.full);
     ka = kend;
-    const int64_t tb0 = o.tboff[b];
+    const int64_t tb0 = uniform(o.tboff[b]);
     ch.t0 = ch.la / ch.nf;
     const int64_t t1 = (ch.lb + ch.nf - 1) / ch.nf;
     while (ch.t0 < t1) {
@@ -862,13 +859,15 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
       }
       pu *= dl * a.ml;
       pv *= dm * a.mm;
-      const double ru = __shfl(pu, 0), rv = __shfl(pv, 0);
+      const double ru = of_lane(pu, 0), rv = of_lane(pv, 0);
       const float x = static_cast<float>(pu - ru), y = static_cast<float>(pv - rv);
-      float xlo = fminf(x, __shfl_xor(x, 1)), xhi = fmaxf(x, __shfl_xor(x, 1));
-      float ylo = fminf(y, __shfl_xor(y, 1)), yhi = fmaxf(y, __shfl_xor(y, 1));
+      const int ln = opaque(lane);
+      const float x1 = from_lane(x, ln ^ 1), y1 = from_lane(y, ln ^ 1);
+      float xlo = fminf(x, x1), xhi = fmaxf(x, x1), ylo = fminf(y, y1), yhi = fmaxf(y, y1);
 #pragma unroll
       for (int q = 2; q < 64; q <<= 1) {
-        const float p0 = __shfl_up(xlo, q), p1 = __shfl_up(xhi, q), p2 = __shfl_up(ylo, q), p3 = __shfl_up(yhi, q);
+        const float p0 = from_lane(xlo, ln - q), p1 = from_lane(xhi, ln - q);
+        const float p2 = from_lane(ylo, ln - q), p3 = from_lane(yhi, ln - q);
         if (lane >= q) {
           xlo = fminf(xlo, p0);
           xhi = fmaxf(xhi, p1);
@@ -881,7 +880,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
       Tile box{0, 0, 0, 0};
       ch.rows = nt;
       float vt;  // cells per time bin
-      const float vf = fmaxf(fabsf(__shfl(x, 1)), fabsf(__shfl(y, 1))) / max(1, ch.nf - 1);  // per frequency bin
+      const float vf = fmaxf(fabsf(of_lane(x, 1)), fabsf(of_lane(y, 1))) / max(1, ch.nf - 1);  // per frequency bin
       const int sl = fits & 1 ? last_lane(fits) : 0, ss = sl >> 1;
       if (fits & 1) ch.rows = static_cast<int>((static_cast<int64_t>(nt - 1) * ss) / 31) + 1;
       // Where the track leaves a tile within kSparse bins (long baselines, wide
@@ -889,16 +888,16 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
       // the chunk as long as it may be (K = 216k of 40 antennas to 8 km, two
       // channels 400 MHz apart, 14 s steps, 150 x 150 pixels: 334 -> 77 us).
       if ((fits & 1) && (ch.rows == nt || ch.rows * ch.nf >= kSparse)) {
-        vt = fmaxf(fabsf(__shfl(x, 2 * ss)), fabsf(__shfl(y, 2 * ss))) / max(1, ch.rows - 1);
-        box.bx = __builtin_amdgcn_readfirstlane(static_cast<int>(__shfl(ex, sl)));
-        box.by = __builtin_amdgcn_readfirstlane(static_cast<int>(__shfl(ey, sl)));
-        const double fx = floor(ru + __shfl(xlo, sl)) - (kW / 2 + kMargin);
-        const double fy = floor(rv + __shfl(ylo, sl)) - (kW / 2 + kMargin);
+        vt = fmaxf(fabsf(of_lane(x, 2 * ss)), fabsf(of_lane(y, 2 * ss))) / max(1, ch.rows - 1);
+        box.bx = static_cast<int>(of_lane(ex, sl));
+        box.by = static_cast<int>(of_lane(ey, sl));
+        const double fx = floor(ru + of_lane(xlo, sl)) - (kW / 2 + kMargin);
+        const double fy = floor(rv + of_lane(ylo, sl)) - (kW / 2 + kMargin);
         box.ox = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(fx - floor(fx / a.ml) * a.ml), 0), a.ml - 1));
         box.oy = __builtin_amdgcn_readfirstlane(min(max(static_cast<int>(fy - floor(fy / a.mm) * a.mm), 0), a.mm - 1));
       } else {
         ch.rows = nt;
-        vt = fmaxf(fabsf(__shfl(x, 62)), fabsf(__shfl(y, 62))) / max(1, nt - 1);
+        vt = fmaxf(fabsf(of_lane(x, 62)), fabsf(of_lane(y, 62))) / max(1, nt - 1);
       }
       ch.rows = __builtin_amdgcn_readfirstlane(ch.rows);
       // rectangle of time x frequency bins per wave: the fewest windows
@@ -1046,6 +1045,13 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
             wx = window_origin(fax, __builtin_amdgcn_readlane(ax, ll), a.ml);
             wy = window_origin(fay, __builtin_amdgcn_readlane(ay, ll), a.mm);
           }
+          // (opaque, or the split operands of both axes, the same in every
+          // window of these bins, are formed ahead of the loop, in registers of
+          // their own)
+          if (MA == kMBF16 || MA == kMFP16)
+#pragma unroll
+            for (int r = 0; r < kW; ++r) asm volatile("" : "+v"(tx[r]));
+          if (MB == kMBF16 || MB == kMFP16) asm volatile("" : "+v"(c.re), "+v"(c.im));
           ++run;
           const int dx = wrap(ax - wx, a.ml), dy = wrap(ay - wy, a.mm);
           const bool go = ((wait >> lane) & 1) != 0 && dx <= kSlack && dy <= kSlack;
@@ -1087,7 +1093,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
                                                                                  __HIP_MEMORY_SCOPE_AGENT));
   if (FUSED && norm) {
     // sum Re c of the span, in a fixed order
-    for (int q = 32; q > 0; q >>= 1) peak += __shfl_xor(peak, q);
+    const int ln = opaque(lane);
+    for (int q = 32; q > 0; q >>= 1) peak += from_lane(peak, ln ^ q);
     lds_barrier();
     if (lane == 0) tab[wave] = peak;
   }

@@ -212,4 +212,43 @@ __device__ __forceinline__ uint32_t f16_lo_pair(uint32_t hi, float v0, float v1)
   return pack_f16x2(__builtin_fmaf(f16_lo_to_f32(hi), m1, v0), __builtin_fmaf(f16_hi_to_f32(hi), m1, v1));
 }
 
+// A value that every lane has, in scalar registers.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  const uint64_t lo = static_cast<uint32_t>(uniform(static_cast<int>(x)));
+  const uint64_t hi = static_cast<uint32_t>(uniform(static_cast<int>(x >> 32)));
+  return static_cast<int64_t>(hi << 32 | lo);
+}
+__device__ __forceinline__ float uniform(float x) {
+  return __builtin_bit_cast(float, uniform(__builtin_bit_cast(int, x)));
+}
+__device__ __forceinline__ double uniform(double x) {
+  return __builtin_bit_cast(double, uniform(__builtin_bit_cast(int64_t, x)));
+}
+
+// A value from lane l: for uniform l, and for one of each lane's own.
+__device__ __forceinline__ float of_lane(float x, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+}
+__device__ __forceinline__ double of_lane(double x, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(b), l));
+  const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(b >> 32), l));
+  return __builtin_bit_cast(double, hi << 32 | lo);
+}
+__device__ __forceinline__ float from_lane(float x, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * l, __builtin_bit_cast(int, x)));
+}
+__device__ __forceinline__ double from_lane(double x, int l) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, x);
+  const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(4 * l, static_cast<int>(b)));
+  const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(4 * l, static_cast<int>(b >> 32)));
+  return __builtin_bit_cast(double, hi << 32 | lo);
+}
+// The lane, opaque: what is computed from it is not kept across a loop.
+__device__ __forceinline__ int opaque(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
 }  // namespace psf
