@@ -63,7 +63,9 @@ typedef enum {
 } psf_status;
 
 /* Arithmetic of the patch contraction.  A patch is evaluated in one of two
- * forms, chosen by K and the patch size (the faster one):
+ * forms, chosen by K, the patch size and the arithmetic (the faster one; split
+ * arithmetics take the gridded one, whose error is the smaller, also where it
+ * is up to 25 us behind):
  *  - dense, for few bins: every bin at every pixel, phase factors formed in
  *    FP64 turns, products in the arithmetic below, FP32 accumulation;
  *  - gridded, for many bins (from K = 24576 on, patches of up to 1044 pixels

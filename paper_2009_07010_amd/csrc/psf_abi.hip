@@ -181,30 +181,42 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
   return p;
 }
 
-// Which patches run gridded.  Measured (MI355X, us per psf_patch call, boxcar
-// bins of 3 x 4 samples, split-BF16; patch_work at 256 CUs and 2.1 GHz follows
-// the dense form within 40%):
-//   pixels        33        65       129       200       257       300
-//   K =  27k   30 | 39   26 | 38   34 | 41   48 | 46   47 | 47   76 | 67   dense | gridded
-//   K =  51k   34 | 39   29 | 39   40 | 41   70 | 45   57 | 46  123 | 67
-//   K = 152k   57 | 46   42 | 47   56 | 46  166 | 54   90 | 55  327 | 74
-//   K = 302k   93 | 53   52 | 52   77 | 53  304 | 60  150 | 59  623 | 77
-// Below 24576 bins the dense call is the shorter.  The line is drawn with 40 us
-// (60 in the symmetric families) for the dense form beside its contraction, 10
-// to 25 more than it takes, so that a patch near the line runs gridded: within
-// 10 us of the other, and with a third of its error.  PSF_PLAIN_BF16, a
+// Which patches run gridded.  Measured (MI355X, us per call, boxcar bins of 3 x
+// 4 samples, 190 baselines over two hours; patch_work at 256 CUs and 2.1 GHz and
+// 20 us, 25 in the symmetric families, follow the dense form within 10% where
+// the two are near each other; at K = 27k, bins of 200 s, the tracks are sparse
+// and the gridded form takes 5 to 12 us more than the rule says):
+//   pixels               33          65         129         200         257         300
+//   split-BF16
+//   K =  27k      26.7 | -   23.7 | 42.6 32.1 | 46.0 44.0 | 61.7 41.4 | 62.7 71.6 | -     dense | gridded
+//   K =  52k   32.7 | 35.7   27.7 | 36.3 36.1 | 37.5 65.7 | 48.9 50.4 | 49.8 116  | 82.0
+//   K = 152k   55.3 | 41.3   38.9 | 41.5 50.9 | 44.3 155  | 52.2 85.6 | 53.1 311  | 76.4
+//   K = 302k   89.2 | 51.6   49.9 | 51.7 73.7 | 49.3 289  | 58.7 140  | 59.7 600  | 74.7
+//   FP32
+//   K =  27k   34.8 | 42.6   29.5 | 42.7 39.8 | 45.9
+//   K =  52k   46.8 | 35.9   33.9 | 36.0 47.4 | 37.6
+//   K = 152k   102  | 42.1   48.7 | 42.3 85.0 | 45.2
+// FP32 takes the shorter.  The split forms run gridded up to `lead` before the
+// times cross.  In the symmetric families, where the dense form's advantage is
+// at most 19 us, because split products of so few bins leave it 1.4 to 2.6e-7
+// off (1.2 times the 2.5e-7 of 2 sum |c| that the gridded form is held to at K =
+// 28k, 129 x 140), gridded 0.4 to 1.9e-7; FP16 because the dense form's columns c b
+// are FP16 as they are and overflow beyond |c| = 65504, while the gridded form
+// scales them.  Below 24576 bins every call is dense.  PSF_PLAIN_BF16, a
 // negative control, stays dense; the mixed and stochastic arithmetics exist in
 // the gridded form only.
 GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec) {
   constexpr int64_t kMinBins = 24576;
   GridPlan g;
-  const int kp = launch_prec(prec, o->K, sym_source(s));
+  const bool sym = sym_source(s);
+  const int kp = launch_prec(prec, o->K, sym);
   if (kp == PSF_PLAIN_BF16 || o->K < kMinBins) return g;
   const int ml = grid_axis(s->nl), mm = grid_axis(s->nm);
   if (ml == 0 || mm == 0) return g;
-  const double dense = (sym_source(s) ? 60e-6 : 40e-6) + patch_work(o, s, kp) / (kTargetWorkgroups * 2.1e9);
-  const double grid = 45e-6 + static_cast<double>(o->K) * 0.06e-9 + static_cast<double>(ml) * mm * 0.05e-9;
-  if (dense <= grid && kp != PSF_MIXED_FP16 && kp != PSF_SR_FP16) return g;
+  const double dense = (sym ? 25e-6 : 20e-6) + patch_work(o, s, kp) / (kTargetWorkgroups * 2.1e9);
+  const double grid = 35e-6 + static_cast<double>(o->K) * 0.06e-9 + static_cast<double>(ml) * mm * 0.05e-9;
+  const double lead = kp == PSF_FP32 ? 0.0 : sym ? 25e-6 : kp == PSF_SPLIT_FP16 ? 10e-6 : 0.0;
+  if (dense + lead <= grid && kp != PSF_MIXED_FP16 && kp != PSF_SR_FP16) return g;
   g.ml = ml;
   g.mm = mm;
   return g;

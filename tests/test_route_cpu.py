@@ -1,0 +1,45 @@
+"""Which patches take the gridded form: the host's rule against the measured
+times of both (MI355X, us): the shorter one in FP32 and, but for the symmetric
+families, in split-BF16; gridded in the other split forms where the two are
+within 25 (symmetric families) or 10 us."""
+import ctypes
+
+import pytest
+
+import paper_2009_07010_amd as pk
+
+SYMBOL = "_ZN3psf10grid_routeEPK7psf_obsPK7psf_srci"  # psf::grid_route(const psf_obs*, const psf_src*, int)
+
+
+def _gridded(K, n, prec):
+    f = getattr(pk.lib(), SYMBOL)
+    f.restype = ctypes.c_uint64  # {int ml, mm}, both 0: dense
+    o, s = pk.PsfObs(), pk.PsfSrc()
+    o.K, o.n_bl, o.n_t, o.n_ch, s.nl, s.nm = K, 190, 1, 1, n, n
+    return f(ctypes.byref(o), ctypes.byref(s), pk.PRECISIONS[prec]) != 0
+
+
+# (pixels, K, dense us, gridded us) where they differ by more than 5%
+TIMES = {"fp32": [(33, 27360, 34.8, 42.6), (65, 27360, 29.5, 42.7), (129, 27360, 39.8, 45.9), (33, 51680, 46.8, 35.9),
+                  (65, 51680, 33.9, 36.0), (129, 51680, 47.4, 37.6), (33, 152000, 101.6, 42.1), (65, 152000, 48.7, 42.3),
+                  (129, 152000, 85.0, 45.2), (65, 302480, 71.1, 52.4)],
+         "split_bf16": [(33, 51680, 32.7, 35.7), (33, 152000, 55.3, 41.3), (200, 27360, 44.0, 61.7),
+                        (200, 51680, 65.7, 48.9), (300, 51680, 116.2, 82.0)]}
+
+
+@pytest.mark.parametrize("prec", sorted(TIMES))
+def test_the_shorter_form(prec):
+    for n, K, dense, grid in TIMES[prec]:
+        assert _gridded(K, n, prec) == (grid < dense), (n, K)
+
+
+def test_accuracy_and_range():
+    for K in (27360, 51680, 152000):
+        for n in (65, 129, 257):
+            for prec in ("split_bf16", "split_fp16"):
+                assert _gridded(K, n, prec), (K, n, prec)
+    assert _gridded(51680, 200, "split_fp16") and not _gridded(27360, 300, "split_fp16")
+    for n in (65, 129, 257):
+        assert _gridded(1 << 18, n, "sr_fp16") and _gridded(1 << 18, n, "mixed_fp16")
+        assert not _gridded(1 << 28, n, "plain_bf16") and not _gridded(24575, n, "split_bf16")
+    assert not _gridded(1 << 20, 1045, "fp32")  # beyond the largest grid
