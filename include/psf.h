@@ -248,8 +248,10 @@ int psf_patch_batched(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs,
  * visibility in reverse mode (G b and G (y b) on the matrix cores, G held
  * on chip); otherwise it
  * forms five derivative patches with the forward contraction (arithmetic
- * chosen by prec) and reduces them against G.  Both accumulate in FP64 in a
- * fixed order (deterministic).
+ * chosen by prec), dense or gridded as a patch of that size is, and reduces
+ * them against G.  Both accumulate in FP64 in a fixed order (deterministic).
+ * Gradients are no closer to 64-bit ones than their arithmetic: of 300
+ * columns, 1e-7 to 6e-7 from dense patches, 4e-8 to 3e-7 from gridded ones.
  * h_srcs (host) gives sizes and out_off, and the directions and grids
  * when d_srcs is NULL; otherwise d_srcs (device, same entries as h_srcs)
  * supplies directions and grids at run time, so a captured forward and
