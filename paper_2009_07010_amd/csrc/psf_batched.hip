@@ -334,15 +334,19 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
   if (json_out == nullptr || json_cap < 64) return fail(PSF_EINVAL, "json_out missing or too small");
   if ((st = check_device()) != PSF_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  // One representative source per family (its first), contracted from its
-  // own records with every candidate launch shape; fastest wins.
+  // One representative source per tile family (the first that runs dense, else
+  // the first), contracted from its own records with every candidate launch
+  // shape; fastest wins.
   std::vector<Family> fams;
   std::vector<int> rep;
   for (int q = 0; q < n_src; ++q) {
     const Family f = dense_family(h_srcs[q]);
-    if (std::find(fams.begin(), fams.end(), f) == fams.end()) {
+    const size_t at = std::find(fams.begin(), fams.end(), f) - fams.begin();
+    if (at == fams.size()) {
       fams.push_back(f);
       rep.push_back(q);
+    } else if (grid_route(obs, &h_srcs[rep[at]], prec).ml > 0 && grid_route(obs, &h_srcs[q], prec).ml == 0) {
+      rep[at] = q;
     }
   }
   size_t part = 0;
@@ -380,8 +384,9 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
       break;
     }
     double best_ms = 1e30;
-    int best_ipc = kDefaultItemsPerCU, best_flush = kFlushChunks;
-    // a gridded patch has no launch shape to choose: timed once, as it runs
+    // a gridded patch has no launch shape to choose: timed once, as it runs,
+    // its family's entry being what an untuned dense call takes
+    int best_ipc = default_items_per_cu(fams[f]), best_flush = kFlushChunks;
     const PatchPlan own = plan_patch(obs, &src, prec, kTargetWorkgroups);
     const bool gridded = own.grid.ml > 0;
     for (int ipc : kItemsCandidates) {
@@ -400,10 +405,10 @@ int psf_autotune(const psf_obs* obs, int32_t n_src, const psf_src* h_srcs, int p
         const int kp = contraction_prec(prec, a);
         auto launch = [&]() {
           if (!gridded) return launch_patch(kp, a, n_wg, s);
-          UvGridArgs g = grid_args(obs, own.grid, false);
+          UvGridArgs g = grid_args(obs, own.grid, grid_fused(obs));
           g.n_src = 1;
           g.src[0] = grid_src(&src, rec, c, partial, P, nullptr);
-          return launch_grid(kp, g, s);
+          return launch_grid(launch_prec(prec, obs->K, own.sym), g, s);
         };
         if ((e = launch()) != hipSuccess) {  // warm-up
           rc = hip_fail(e, "k_patch launch");
