@@ -232,8 +232,27 @@ UvGridArgs grid_args(const psf_obs* o, const GridPlan& g, bool fused) {
   return a;
 }
 
+// The spreading kernel holds the samples of 1024 time rows at a time and gives
+// each bin a lane, so where bins are long and frequency bins few its lanes
+// idle; and it sums the channels of bins of more than 16 one by one, where
+// k_decorr has a recurrence (from two time rows on).  Measured (us per 129 x 129
+// patch, 2016 baselines; frequency bins x (time x channels) of a bin):
+//              1 x (8 x 1)  1 x (16 x 1)  4 x (32 x 1)  4 x (64 x 1)  8 x (64 x 1)  8 x (128 x 1)
+//   in lanes           128            64           128            64           128             64
+//   fused              139           200           152           241           172            333
+//   records            175           178           164           162           182            276
+//              4 x (16 x 4)  8 x (32 x 4)  8 x (64 x 4)  6 x (10 x 20)  6 x (4 x 20)  6 x (2 x 32)
+//   in lanes           256           256           128            612          1536           3072
+//   fused              179           211           236            405           215            321
+//   records            185           203           184            237           208            680
+// The averages over the observation stand for its bins, whose own sizes are on
+// the device.
 bool grid_fused(const psf_obs* o) {
-  return o->win_t == nullptr && o->win_c == nullptr && !use_wave_bins(view(o));
+  if (o->win_t != nullptr || o->win_c != nullptr || use_wave_bins(view(o)) || o->n_tb < 1) return false;
+  const double nt = static_cast<double>(o->n_bl) * o->n_t / static_cast<double>(o->n_tb);
+  const double nf = static_cast<double>(o->K) / static_cast<double>(o->n_tb), nc = o->n_ch / std::max(nf, 1.0);
+  if (nt > 1024.0 || (nc > 16.0 && nt > 3.0)) return false;
+  return std::floor(1024.0 / nt) * nf >= (nc >= 2.5 ? 192.0 : 96.0);
 }
 
 UvGridSrc grid_src(const psf_src* h_src, const BinRec* rec, const float2* c, void* work, float* P, const double* dir,

@@ -60,7 +60,8 @@ GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec);
 // Fills everything of a gridded launch but its sources.
 UvGridArgs grid_args(const psf_obs* o, const GridPlan& g, bool fused);
 // Whether a gridded patch forms its decorrelation factors while spreading
-// (boxcar averaging, bins of one lane each), without records.
+// (boxcar averaging, bins of one lane each that are not too long), without
+// records.
 bool grid_fused(const psf_obs* o);
 int run_grid_fused(const psf_obs* obs, const psf_src* h_src, const PatchPlan& plan, int prec, void* work, float* P,
                    hipStream_t s, const double* dir, bool norm);

@@ -43,3 +43,30 @@ def test_accuracy_and_range():
         assert _gridded(1 << 18, n, "sr_fp16") and _gridded(1 << 18, n, "mixed_fp16")
         assert not _gridded(1 << 28, n, "plain_bf16") and not _gridded(24575, n, "split_bf16")
     assert not _gridded(1 << 20, 1045, "fp32")  # beyond the largest grid
+
+
+def _fused(n_bl, n_t, n_ch, nt, nc):
+    f = getattr(pk.lib(), "_ZN3psf10grid_fusedEPK7psf_obs")  # psf::grid_fused(const psf_obs*)
+    f.restype = ctypes.c_bool
+    o = pk.PsfObs()
+    o.n_bl, o.n_t, o.n_ch = n_bl, n_t, n_ch
+    o.n_tb = n_bl * -(-n_t // nt)
+    o.K = o.n_tb * -(-n_ch // nc)
+    return f(ctypes.byref(o))
+
+
+# (samples, channels, of a bin; us with the factors formed while spreading, us from records), 2016 baselines
+LONG = [(1440, 1, 4, 1, 88.6, 103.3), (3600, 1, 8, 1, 138.8, 174.6), (3600, 1, 16, 1, 200.5, 178.3),
+        (3600, 1, 32, 1, 204.7, 167.4), (3600, 4, 32, 1, 151.7, 164.0), (3600, 4, 64, 1, 240.7, 162.5),
+        (3600, 16, 16, 4, 178.6, 184.8), (3600, 16, 64, 4, 331.0, 161.9), (3600, 32, 10, 4, 302.5, 334.5),
+        (3600, 32, 64, 4, 236.1, 184.2), (7200, 32, 128, 4, 514.6, 279.3), (3600, 8, 64, 1, 172.3, 181.6),
+        (7200, 8, 128, 1, 332.9, 276.0), (3600, 32, 64, 1, 273.2, 442.5), (7200, 32, 256, 1, 545.9, 683.1),
+        (1800, 128, 32, 8, 187.3, 289.4), (720, 256, 1, 64, 499.9, 1500.2), (1800, 120, 10, 20, 404.7, 237.2),
+        (720, 192, 2, 32, 321.4, 679.5), (600, 64, 10, 32, 110.5, 51.0)]
+
+
+def test_factors_while_spreading_or_before():
+    for n_t, n_ch, nt, nc, fused, records in LONG:
+        n_bl = 276 if n_t == 600 else 2016
+        assert _fused(n_bl, n_t, n_ch, nt, nc) == (fused < records), (n_t, n_ch, nt, nc)
+    assert not _fused(2016, 20000, 2, 1200, 1)  # longer than the kernel's table
