@@ -1242,13 +1242,20 @@ hipError_t launch_grid(int prec, UvGridArgs a, hipStream_t stream) {
   // fewer than 768 bins each, workgroups of 512 (two rounds of 64 bins per
   // wave) instead, the last of which follow the first that are done, or of 256
   // while those leave compute units idle (K = 26k to 76k: 48-50 -> 39-43 us
-  // for 33 to 129 pixels; with 128 bins 39-46).  One span each below 8192 bins per workgroup (K =
+  // for 33 to 129 pixels).  Below that, of 128 bins where 256 leave fewer than
+  // 160 workgroups (K = 27k: 43 -> 36 us for 65 pixels; at 52k instead 36 -> 39),
+  // and, where baselines have fewer than 100 bins, so that successive ones
+  // share few windows, as few as 64 while fewer than 380 workgroups (2016
+  // baselines of 16 bins: 131 -> 58 us; of 32 bins, in 128 each, 79 -> 60).
+  // One span each below 8192 bins per workgroup (K =
   // 5.9M of uneven bins: 195 us against 229 with three levels; six patches of
   // K = 1.45M 1258 against 1356), from there on as many levels as leave the
   // last at least 1024 bins (K = 23.2M, three sources: 1846 us with six levels,
   // 1918 with five, 2150 with one).
   const int resident = 768 / a.n_src;
-  const int least = K * a.n_src < 512 * 256 ? 256 : 512;
+  const int wanted = K < 100 * static_cast<int64_t>(a.o.n_bl) ? 380 : 160;
+  int least = K * a.n_src < 512 * 256 ? 256 : 512;
+  while (least > 64 && least < 512 && K * a.n_src < static_cast<int64_t>(wanted) * least) least /= 2;
   a.n_wg = K / resident < 768 ? static_cast<int>((K + least - 1) / least) : resident;
   a.levels = 1;
   if (K / a.n_wg >= 8 * kLeastSpan)

@@ -181,30 +181,38 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
   return p;
 }
 
-// Which patches run gridded.  Measured (MI355X, us per call, boxcar bins of 3 x
-// 4 samples, 190 baselines over two hours; patch_work at 256 CUs and 2.1 GHz and
-// 20 us, 25 in the symmetric families, follow the dense form within 10% where
-// the two are near each other; at K = 27k, bins of 200 s, the tracks are sparse
-// and the gridded form takes 5 to 12 us more than the rule says):
+// Which patches run gridded.  Measured (MI355X, us per call, both forms in turn;
+// bins of 3 x 4 samples, 190 baselines over two hours):
 //   pixels               33          65         129         200         257         300
 //   split-BF16
-//   K =  27k      26.7 | -   23.7 | 42.6 32.1 | 46.0 44.0 | 61.7 41.4 | 62.7 71.6 | -     dense | gridded
-//   K =  52k   32.7 | 35.7   27.7 | 36.3 36.1 | 37.5 65.7 | 48.9 50.4 | 49.8 116  | 82.0
-//   K = 152k   55.3 | 41.3   38.9 | 41.5 50.9 | 44.3 155  | 52.2 85.6 | 53.1 311  | 76.4
-//   K = 302k   89.2 | 51.6   49.9 | 51.7 73.7 | 49.3 289  | 58.7 140  | 59.7 600  | 74.7
+//   K =  27k      26.9 | -   24.1 | 36.4 32.0 | 38.4 44.1 | -    41.7 | 52.2 71.7 | -     dense | gridded
+//   K =  52k   32.5 | 35.7   27.6 | 36.3 36.0 | 37.4 65.8 | 48.9 50.2 | 49.6 116  | 81.7
+//   K = 152k   55.3 | 41.3   39.0 | 41.5 50.9 | 44.3 155  | 52.2 85.6 | 53.1 311  | 76.4
+//   K = 302k   89.2 | 51.6   49.7 | 51.9 73.7 | 49.3 289  | 58.7 140  | 59.7 600  | 74.7
 //   FP32
-//   K =  27k   34.8 | 42.6   29.5 | 42.7 39.8 | 45.9
-//   K =  52k   46.8 | 35.9   33.9 | 36.0 47.4 | 37.6
-//   K = 152k   102  | 42.1   48.7 | 42.3 85.0 | 45.2
-// FP32 takes the shorter.  The split forms run gridded up to `lead` before the
-// times cross.  In the symmetric families, where the dense form's advantage is
-// at most 19 us, because split products of so few bins leave it 1.4 to 2.6e-7
-// off (1.2 times the 2.5e-7 of 2 sum |c| that the gridded form is held to at K =
-// 28k, 129 x 140), gridded 0.4 to 1.9e-7; FP16 because the dense form's columns c b
-// are FP16 as they are and overflow beyond |c| = 65504, while the gridded form
-// scales them.  Below 24576 bins every call is dense.  PSF_PLAIN_BF16, a
-// negative control, stays dense; the mixed and stochastic arithmetics exist in
-// the gridded form only.
+//   K =  27k   34.7 | 37.6   29.6 | 36.4 40.0 | 38.4
+//   K =  52k   47.2 | 35.8   33.8 | 36.0 47.6 | 37.6
+//   K = 152k   102  | 42.1   48.6 | 42.3 85.0 | 45.2
+// Many baselines of few bins each share few windows and tiles (split-BF16):
+//   pixels                    65          129          200
+//   2016 baselines of 16  26.4 | 57.9  32.8 | 63.3  49.9 | -      dense | gridded
+//                  of 32  31.5 | 59.8  39.9 | 65.0  77.5 | 101
+//                  of 64  39.4 | 59.2  49.1 | 66.0   133 | 72 to 108
+//                 of 128  50.7 | 61.5  72.0 | 62.0   251 | 70 to 87
+//    780 baselines of 32  24.2 | 41.8  30.4 | 45.5  42.9 | -
+//                  of 64  29.8 | 41.1  36.7 | 42.9  64.5 | 53 to 77
+//                 of 128  36.2 | 42.2  43.9 | 43.8   109 | 51 to 66
+// The dense form follows patch_work at 256 CUs and 2.1 GHz and 18 us, 25 in the
+// symmetric families; the gridded one 32 us, 60 ps per bin, 50 ps per cell and a
+// share for the baselines.  FP32, and split-BF16 but in the symmetric families,
+// take the shorter by that.  Split-BF16 in the symmetric families runs gridded
+// from 14 us before: of so few bins its dense form is 1.4 to 2.6e-7 off (at K =
+// 28k, 129 x 140 pixels, 1.2 times the 2.5e-7 of 2 sum |c| that the gridded form
+// is held to), gridded 0.4 to 1.9e-7.  Split-FP16 runs gridded by a line 25 to 35
+// us further, because the dense form's columns c b are FP16 as they are and
+// overflow beyond |c| = 65504, while the gridded form scales them.  Below 24576
+// bins every call is dense.  PSF_PLAIN_BF16, a negative control, stays dense; the
+// mixed and stochastic arithmetics exist in the gridded form only.
 GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec) {
   constexpr int64_t kMinBins = 24576;
   GridPlan g;
@@ -213,10 +221,15 @@ GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec) {
   if (kp == PSF_PLAIN_BF16 || o->K < kMinBins) return g;
   const int ml = grid_axis(s->nl), mm = grid_axis(s->nm);
   if (ml == 0 || mm == 0) return g;
-  const double dense = (sym ? 25e-6 : 20e-6) + patch_work(o, s, kp) / (kTargetWorkgroups * 2.1e9);
-  const double grid = 35e-6 + static_cast<double>(o->K) * 0.06e-9 + static_cast<double>(ml) * mm * 0.05e-9;
-  const double lead = kp == PSF_FP32 ? 0.0 : sym ? 25e-6 : kp == PSF_SPLIT_FP16 ? 10e-6 : 0.0;
-  if (dense + lead <= grid && kp != PSF_MIXED_FP16 && kp != PSF_SR_FP16) return g;
+  const double cells = static_cast<double>(ml) * mm, per_bl = static_cast<double>(o->K) / o->n_bl;
+  const double work = patch_work(o, s, kp) / (kTargetWorkgroups * 2.1e9);
+  if (kp == PSF_SPLIT_FP16) {
+    if ((sym ? 60e-6 : 40e-6) + work <= 45e-6 + o->K * 0.06e-9 + cells * 0.05e-9) return g;
+  } else if (kp == PSF_FP32 || kp == PSF_SPLIT_BF16) {
+    const double sparse = 0.012e-6 * o->n_bl * std::min(1.0, 64.0 / per_bl) * std::sqrt(std::max(1.0, cells / 65536.0));
+    const double lead = kp == PSF_SPLIT_BF16 && sym ? 14e-6 : 0.0;
+    if ((sym ? 25e-6 : 18e-6) + work + lead <= 32e-6 + sparse + o->K * 0.06e-9 + cells * 0.05e-9) return g;
+  }
   g.ml = ml;
   g.mm = mm;
   return g;

@@ -1,7 +1,8 @@
-"""Which patches take the gridded form: the host's rule against the measured
-times of both (MI355X, us): the shorter one in FP32 and, but for the symmetric
-families, in split-BF16; gridded in the other split forms where the two are
-within 25 (symmetric families) or 10 us."""
+"""Which patches take the gridded form, and where its factors are formed: the
+host's rules against the measured times (MI355X, us): the shorter form in FP32
+and, but for the symmetric families, in split-BF16; gridded also up to 14 us
+(split-BF16 in the symmetric families) or 25 to 35 us (split-FP16) before it is
+the shorter."""
 import ctypes
 
 import pytest
@@ -11,26 +12,36 @@ import paper_2009_07010_amd as pk
 SYMBOL = "_ZN3psf10grid_routeEPK7psf_obsPK7psf_srci"  # psf::grid_route(const psf_obs*, const psf_src*, int)
 
 
-def _gridded(K, n, prec):
+def _gridded(K, n, prec, n_bl=190):
     f = getattr(pk.lib(), SYMBOL)
     f.restype = ctypes.c_uint64  # {int ml, mm}, both 0: dense
     o, s = pk.PsfObs(), pk.PsfSrc()
-    o.K, o.n_bl, o.n_t, o.n_ch, s.nl, s.nm = K, 190, 1, 1, n, n
+    o.K, o.n_bl, o.n_t, o.n_ch, s.nl, s.nm = K, n_bl, 1, 1, n, n
     return f(ctypes.byref(o), ctypes.byref(s), pk.PRECISIONS[prec]) != 0
 
 
 # (pixels, K, dense us, gridded us) where they differ by more than 5%
-TIMES = {"fp32": [(33, 27360, 34.8, 42.6), (65, 27360, 29.5, 42.7), (129, 27360, 39.8, 45.9), (33, 51680, 46.8, 35.9),
-                  (65, 51680, 33.9, 36.0), (129, 51680, 47.4, 37.6), (33, 152000, 101.6, 42.1), (65, 152000, 48.7, 42.3),
-                  (129, 152000, 85.0, 45.2), (65, 302480, 71.1, 52.4)],
-         "split_bf16": [(33, 51680, 32.7, 35.7), (33, 152000, 55.3, 41.3), (200, 27360, 44.0, 61.7),
-                        (200, 51680, 65.7, 48.9), (300, 51680, 116.2, 82.0)]}
+TIMES = {"fp32": [(33, 27360, 34.7, 37.6), (65, 27360, 29.6, 36.4), (33, 51680, 47.2, 35.8), (65, 51680, 33.8, 36.0),
+                  (129, 51680, 47.6, 37.6), (33, 152000, 101.6, 42.1), (65, 152000, 48.6, 42.3), (129, 152000, 85.0, 45.2),
+                  (65, 302480, 71.1, 52.4)],
+         "split_bf16": [(33, 51680, 32.5, 35.7), (33, 152000, 55.3, 41.3), (200, 51680, 65.8, 48.9), (300, 51680, 116.1, 81.7)]}
+# (pixels, baselines, bins of each, dense us, gridded us), split-BF16
+SPARSE = [(65, 2016, 16, 26.4, 57.9), (129, 2016, 16, 32.8, 63.3), (65, 2016, 32, 31.5, 59.8), (129, 2016, 32, 39.9, 65.0),
+          (200, 2016, 32, 77.5, 101.0), (65, 2016, 64, 39.4, 59.2), (129, 2016, 64, 49.1, 66.0), (200, 2016, 64, 133.0, 108.3),
+          (129, 2016, 128, 72.0, 62.0), (200, 2016, 128, 251.0, 86.7), (65, 2016, 256, 83.8, 71.0), (129, 2016, 256, 125.1, 73.2),
+          (65, 780, 32, 24.2, 41.8), (129, 780, 32, 30.4, 45.5), (65, 780, 64, 29.8, 41.1), (129, 780, 64, 36.7, 42.9),
+          (200, 780, 128, 108.5, 65.5), (129, 780, 256, 62.8, 50.5), (200, 780, 256, 200.3, 52.9)]
 
 
 @pytest.mark.parametrize("prec", sorted(TIMES))
 def test_the_shorter_form(prec):
     for n, K, dense, grid in TIMES[prec]:
         assert _gridded(K, n, prec) == (grid < dense), (n, K)
+
+
+def test_many_baselines_of_few_bins():
+    for n, n_bl, bins, dense, grid in SPARSE:
+        assert _gridded(n_bl * bins, n, "split_bf16", n_bl) == (grid < dense), (n, n_bl, bins)
 
 
 def test_accuracy_and_range():
