@@ -37,8 +37,8 @@ COMMON = [
 EXTRA = {
     "k_patch.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
     # the polynomials' FP64 coefficients, 52 registers, are not hoisted out of the
-    # sums' loops: the windowed kernel would spill at its four waves per SIMD
-    "k_decorr.hip": ["-mllvm", "-disable-machine-licm"],
+    # sums' loops: the kernel would spill at its four waves per SIMD
+    "k_decorr_window.hip": ["-mllvm", "-disable-machine-licm"],
 }
 
 

@@ -1,7 +1,7 @@
 // Reverse-mode adjoint of the patch for patches of up to 288 columns (and
 // rows within 16 ranges that fit in LDS) in the FP32, split-BF16 and
 // split-FP16 forms.  The derivatives are those of the
-// five-patch form in psf_backward.hip (derivation in k_decorr.hip),
+// five-patch form in psf_backward.hip (derivation in k_decorr_bin.hpp),
 // regrouped per visibility:
 //   dL/dl0 = 2 Re sum_k [e0_k H_k + e2_k Hx_k + e3_k Hy_k]
 //   dL/dm0 = 2 Re sum_k [e1_k H_k + e3_k Hx_k + e4_k Hy_k]

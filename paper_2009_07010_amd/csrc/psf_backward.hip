@@ -1,7 +1,7 @@
 // Adjoint of the patch with respect to the source direction (grid fixed).
 //
 // With G = dLoss/dP and the five coefficient vectors e0..e4 that k_decorr
-// forms per bin (derivation in k_decorr.hip), write Q[e] for the patch of
+// forms per bin (derivation in k_decorr_bin.hpp), write Q[e] for the patch of
 // the same form as P with c_k replaced by e_k.  Then
 //   dLoss/dl0 = sum_ij G_ij (Q0 + x_i Q2 + y_j Q3)_ij
 //   dLoss/dm0 = sum_ij G_ij (Q1 + x_i Q3 + y_j Q4)_ij

@@ -93,7 +93,7 @@ constexpr int kPatchChunkSym = 32;  // visibilities per chunk of the symmetric f
 constexpr double kAdjointScale = 1.0 / 4096.0;
 
 // coef_out (optional, [5][K]): the adjoint coefficient vectors e0..e4 (see
-// k_decorr.hip) times kAdjointScale; needs D_in == nullptr.
+// k_decorr_bin.hpp) times kAdjointScale; needs D_in == nullptr.
 // dir (optional): device memory laid out as psf_src (l0, m0, l_first,
 // m_first, dl, dm) from which the direction and cells are read at run time
 // instead of l0, m0, dl, dm.
