@@ -1211,7 +1211,7 @@ int grid_axis(int n) {
 
 size_t grid_bytes(const GridPlan& g, int nm) {
   return (static_cast<size_t>(g.ml) * g.mm + static_cast<size_t>(g.ml) * nm) * sizeof(double2) +
-         sizeof(UvGridState);
+         sizeof(UvGridState) + kGridAlign;
 }
 
 template <int PREC>

@@ -273,7 +273,7 @@ UvGridSrc grid_src(const psf_src* h_src, const BinRec* rec, const float2* c, voi
   UvGridSrc s;
   s.rec = rec;
   s.c = c;
-  s.work = static_cast<uint8_t*>(work);
+  s.work = reinterpret_cast<uint8_t*>(align_up(reinterpret_cast<uintptr_t>(work), kGridAlign));
   s.P = P;
   s.peak = peak;
   s.norm = 0;

@@ -17,7 +17,10 @@ struct GridPlan {
 // 32) that oversamples it by 1.96 or more; 0 if that exceeds kGridMaxAxis.
 constexpr int kGridMaxAxis = 2048;
 int grid_axis(int n);
-// Bytes of one source's grid, half-transformed grid and state.
+// Bytes of one source's grid, half-transformed grid and state, and what
+// aligning them takes: the cells are summed by 64-bit atomics, while a
+// caller's workspace may begin anywhere.
+constexpr size_t kGridAlign = 16;
 size_t grid_bytes(const GridPlan& g, int nm);
 
 struct UvGridScale;  // what scales a source's fixed point (k_grid.hip)
@@ -28,7 +31,7 @@ struct UvGridScale;  // what scales a source's fixed point (k_grid.hip)
 struct UvGridSrc {
   const BinRec* rec;
   const float2* c;
-  uint8_t* work;  // grid_bytes: cells, half-transformed grid, state
+  uint8_t* work;  // cells, half-transformed grid, state (aligned to kGridAlign, within grid_bytes)
   float* P;
   const double* peak;  // not fused: see SrcPlan
   const double* dir;
