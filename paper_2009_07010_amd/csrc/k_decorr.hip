@@ -90,7 +90,7 @@ bool use_wave_bins(const ObsView& o) {
 
 // The kernel without derivatives: wide where there are channels enough, with
 // windows only from 128 samples per bin on average (the bins' own sizes are on
-// the device), since that form takes 126 registers to the other's 68.
+// the device), since that form takes 126 registers to the other's 66.
 static decltype(&k_decorr<false, kNotWide>) decorr_kernel(const ObsView& o) {
   if (o.n_ch < kEvenBin) return k_decorr<false, kNotWide>;
   if (o.win_t == nullptr && o.win_c == nullptr) return k_decorr<false, kWideBoxcar>;
@@ -101,7 +101,7 @@ static decltype(&k_decorr<false, kNotWide>) decorr_kernel(const ObsView& o) {
 // Without derivatives also for observations of few bins: one wave per bin
 // where all of them run at once and a bin has samples for a quarter of the
 // lanes (420 bins of 30 samples: 8.5 us with one lane each, whose loads follow
-// one another, 4.5 with a wave each).
+// one another, 5.6 with a wave each).
 static bool few_bins(const ObsView& o) {
   const double samples = static_cast<double>(o.n_bl) * o.n_t * o.n_ch;
   return use_wave_bins(o) || (o.K > 0 && o.K <= 8192 && samples >= 16.0 * static_cast<double>(o.K));

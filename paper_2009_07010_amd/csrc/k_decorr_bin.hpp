@@ -321,8 +321,8 @@ __device__ __forceinline__ void finish_bin(const ObsView& o, int64_t k, double l
 // two doubles) when dirs is given, and whose records start y * rec_stride
 // elements into rec_out and c_out.
 //
-// wide: wide_sums, for observations that may hold bins it is good for (54
-// registers for boxcar averaging, 126 with windows; bin_sums alone takes 68).
+// wide: wide_sums, for observations that may hold bins it is good for (72
+// registers for boxcar averaging, 126 with windows; bin_sums alone takes 66).
 // Bins of 20 x 40 samples, K = 2.2M: 1087 -> 331 us, with windows 1574 -> 507
 // (arithmetic: 2 or 3 FP64 operations per sample and about 100 per row).
 // Nothing is spilled: the windowed kernel held 44 registers in scratch memory,

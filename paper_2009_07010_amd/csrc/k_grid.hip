@@ -38,13 +38,13 @@
 // every cell: finer than the FP32 sums of a window whatever the weights'
 // spread, so what remains is those sums' own rounding.
 //
-// FUSED, the boxcar case, forms D_k in the same kernel: bins leave no records
-// in memory (40 bytes each way, 10.6 GB per source at K = 265M).
+// FUSED, the boxcar case but for long bins, forms D_k in the same kernel: bins
+// leave no records in memory (40 bytes each way, 10.6 GB per source at K = 265M).
 //
 // Measured (one 257 x 257 patch, K = 5.8M in bins of 10 x 4 samples,
-// stochastic FP16): 307 us per call, spreading 275, against 1400 us of the
-// dense contraction it replaced (FP32 345 against 7540); per source at K =
-// 265M of baseline-dependent bins 4.4 ms against 37.  The workgroups' time at
+// stochastic FP16): 302 us per call, spreading 280, against 1400 us of the
+// dense contraction it replaced (FP32 337 against 7540); per source at K =
+// 265M of baseline-dependent bins 4.3 ms against 37.  The workgroups' time at
 // K = 5.8M: half is the set-up of chunks and their tables (latency), a third the
 // samples' factors, a sixth staging and contraction; at one sample per bin
 // (K = 116M) staging and contraction are 60% and the factors 30%, bound by
@@ -492,6 +492,7 @@ __device__ __forceinline__ g_f32x4 contract_frags(const Frags& a, const Frags& b
   return acc;
 }
 
+// The 32-bit finaliser of MurmurHash3.
 __device__ __forceinline__ uint32_t mix_word(uint32_t h) {
   h ^= h >> 16;
   h *= 0x85EBCA6Bu;

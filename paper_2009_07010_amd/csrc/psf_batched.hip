@@ -1,15 +1,18 @@
 // Many sources in few launches: the batched path and its autotuner.
 //
-// Sources are grouped by tile family (the compiled tile shapes their patch
-// size selects), in groups of at most kMaxBatch whose per-bin records fit
-// a fixed budget.  Per group:
-//   * one k_decorr launch per source writes that source's records (u', v',
-//     W D) into its slot, reading the direction from the caller's device
-//     source array, so a captured graph replays with new directions;
-//   * one persistent contraction launch runs every (source, tile, k-slice)
-//     work item of the group, items sized to cost alike, workgroup w taking
-//     items w, w + G, w + 2G, ... (static, no atomics, nothing to reset);
-//   * one finalise launch writes every patch of the group into P_all.
+// Sources are grouped by form and size: gridded ones by their grid, dense ones
+// by tile family (the compiled tile shapes their patch size selects), in
+// groups of at most kMaxBatch whose grids or per-bin records fit a fixed
+// budget.  Directions are read from the caller's device source array, so a
+// captured graph replays with new ones.  Per group:
+//   * gridded, factors formed while spreading (boxcar bins that are not too
+//     long): the four launches of k_grid.hip over the group's sources;
+//   * otherwise one k_decorr launch per source writes that source's records
+//     (u', v', W D) into its slot; then the gridded form's four launches, or
+//   * dense: one persistent contraction launch runs every (source, tile,
+//     k-slice) work item of the group, items sized to cost alike, workgroup w
+//     taking items w, w + G, w + 2G, ... (static, no atomics, nothing to
+//     reset), and one finalise launch writes every patch of the group.
 // Every launch is asynchronous on the caller's stream with no allocation,
 // memset or host synchronisation, so the whole call can be captured into a
 // HIP graph.
@@ -17,6 +20,7 @@
 // Launch shapes per tile family (work items per compute unit, first-level
 // accumulation run) come from a tuning table that psf_autotune writes by
 // timing candidates on the caller's data; without a table, defaults apply.
+// Gridded sources have no launch shape to choose.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
