@@ -202,6 +202,16 @@ PatchPlan plan_patch_items(const psf_obs* o, const psf_src* s, int prec, double 
 //    780 baselines of 32  24.2 | 41.8  30.4 | 45.5  42.9 | -
 //                  of 64  29.8 | 41.1  36.7 | 42.9  64.5 | 53 to 77
 //                 of 128  36.2 | 42.2  43.9 | 43.8   109 | 51 to 66
+// Uneven bins (baseline-dependent averaging of up to 64 x 8 samples), which the
+// dense form's factors wait for and the spreading kernel's spans even out, of
+// K bins and n baselines (counts of time and frequency bins that do not divide
+// evenly tell them):
+//   pixels                        33           100          200
+//   K =  55k, n = 276     50.2 | 42.9  52.1 | 46.1  85.0 | 50.9   dense | gridded
+//   K =  61k, n = 435     52.3 | 55.8  54.6 | 58.2  92.0 | 63.3
+//   K =  78k, n = 780     55.1 | 53.3  57.2 | 57.7   107 | 62.8
+//   K = 162k, n = 2016    76.6 | 87.2  78.8 | 91.2   184 | 98.3
+//   K = 185k, n = 276     83.0 | 49.7  85.1 | 51.3   205 | 57.2
 // The dense form follows patch_work at 256 CUs and 2.1 GHz and 18 us, 25 in the
 // symmetric families; the gridded one 32 us, 60 ps per bin, 50 ps per cell and a
 // share for the baselines.  FP32, and split-BF16 but in the symmetric families,
@@ -226,8 +236,10 @@ GridPlan grid_route(const psf_obs* o, const psf_src* s, int prec) {
   if (kp == PSF_SPLIT_FP16) {
     if ((sym ? 60e-6 : 40e-6) + work <= 45e-6 + o->K * 0.06e-9 + cells * 0.05e-9) return g;
   } else if (kp == PSF_FP32 || kp == PSF_SPLIT_BF16) {
-    const double sparse = 0.012e-6 * o->n_bl * std::min(1.0, 64.0 / per_bl) * std::sqrt(std::max(1.0, cells / 65536.0));
-    const double lead = kp == PSF_SPLIT_BF16 && sym ? 14e-6 : 0.0;
+    const bool uneven = o->n_tb < 1 || o->n_tb % o->n_bl != 0 || o->K % o->n_tb != 0;
+    const double sparse = (uneven ? 0.024e-6 : 0.012e-6) * o->n_bl * std::min(1.0, 64.0 / per_bl) *
+                          std::sqrt(std::max(1.0, cells / 65536.0));
+    const double lead = (kp == PSF_SPLIT_BF16 && sym ? 14e-6 : 0.0) + (uneven ? 11e-6 : 0.0);
     if ((sym ? 25e-6 : 18e-6) + work + lead <= 32e-6 + sparse + o->K * 0.06e-9 + cells * 0.05e-9) return g;
   }
   g.ml = ml;

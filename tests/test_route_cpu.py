@@ -12,11 +12,14 @@ import paper_2009_07010_amd as pk
 SYMBOL = "_ZN3psf10grid_routeEPK7psf_obsPK7psf_srci"  # psf::grid_route(const psf_obs*, const psf_src*, int)
 
 
-def _gridded(K, n, prec, n_bl=190):
+def _gridded(K, n, prec, n_bl=190, n_tb=None):
     f = getattr(pk.lib(), SYMBOL)
     f.restype = ctypes.c_uint64  # {int ml, mm}, both 0: dense
     o, s = pk.PsfObs(), pk.PsfSrc()
     o.K, o.n_bl, o.n_t, o.n_ch, s.nl, s.nm = K, n_bl, 1, 1, n, n
+    o.n_tb = n_tb or (K if K % n_bl == 0 else n_bl)  # time bins over all baselines; as if all bins were alike
+    if n_tb is None:
+        o.K -= o.K % o.n_tb
     return f(ctypes.byref(o), ctypes.byref(s), pk.PRECISIONS[prec]) != 0
 
 
@@ -42,6 +45,19 @@ def test_the_shorter_form(prec):
 def test_many_baselines_of_few_bins():
     for n, n_bl, bins, dense, grid in SPARSE:
         assert _gridded(n_bl * bins, n, "split_bf16", n_bl) == (grid < dense), (n, n_bl, bins)
+
+
+# (pixels, K, baselines, time bins over all of them, dense us, gridded us) where they differ by more than 8%: uneven bins
+UNEVEN = [(33, 54611, 276, 54611, 50.2, 42.9), (100, 54611, 276, 54611, 52.1, 46.1), (200, 54611, 276, 54611, 85.0, 50.9),
+          (200, 43239, 120, 30858, 72.4, 54.9), (33, 116454, 276, 43112, 63.6, 46.4), (200, 116454, 276, 43112, 138.9, 55.8),
+          (200, 61304, 435, 39704, 92.0, 63.3), (200, 78471, 780, 78471, 106.6, 62.8), (33, 184686, 276, 129186, 83.0, 49.7),
+          (100, 184686, 276, 129186, 85.1, 51.3), (33, 162301, 2016, 162301, 76.6, 87.2), (100, 162301, 2016, 162301, 78.8, 91.2),
+          (65, 162301, 2016, 162301, 59.4, 88.0), (200, 162301, 2016, 162301, 183.5, 98.3)]
+
+
+def test_uneven_bins():
+    for n, K, n_bl, n_tb, dense, grid in UNEVEN:
+        assert _gridded(K, n, "split_bf16", n_bl, n_tb) == (grid < dense), (n, K, n_bl)
 
 
 def test_accuracy_and_range():
