@@ -68,10 +68,8 @@ typedef __attribute__((address_space(3))) uint8_t g_lds;
 constexpr int kW = 9;             // taps per axis
 constexpr int kWin = 16;          // cells per axis of a window
 constexpr int kSlack = kWin - kW; // a window holds anchors 0 .. kSlack past its origin
-constexpr int kTileCells = 1024;  // cells of a workgroup's LDS tile (16 bytes each)
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kTileSide = 32;     // a tile grows to about this side when its chunk leaves room
 constexpr int kChunkBins = 1 << 14;  // bins of a chunk, at most (one row of frequency bins may be longer)
 constexpr int kTabRows = 1024;    // samples of a chunk whose projections sit in LDS
 constexpr int kTabFreq = 512;     // frequency bins whose centre frequencies do
@@ -88,7 +86,6 @@ constexpr int kMargin = 1;        // cells added around a tile's sampled extent
 // eight rows' 16-byte reads fall on distinct banks; FP32: one plane, rows of
 // 256 + 16 bytes.
 constexpr int kRow16 = 144, kPlane16 = 16 * kRow16, kRow32 = 272;
-constexpr int kStage = 5120;  // bytes per wave: the operand, up to a whole number of 16-byte stores per lane
 
 // The taps' polynomials times kTapScale: tap r and tap 8 - r are
 // E_r(f^2) +- f O_r(f^2), f = position - nearest cell in [-1/2, 1/2].
@@ -423,14 +420,33 @@ __device__ __forceinline__ void stage_taps(g_lds* st, int row0, int lane, const 
   }
 }
 
+// Bytes of a staged operand, and of a wave's stage.
+constexpr int operand_bytes(Mode m) { return m == kMSR ? kPlane16 : m == kM32 ? 16 * kRow32 : 2 * kPlane16; }
+constexpr int stage_bytes(Mode a, Mode b) { return operand_bytes(a) > operand_bytes(b) ? operand_bytes(a) : operand_bytes(b); }
+
 template <Mode M>
 __device__ __forceinline__ void stage_clear(g_lds* st, int lane) {
   typedef __attribute__((address_space(3))) g_u32x4 lds_u32x4;
-  constexpr int n = M == kMSR ? kPlane16 : M == kM32 ? 16 * kRow32 : 2 * kPlane16;
-  static_assert((n + 1023) / 1024 * 1024 <= kStage, "the stage holds the operand");
+  constexpr int n = operand_bytes(M), whole = n / 1024;
 #pragma unroll
-  for (int q = 0; q < (n + 1023) / 1024; ++q)
+  for (int q = 0; q < whole; ++q)
     *reinterpret_cast<lds_u32x4*>(st + q * 1024 + lane * 16) = g_u32x4{0, 0, 0, 0};
+  if (lane < n % 1024 / 16) *reinterpret_cast<lds_u32x4*>(st + whole * 1024 + lane * 16) = g_u32x4{0, 0, 0, 0};
+}
+
+// Cells of a workgroup's LDS tile (16 bytes each): what the stages and tables
+// leave of a third of a compute unit's LDS (160 KiB in pieces of 1280 bytes).
+// Fast tracks, which leave a tile soon, are 3 to 7% slower with 1024.
+constexpr int tile_cells(Mode a, Mode b, bool fused) {
+  const int used = kWaves * stage_bytes(a, b) + (fused ? (kTabRows + 2 * kTabFreq) * 8 : 24) + 16;
+  const int n = (42 * 1280 - used) / 16 / 16 * 16;
+  return n < 2048 ? n : 2048;
+}
+// The side to which a tile grows when its chunk leaves room.
+constexpr int tile_side(int cells) {
+  int n = 16;
+  while ((n + 1) * (n + 1) <= cells) ++n;
+  return n;
 }
 
 // A wave's LDS operations run in order; this keeps the compiler's order too.
@@ -760,6 +776,7 @@ __device__ __forceinline__ void lds_barrier() {
 template <int PREC, bool FUSED>
 __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
   constexpr Mode MA = row_mode(PREC), MB = col_mode(PREC);
+  constexpr int kTileCells = tile_cells(MA, MB, FUSED), kTileSide = tile_side(kTileCells), kStage = stage_bytes(MA, MB);
   __shared__ unsigned long long tre[kTileCells], tim[kTileCells];
   __shared__ __attribute__((aligned(16))) uint8_t stage_raw[kWaves * kStage];
   __shared__ double tab[FUSED ? kTabRows : 1], tabnu[FUSED ? kTabFreq : 1], tabh[FUSED ? kTabFreq : 1];
@@ -1052,7 +1069,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_grid_spread(UvGridArgs a) {
           if (MA == kMBF16 || MA == kMFP16)
 #pragma unroll
             for (int r = 0; r < kW; ++r) asm volatile("" : "+v"(tx[r]));
-          if (MB == kMBF16 || MB == kMFP16) asm volatile("" : "+v"(c.re), "+v"(c.im));
+          if (MB != kM32) asm volatile("" : "+v"(c.re), "+v"(c.im));
           ++run;
           const int dx = wrap(ax - wx, a.ml), dy = wrap(ay - wy, a.mm);
           const bool go = ((wait >> lane) & 1) != 0 && dx <= kSlack && dy <= kSlack;
