@@ -34,7 +34,7 @@ namespace psf {
 namespace {
 
 constexpr size_t kRecordBudget = size_t(16) << 30;  // bytes of per-bin records per group
-constexpr size_t kGridBudget = size_t(1) << 30;     // bytes of grids per group of the fused gridded form
+constexpr size_t kGridBudget = size_t(1) << 30;     // bytes of grids per group
 constexpr int kComputeUnits = 256;                  // MI355X: one contraction workgroup per CU
 constexpr int kDefaultItemsPerCU = 2;
 const int kFlushCandidates[] = {32, 64, 128};
@@ -138,14 +138,15 @@ struct Group {
 };
 
 // Sources per group: at most kMaxBatch whose per-bin records (dense form, or
-// gridded from records) or grids fit the budgets.
+// gridded from records) and grids fit the budgets.
 int group_capacity(const psf_obs* o, const Family& f) {
-  if (f.ml > 0 && grid_fused(o)) {
-    const size_t g = grid_bytes({f.ml, f.mm}, f.mm);
-    return static_cast<int>(std::max<size_t>(1, std::min<size_t>(kMaxBatch, kGridBudget / g)));
+  size_t n = kMaxBatch;
+  if (f.ml > 0) n = std::min(n, kGridBudget / grid_bytes({f.ml, f.mm}, f.mm));
+  if (f.ml == 0 || !grid_fused(o)) {
+    const size_t rec = static_cast<size_t>(std::max<int64_t>(o->K, 1)) * (sizeof(BinRec) + sizeof(float2));
+    n = std::min(n, kRecordBudget / rec);
   }
-  const size_t rec = static_cast<size_t>(std::max<int64_t>(o->K, 1)) * (sizeof(BinRec) + sizeof(float2));
-  return static_cast<int>(std::max<size_t>(1, std::min<size_t>(kMaxBatch, kRecordBudget / rec)));
+  return static_cast<int>(std::max<size_t>(1, n));
 }
 
 std::vector<Group> make_groups(const psf_obs* o, int n_src, const psf_src* h, int prec) {

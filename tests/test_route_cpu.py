@@ -92,6 +92,18 @@ LONG = [(1440, 1, 4, 1, 88.6, 103.3), (3600, 1, 8, 1, 138.8, 174.6), (3600, 1, 1
         (720, 192, 2, 32, 321.4, 679.5), (600, 64, 10, 32, 110.5, 51.0)]
 
 
+def test_a_groups_grids_are_bounded():
+    """Sixteen large windowed patches (records and grids): at most 1 GiB of
+    grids at a time beside 16 GiB of records."""
+    fake = 0x1000
+    o = pk.PsfObs(n_bl=190, n_t=1600, n_ch=16, reserved=0, K=190 * 533 * 4, n_tb=190 * 533, uvw_m=fake, freq_hz=fake, bl_bin=fake,
+                  bl_koff=fake, bl_tboff=fake, uvw_c_m=fake, W=fake, win_t=fake)
+    srcs = (pk.PsfSrc * 16)(*[pk.PsfSrc(l0=0.01, m0=0.02, l_first=0.0, m_first=0.0, dl=1e-5, dm=1e-5, nl=1000, nm=1000,
+                                        out_off=q * 1000000) for q in range(16)])
+    assert _gridded(o.K, 1000, "fp32")
+    assert pk.psf_workspace_bytes(o, srcs, "fp32") <= 16 * 40 * (o.K + 64) + (1 << 30) + (1 << 22)
+
+
 def test_factors_while_spreading_or_before():
     for n_t, n_ch, nt, nc, fused, records in LONG:
         n_bl = 276 if n_t == 600 else 2016
