@@ -218,10 +218,10 @@ int psf_patch(const psf_obs* obs, const psf_src* h_src, const float* D, int prec
 
 /* Many sources per call [section 3.3: one PSF per source direction].
  * Sources are grouped by form and size (grid or tile family), in groups of
- * at most 16.  Gridded sources (boxcar averaging, bins not too long) share
- * four launches per group: the decorrelation factors are formed while
- * spreading, and the workspace holds one group's grids.  Otherwise a group's per-bin records
- * fit 16 GiB: each source gets K records of 40 bytes (u', v' in FP64, the
+ * at most 16, of gridded ones at most 1 GiB of grids.  Gridded sources
+ * (boxcar averaging, bins not too long) share four launches per group: the
+ * decorrelation factors are formed while spreading, and the workspace holds
+ * one group's grids.  Otherwise a group's per-bin records also fit 16 GiB: each source gets K records of 40 bytes (u', v' in FP64, the
  * 16-pixel phase steps of both axes, W D), written by one decorrelation
  * launch per source; one persistent contraction launch (or the gridded
  * form's four) then runs the group, and one finalise launch writes its
